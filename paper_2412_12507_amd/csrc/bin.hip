@@ -19,18 +19,20 @@
 //   K4 bin_scatter_kernel   each block writes its pairs' 64-bit keys (depth
 //                           bits << 32 | entry id) at its offsets in the lists
 //   K5 tile_sort_*_kernel   per list, in LDS: a bucket sort on the highest
-//                           bits that vary within it with a direct rank
-//                           count inside each bucket; one wave per list
-//                           below 1024 entries, 256 threads up to 4095, 1024
-//                           threads beyond (cutting lists over 16384 into
-//                           runs first); lists with a large bucket take a
-//                           stable LSD radix sort instead
+//                           bits of the distance from its nearest key, with a
+//                           direct rank count inside each bucket; one wave per
+//                           list below 1024 entries, 256 threads up to 4095,
+//                           1024 threads beyond (cutting lists over 16384 into
+//                           runs first); lists with a large bucket go to a
+//                           sort with buckets dealt out by need, and from
+//                           there, if need be, to a stable LSD radix sort
 // Nothing needs a device-wide atomic per pair or per touched tile: blocks on
 // different XCDs meet only in the count matrix, whose columns K2 scans.
 // The (depth bits, id) key orders exactly as a full (tile, depth, id) sort
 // would: depths are non-negative, so their bits order as the floats do.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 
@@ -800,18 +802,32 @@ __device__ __forceinline__ void sort_list_chunked(unsigned long long* __restrict
   }
 }
 
-// Bucket sort of one list, the common path.  The keys of a list agree on
-// every bit above the highest one that varies within it, so the next db
-// bits from there down, taken as a digit, order the keys (coarsely) as the
-// keys themselves do.  The keys are counted per digit, moved into their
-// digit's bucket in LDS (in any order inside it), and each key's place in
-// the list is its bucket's start plus the number of keys of its bucket below
-// it: a direct comparison of the whole (depth, id) keys, so equal depths
-// need no second step.  db grows with the list: depths inside a tile bunch
-// up, so the buckets need to be much finer than L to stay small.  When a
-// bucket holds more than kBucketMax keys (the comparisons would cost more
-// than a radix sort) the sort gives up before touching ids, and the list
-// goes to the radix sort.
+// Bucket sort of one list, the common path.  A key's digit is the top db bits
+// of its depth's distance from the list's nearest depth, in the depths' bit
+// patterns and over the bits of the list's range, which orders the keys
+// (coarsely) as the keys themselves do.  The keys are counted per digit, moved
+// into their digit's bucket in LDS (in any order inside it), and each key's
+// place in the list is its bucket's start plus the number of keys of its
+// bucket below it: a direct comparison of the whole (depth, id) keys, so equal
+// depths need no second step.  db grows with the list: depths inside a tile
+// bunch up, so the buckets need to be much finer than L to stay small.  The
+// digit is taken of the distance and not of the depth, because a list that
+// straddles a power of two differs in most of its exponent bits (a depth of 2
+// flips all eight), which leaves a digit of the depth a handful of buckets:
+// 1M particles seen from inside their clusters (two 1920x1080 views) then sent
+// so many lists to the radix sort that it took 338 us; now none goes (4 us).
+// When a bucket holds more than bucket_max keys all the same (a thin cluster
+// in a list that also reaches the far background: most buckets are empty) the
+// sort gives up before touching ids and the list goes to
+// tile_sort_fallback_kernel, which runs the same sort with DEAL: the digits
+// are dealt out by need, from whole keys.  Each of NT equal pieces of the
+// range gets a power of two of the buckets in proportion to its keys, from a
+// count of the pieces; half of the counters hold the buckets and the pieces'
+// table lies behind them.  Such lists of a 3M-particle rolling-shutter view
+// (1600x1200) take 95 us there and took 390 by the radix sort.  (Dealing in
+// every list, or after a failed count in the same kernel, holds more
+// registers: the sorts of 256 entries and more then run at half the waves or
+// spill, and took 1.3 to 3 times as long.)
 constexpr uint32_t kBucketMax = 64;
 
 // A block of NT threads sorts one list of L <= NT ROWS keys with the bucket
@@ -830,7 +846,7 @@ struct BlockSortSmem {
     struct {
       uint32_t wsum[NT / 64];
       uint32_t wmax[NT / 64];
-      unsigned long long wor[NT / 64];
+      unsigned long long wlo[NT / 64], whi[NT / 64];
     } w;  // the waves' partials, read only before the keys move in
   };
   uint32_t cnt[P16 ? (1 << DBM) / 2 : (1 << DBM)];
@@ -853,7 +869,7 @@ __device__ inline uint32_t ctr_inc(uint32_t* c, uint32_t i) {
   return (atomicAdd(&c[i >> 1], 1u << sh) >> sh) & 0xffffu;
 }
 
-template <int NT, int ROWS, int DBM, bool P16>
+template <int NT, int ROWS, int DBM, bool P16, bool DEAL = false>
 __device__ __forceinline__ bool block_bucket_sort(const unsigned long long* __restrict__ keys, uint32_t L,
                                          uint32_t* __restrict__ ids, BlockSortSmem<NT, ROWS, DBM, P16>& S,
                                          uint32_t bucket_max = kBucketMax) {
@@ -870,31 +886,84 @@ __device__ __forceinline__ bool block_bucket_sort(const unsigned long long* __re
     ok[r] = p < L;
     kk[r] = ok[r] ? keys[p] : 0ull;
   }
-  const int db = min(DBM, 34 - __clz(L));  // bit length of L, plus two
+  // the bit length of L, plus two; dealt digits use half of the counters
+  const int db = DEAL ? DBM - 1 : min(DBM, 34 - __clz(L));
   const uint32_t nb = 1u << db;
   const int lq = db > LNT ? db - LNT : 0;
-  const uint32_t q = 1u << lq;  // digits per thread
+  const uint32_t q = 1u << lq;        // digits per thread
   const bool own = (uint32_t)t < nb;  // thread owns digits (all once nb >= NT)
-  // the bits that vary within the list (any of its keys is a reference)
-  const unsigned long long k0 = keys[0];
-  unsigned long long orv = 0;
+  // the list's lowest and highest key: the depths alone (32-bit words), or
+  // the whole keys where the digits are dealt out
+  using word = typename std::conditional<DEAL, unsigned long long, uint32_t>::type;
+  auto word_of = [](unsigned long long k) -> word { return DEAL ? (word)k : (word)(k >> 32); };
+  word lo = ~(word)0, hi = 0;
 #pragma unroll
-  for (int r = 0; r < ROWS; r++) orv |= ok[r] ? kk[r] ^ k0 : 0ull;
-  for (int o = 32; o > 0; o >>= 1) orv |= __shfl_xor(orv, o, 64);
-  if (W > 1 && lane == 0) S.w.wor[w] = orv;
+  for (int r = 0; r < ROWS; r++) {
+    const word v = word_of(kk[r]);
+    lo = ok[r] ? min(lo, v) : lo;
+    hi = max(hi, v);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = min(lo, (word)__shfl_xor(lo, o, 64));
+    hi = max(hi, (word)__shfl_xor(hi, o, 64));
+  }
+  if (W > 1 && lane == 0) {
+    S.w.wlo[w] = lo;
+    S.w.whi[w] = hi;
+  }
   for (uint32_t i = t; i < (P16 ? (nb + 1) / 2 : nb); i += NT) S.cnt[i] = 0u;
+  uint32_t* tab = S.cnt + (P16 ? nb / 2 : nb);  // (DEAL)
+  if (DEAL) tab[t] = 0u;
   __syncthreads();
   if (W > 1) {
-    orv = 0;
 #pragma unroll
-    for (int k = 0; k < W; k++) orv |= S.w.wor[k];
+    for (int k = 0; k < W; k++) {
+      lo = min(lo, (word)S.w.wlo[k]);
+      hi = max(hi, (word)S.w.whi[k]);
+    }
   }
-  const int hb = orv ? 63 - __clzll((long long)orv) : 0;
-  const int shift = hb >= db - 1 ? hb - (db - 1) : 0;
+  const int bits = hi > lo ? 64 - __clzll((long long)(hi - lo)) : 1;
+  const int shift = DEAL ? (bits > LNT ? bits - LNT : 0) : (bits > db ? bits - db : 0);
+  if (DEAL) {
+    // thread t's piece (the keys whose top LNT bits of the distance are t)
+    // holds tot keys and gets 2^b <= tot (nb - NT) / L buckets (at least one;
+    // at most nb in all) from tab[t] & 0xffff on, told apart by the keys' next
+    // b = tab[t] >> 16 bits
+    static_assert(!DEAL || DBM - 1 > LNT, "dealt digits need more buckets than threads");
+#pragma unroll
+    for (int r = 0; r < ROWS; r++)
+      if (ok[r]) atomicAdd(&tab[(uint32_t)((word_of(kk[r]) - lo) >> shift)], 1u);
+    __syncthreads();
+    const uint32_t tot = tab[t], share = tot * (nb - NT) / L;
+    const int b = share ? min(31 - __clz(share), shift) : 0;
+    const uint32_t mine = tot ? 1u << b : 0u;
+    uint32_t x = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    uint32_t base = x - mine;
+    if (W > 1) {
+      if (lane == 63) S.w.wsum[w] = x;
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < W; k++)
+        if (k < w) base += S.w.wsum[k];
+    }
+    tab[t] = base | (uint32_t)b << 16;
+    __syncthreads();
+  }
+  auto digit = [&](unsigned long long key) -> uint32_t {
+    const word x = word_of(key) - lo;
+    if (!DEAL) return (uint32_t)(x >> shift) & (nb - 1);
+    const uint32_t e = tab[(uint32_t)(x >> shift) & (NT - 1)], b = e >> 16;
+    return (e & 0xffffu) + ((uint32_t)(x >> (shift - (int)b)) & ((1u << b) - 1u));
+  };
   uint32_t sl[ROWS];
 #pragma unroll
   for (int r = 0; r < ROWS; r++) {
-    const uint32_t d = (uint32_t)(kk[r] >> shift) & (nb - 1);
+    const uint32_t d = ok[r] ? digit(kk[r]) : 0u;
     sl[r] = ((d & (q - 1)) << LNT) | (d >> lq);
   }
 #pragma unroll
@@ -951,7 +1020,7 @@ __device__ __forceinline__ bool block_bucket_sort(const unsigned long long* __re
   uint32_t base[ROWS], len[ROWS], most = 0;
 #pragma unroll
   for (int r = 0; r < ROWS; r++) {
-    const uint32_t d = (uint32_t)(kk[r] >> shift) & (nb - 1), dp = d ? d - 1 : 0u;
+    const uint32_t d = ok[r] ? digit(kk[r]) : 0u, dp = d ? d - 1 : 0u;
     const uint32_t e = ctr_get<P16>(S.cnt, ((d & (q - 1)) << LNT) | (d >> lq));
     const uint32_t s0 = ctr_get<P16>(S.cnt, ((dp & (q - 1)) << LNT) | (dp >> lq));
     base[r] = d ? s0 : 0u;
@@ -1028,28 +1097,6 @@ __global__ void __launch_bounds__(64) tile_sort_small_kernel(const uint2* __rest
   if (!done && threadIdx.x == 0) fall[atomicAdd(nfall, 1u)] = blockIdx.x;
 }
 
-// The lists whose buckets came out too large, by the stable LSD radix sort:
-// in LDS up to 4096 entries, else in chunks through the ping-pong buffer.
-constexpr int kFallThreads = 256, kFallBlocks = 256;
-__global__ void __launch_bounds__(kFallThreads) tile_sort_fallback_kernel(const uint2* __restrict__ ranges,
-                                                                         unsigned long long* __restrict__ keys,
-                                                                         unsigned long long* __restrict__ tmp,
-                                                                         uint32_t* __restrict__ ids,
-                                                                         const uint32_t* __restrict__ nfall,
-                                                                         const uint32_t* __restrict__ fall) {
-  __shared__ TileSortSmem<kFallThreads> S;
-  const uint32_t m = *nfall;
-  for (uint32_t i = blockIdx.x; i < m; i += gridDim.x) {
-    const uint2 r = ranges[fall[i]];
-    const uint32_t L = r.y - r.x;
-    if (L <= (uint32_t)kFallThreads * kTSItems)
-      sort_list_lds<kFallThreads>(keys + r.x, L, ids + r.x, S);
-    else
-      sort_list_chunked<kFallThreads>(keys + r.x, tmp + r.x, L, ids + r.x, S);
-    __syncthreads();  // the LDS is reused by the next list
-  }
-}
-
 // The t-th tile of the positions [n_from[c], n_to[c]) of the cameras' render
 // orders (n_from null: from 0), counted across the cameras in turn.
 __device__ inline uint32_t order_tile(uint32_t g, const uint32_t* __restrict__ order, const CamTiles& ct,
@@ -1100,8 +1147,8 @@ __global__ void __launch_bounds__(kMidThreads, 4) tile_sort_mid_kernel(
 // K5 for lists of 4096 entries and more (the positions [0, nbig)): a fixed
 // grid of 1024-thread blocks, one per CU, by the bucket sort with up to 8192
 // buckets (16-bit counters) for lists of up to 16384 entries.  A longer list
-// is first cut into runs of at most 16384 by the 8 bits below its highest
-// varying bit (runs of whole digit values, so every key of a run is below
+// is first cut into runs of at most 16384 by the top 8 bits of the distance
+// from its lowest key (runs of whole digit values, so every key of a run is below
 // every key of the next), moved run by run into the ping-pong buffer, and
 // each run is bucket-sorted there.  A list with a run or bucket of more than
 // 128 entries, or a digit value of more than 16384, goes on the list for
@@ -1114,7 +1161,7 @@ struct SplitSmem {
   uint32_t hist[256];
   uint32_t run_of[256];  // the run of each digit value
   uint32_t fill[kMaxRuns];
-  unsigned long long wor[kBigThreads / 64];
+  unsigned long long wlo[kBigThreads / 64], whi[kBigThreads / 64];
   uint32_t ok;
 };
 union BigSortSmem {
@@ -1131,30 +1178,41 @@ __device__ inline bool split_list(const unsigned long long* __restrict__ src, ui
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   constexpr int U = 8;  // loads in flight per thread
   const unsigned long long k0 = src[0];
-  unsigned long long orv = 0;
+  unsigned long long lo = k0, hi = k0;
   for (uint32_t p0 = t; p0 < L; p0 += U * kBigThreads) {
     unsigned long long k[U];
 #pragma unroll
     for (int j = 0; j < U; j++) k[j] = p0 + j * kBigThreads < L ? src[p0 + j * kBigThreads] : k0;
 #pragma unroll
-    for (int j = 0; j < U; j++) orv |= k[j] ^ k0;
+    for (int j = 0; j < U; j++) {
+      lo = min(lo, k[j]);
+      hi = max(hi, k[j]);
+    }
   }
-  for (int o = 32; o > 0; o >>= 1) orv |= __shfl_xor(orv, o, 64);
-  if (lane == 0) S.wor[w] = orv;
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = min(lo, (unsigned long long)__shfl_xor(lo, o, 64));
+    hi = max(hi, (unsigned long long)__shfl_xor(hi, o, 64));
+  }
+  if (lane == 0) {
+    S.wlo[w] = lo;
+    S.whi[w] = hi;
+  }
   if (t < 256) S.hist[t] = 0u;
   __syncthreads();
-  orv = 0;
 #pragma unroll
-  for (int k = 0; k < kBigThreads / 64; k++) orv |= S.wor[k];
-  const int hb = orv ? 63 - __clzll((long long)orv) : 0;
-  const int shift = hb >= 7 ? hb - 7 : 0;
+  for (int k = 0; k < kBigThreads / 64; k++) {
+    lo = min(lo, S.wlo[k]);
+    hi = max(hi, S.whi[k]);
+  }
+  const int bits = hi > lo ? 64 - __clzll((long long)(hi - lo)) : 1;
+  const int shift = bits > 8 ? bits - 8 : 0;
   for (uint32_t p0 = t; p0 < L; p0 += U * kBigThreads) {
     unsigned long long k[U];
 #pragma unroll
     for (int j = 0; j < U; j++) k[j] = p0 + j * kBigThreads < L ? src[p0 + j * kBigThreads] : 0ull;
 #pragma unroll
     for (int j = 0; j < U; j++)
-      if (p0 + j * kBigThreads < L) atomicAdd(&S.hist[(uint32_t)(k[j] >> shift) & 255u], 1u);
+      if (p0 + j * kBigThreads < L) atomicAdd(&S.hist[(uint32_t)((k[j] - lo) >> shift) & 255u], 1u);
   }
   __syncthreads();
   if (t == 0) {  // greedy cut at digit boundaries
@@ -1189,7 +1247,7 @@ __device__ inline bool split_list(const unsigned long long* __restrict__ src, ui
     for (int j = 0; j < U; j++) k[j] = p0 + j * kBigThreads < L ? src[p0 + j * kBigThreads] : 0ull;
 #pragma unroll
     for (int j = 0; j < U; j++)
-      if (p0 + j * kBigThreads < L) dst[atomicAdd(&S.fill[S.run_of[(uint32_t)(k[j] >> shift) & 255u]], 1u)] = k[j];
+      if (p0 + j * kBigThreads < L) dst[atomicAdd(&S.fill[S.run_of[(uint32_t)((k[j] - lo) >> shift) & 255u]], 1u)] = k[j];
   }
   __syncthreads();  // the runs are in dst for the whole block
   return true;
@@ -1225,6 +1283,63 @@ __global__ void __launch_bounds__(kBigThreads) tile_sort_big_kernel(
     }
     // the list's keys are still whole in keys: the radix sort takes it over
     if (!done && threadIdx.x == 0) fall[atomicAdd(nfall, 1u)] = tile;
+    __syncthreads();  // the LDS is reused by the next list
+  }
+}
+
+// The lists whose buckets came out too large: the bucket sort with dealt
+// digits, cutting a list over 16384 entries into runs first as above; a list
+// that still has too large a bucket or run (many equal depths) takes the
+// stable LSD radix sort, in LDS up to 16384 entries, else in chunks through
+// the ping-pong buffer.
+constexpr int kFallBlocks = 256;
+constexpr uint32_t kFallBucketMax = 256;
+union FallSmem {
+  BlockSortSmem<kBigThreads, kBigRows, 13, true> bucket;
+  SplitSmem split;
+  TileSortSmem<kBigThreads> radix;
+};
+__global__ void __launch_bounds__(kBigThreads) tile_sort_fallback_kernel(const uint2* __restrict__ ranges,
+                                                                        unsigned long long* __restrict__ keys,
+                                                                        unsigned long long* __restrict__ tmp,
+                                                                        uint32_t* __restrict__ ids,
+                                                                        const uint32_t* __restrict__ nfall,
+                                                                        const uint32_t* __restrict__ fall) {
+  __shared__ FallSmem S;
+  __shared__ uint32_t bounds[kMaxRuns + 1];
+  __shared__ uint32_t nrun;
+  const uint32_t m = *nfall;
+  for (uint32_t i = blockIdx.x; i < m; i += gridDim.x) {
+    const uint2 r = ranges[fall[i]];
+    const uint32_t L = r.y - r.x;
+    const unsigned long long* src = keys + r.x;
+    bool done = true;
+    if (L <= kBigMax) {
+      if (threadIdx.x == 0) {
+        bounds[0] = 0u;
+        bounds[1] = L;
+        nrun = 1u;
+      }
+      __syncthreads();
+    } else {
+      src = tmp + r.x;
+      done = L <= kBigMax * (kMaxRuns / 2) && split_list(keys + r.x, L, tmp + r.x, S.split, bounds, &nrun);
+    }
+    if (done) {
+      const uint32_t nr = nrun;
+      for (uint32_t k = 0; k < nr && done; k++) {
+        const uint32_t a = bounds[k], n = bounds[k + 1] - a;
+        if (n > 0)
+          done = block_bucket_sort<kBigThreads, kBigRows, 13, true, true>(src + a, n, ids + r.x + a, S.bucket,
+                                                                          kFallBucketMax);
+        __syncthreads();
+      }
+    }
+    __syncthreads();
+    if (!done) {  // the list's keys are still whole in keys
+      if (L <= kBigMax) sort_list_lds<kBigThreads>(keys + r.x, L, ids + r.x, S.radix);
+      else sort_list_chunked<kBigThreads>(keys + r.x, tmp + r.x, L, ids + r.x, S.radix);
+    }
     __syncthreads();  // the LDS is reused by the next list
   }
 }
@@ -1380,7 +1495,9 @@ gut_status bin_sort_launch(const gut_projected* proj, int n, const DevCam* dc, i
     GUT_LAUNCH_CHECK();
   }
   if (phases & kSortFallback) {
-    tile_sort_fallback_kernel<<<kFallBlocks, kFallThreads, 0, s>>>((const uint2*)tile_ranges, keys, tmp, sorted_ids,
+    // (an empty launch of 256 such blocks costs 5 us, of 16 one)
+    const unsigned nf = (unsigned)std::min<int64_t>(kFallBlocks, (T + 3) / 4);
+    tile_sort_fallback_kernel<<<nf, kBigThreads, 0, s>>>((const uint2*)tile_ranges, keys, tmp, sorted_ids,
                                                                    nfall, fall);
     GUT_LAUNCH_CHECK();
   }
