@@ -1,25 +1,35 @@
 // K5 -- per-tile front-to-back compositing (Eq. 5) with each particle's
 // response evaluated in 3D at its maximum along the pixel ray (Eq. 11).
 //
-// One 128-thread block (2 wave64s) per 16x16 tile; each wave owns a 16x8
-// half-tile and each thread two pixels of one column, 4 rows apart, so every
-// pair read from LDS serves two evaluations.  The tile's sorted list is
+// One 128-thread block (2 wave64s) per 16x16 tile; each wave owns two 8x8
+// quadrants, one above the other, and each thread one pixel of either, so a
+// pair read from LDS serves up to two evaluations.  The tile's sorted list is
 // consumed in batches of 128: each thread gathers one pair's 64-byte render
 // record, forms the pair's FP64 tile-frame terms (tile_eval.h), including
-// which half-tiles the particle's alpha_min ellipse can reach, and stores
-// them in LDS.  Each wave then walks only the pairs flagged for its half
-// (a scalar bit loop), reading each pair as an LDS broadcast; per pixel the
-// cheap test omega^2 <= K comes first and the reciprocal and exponential run
-// only when some lane of the wave passes it.  The walk is branch-free per
-// pixel (predicated updates); a wave leaves the batch as soon as all its
-// pixels have stopped, and the block stops when no pixel is still going.
-// Blocks take tiles in the render order from gut_bin (longest lists first)
-// and waves of long lists raise their issue priority, so the longest tiles
-// neither start last nor crawl behind short ones.  The compositing kernels
-// run five waves per SIMD (96 VGPRs; the FP64 pair setup keeps 12 values in
-// scratch): 8% faster than four waves without spills (114 VGPRs).  The walk
-// is a chain of dependent LDS reads, compares and transcendentals, and a
-// fifth wave hides more of it than the setup's spills cost.
+// which quadrants the particle's alpha_min ellipse can reach, and stores
+// them in LDS.  Each wave then walks only the pairs flagged for one of its
+// quadrants (a scalar bit loop), reading each pair as an LDS broadcast, and
+// evaluates a quadrant only if the pair is flagged for it; per pixel the cheap
+// test omega^2 <= K comes first and the reciprocal and exponential run only
+// when some lane of the quadrant passes it.  A quadrant drops out of the walk
+// as soon as all its pixels have stopped, and the block stops when no pixel
+// is still going.
+// Blocks take tiles in the render order from gut_bin (longest lists first), the
+// longest as two blocks of two quadrants each (split_tiles below), and waves of
+// long lists raise their issue priority, so that the longest tiles neither
+// start last nor crawl behind short ones.
+//
+// What bounds it: the vector ALUs on a full chip (two 1920x1080 views of 1M
+// particles: 0.53 ms, 0.59 with 16 x 8 half-tiles per wave, whose walk
+// evaluated 8.3M half-quadrants of which 6.0M can be hit), else the longest
+// list.  Quadrants hold 8 x 8 pixels because the particles are about that
+// size: of the (part, pair) combinations with a live pixel, 5.6M 8 x 8
+// quadrants have a third more live lanes than 3.7M 16 x 8 halves.  The
+// global-shutter kernels ask for five waves per SIMD (96 VGPRs; the FP64 pair
+// setup keeps a few values in scratch): with 16 x 8 halves that was 8% faster
+// than four waves without spills.
+#include <algorithm>
+
 #include "tile_eval.h"
 
 namespace gut {
@@ -27,25 +37,99 @@ namespace gut {
 constexpr int kRThreads = 128;
 constexpr int kRBatch = kRThreads;
 
-// One tile of one camera.  pd, pf, F, wb and red are the block's LDS; out_*
+// Tiles of a camera that take two blocks, each with one quadrant per wave: the
+// count n (the longest lists) and the list length from which they do.  A tile
+// is a serial walk, so below some 2500 blocks (256 CUs at ten blocks each) a
+// launch ends with its longest list and not with the chip full; two blocks
+// halve the walk and pay the pair setup twice.  So every tile takes two while
+// both fit at once, as many of the longest as fit after that, and an eighth
+// of them always, from 256 entries on: an eighth of 8160 tiles shortens the
+// end of the launch and costs 2% more setup.  Per launch, one quadrant a wave
+// against two (and the 16 x 8 half-tiles before quadrants): 3M particles,
+// 1600x1200 rolling 0.64 (1.66) ms, 300k, 800x600 rolling 0.52 (1.10) ms,
+// 1M fisheye 1920x1080 0.28 (0.60) ms, 1k particles, 128x128 17 (25) us.
+struct Split {
+  int n;
+  uint32_t len;
+};
+inline Split split_tiles(int T, int n_cams) {
+  const int fill = 2560 / n_cams;
+  return 2 * T <= fill ? Split{T, 1u} : Split{std::max(T / 8, std::min(T, fill - T)), 256u};
+}
+
+// One pixel of a thread: its ray in tile coordinates, transmittance and
+// running sums.  A pixel that has stopped (or is outside the image) has
+// u = NaN: its omega^2 <= K test then fails by itself.
+struct Pixel {
+  float u, v, dt, dlen, clip, T;
+  // Colour accumulates in FP64 (three FMAs per contributing entry) so that
+  // the backward can form suffix sums C - C_<=j without FP32 cancellation.
+  double C[3];
+  uint32_t last, nev;
+};
+
+// One list entry (its 1-based place in the list is idx1) against one pixel
+// per lane.  Returns true when a lane stopped at it.  A lane the entry does
+// not hit takes alpha = 0, which changes neither T nor C, so only the last
+// contributor and the rare stop need lane flags.
+template <bool RS, bool NE, bool GEN, bool CLIP>
+__device__ __forceinline__ bool pixel_step(const PairRegs<RS>& r, const float4* P, uint32_t idx1,
+                                           const Thresholds& th, Pixel& p) {
+  Eval ev;
+  eval_test<RS>(r, P, p.u, p.v, p.dt, &ev);
+  if (CLIP) clip_test<RS>(r, P, p.u, p.v, p.dt, p.dlen, p.clip, &ev);
+  const bool live = eval_hit<RS>(r, ev);
+  if (!wave_any(live)) return false;  // nothing reaches alpha_min here
+  eval_alpha<RS, GEN>(r, th, &ev);
+  double col[3];
+  pair_colour<RS>(P, col);
+  float a = live ? ev.a : 0.0f;
+  float Tn = fmaf(-a, p.T, p.T);  // T (1 - alpha)
+  uint32_t last = live ? idx1 : p.last;
+  bool stopped = false;
+  if (wave_any(Tn < th.t_min)) {  // these stop before adding this particle
+    const bool stop = Tn < th.t_min;
+    a = stop ? 0.0f : a;
+    Tn = stop ? p.T : Tn;
+    last = stop ? p.last : last;
+    p.u = stop ? __builtin_nanf("") : p.u;
+    if (NE) p.nev = stop ? idx1 : p.nev;
+    stopped = true;
+  }
+  const double w = (double)(a * p.T);
+  p.C[0] = fma(w, col[0], p.C[0]);
+  p.C[1] = fma(w, col[1], p.C[1]);
+  p.C[2] = fma(w, col[2], p.C[2]);
+  p.T = Tn;
+  p.last = last;
+  return stopped;
+}
+
+// One tile of one camera, or (part = 0 or 1) its upper or lower two
+// quadrants, one per wave.  pd, pf, F, wb and red are the block's LDS; out_*
 // are indexed by pix_base + y * W + x.  GEN: response of degree th.kdeg > 2.
 // CLIP: per-pixel clip distances (hybrid rendering, Sec. 6.2), indexed as
 // the outputs; hits beyond them are discarded.
 template <bool RS, bool NE, bool GEN, bool CLIP>
 __device__ __forceinline__ void render_tile(
-    const DevCam& cam, const Thresholds& th, int n, int cam_idx, int tile,
+    const DevCam& cam, const Thresholds& th, int n, int cam_idx, int tile, int part, uint32_t split_len,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ ids,
     const float4* __restrict__ record, const float* __restrict__ rgb, const float* __restrict__ clip,
     float* __restrict__ out_rgb,
     float* __restrict__ out_T, uint32_t* __restrict__ out_nc, uint32_t* __restrict__ out_ne,
-    long long pix_base, float4* pd, uint32_t* pf, TileFrameD& F, WaveBoxes& wb, float* red) {
+    long long pix_base, float4* pd, uint32_t* pf, TileFrameD& F, QuadBoxes& wb, float* red) {
   constexpr int S = Slots<RS, false>::N;
+  const uint2 rg = ranges[cam.tile_base + tile];
+  const uint32_t len = __builtin_amdgcn_readfirstlane(rg.y - rg.x);
+  if (part >= 0 && len < split_len) {  // too short to be worth two setups: the first block takes it all
+    if (part == 1) return;
+    part = -1;
+  }
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
-  const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
-  // wave wv owns the 16 x 8 half-tile of rows 8 wv .. 8 wv + 7; a thread
-  // owns the pixels (px, py0) and (px, py0 + 4)
-  const int px = tx * kTile + (lane & (kTile - 1));
-  const int py0 = ty * kTile + 8 * wv + (lane >> 4);
+  const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  // wave wv owns the quadrants wv and wv + 2: a thread has the pixels (px, py0) and (px, py0 + 8)
+  const int px = tx * kTile + 8 * wv + (lane & 7);
+  const int py0 = ty * kTile + (lane >> 3);
   if (t == 0) tile_frame(cam, tx, ty, &F);
   __syncthreads();
 
@@ -53,10 +137,12 @@ __device__ __forceinline__ void render_tile(
   float u[2] = {0.f, 0.f}, v[2] = {0.f, 0.f}, dt[2] = {0.f, 0.f};
 #pragma unroll
   for (int k = 0; k < 2; k++) {
-    const int py = py0 + 4 * k;
+    const int py = py0 + 8 * k;
     inside[k] = px < cam.W && py < cam.H;
     active[k] = inside[k] && pixel_ray(cam, F, px, py, &u[k], &v[k], &dt[k]);
   }
+  // (a block of one part takes the whole tile's bounds too: the pair setup's
+  // sign classification, and with it every result, is that of the whole tile)
   float umax, vmax, dtmax;
   tile_bounds<2>(u, v, dt, active, red, &umax, &vmax, &dtmax);
   // The pair setup reads the tile's bounds from LDS at each batch (published
@@ -68,122 +154,121 @@ __device__ __forceinline__ void render_tile(
     F.dtmax = dtmax;
     F.l2amin = log2f(th.alpha_min);
   }
-  wave_box<2>(u, v, active, &wb);
-  float clipv[2] = {0.f, 0.f}, dlen[2] = {1.f, 1.f};
-  if (CLIP) {
+  Pixel p[2];
 #pragma unroll
-    for (int k = 0; k < 2; k++) {
-      if (!active[k]) continue;
-      clipv[k] = clip[pix_base + (long long)(py0 + 4 * k) * cam.W + px];
-      dlen[k] = sqrtf(fmaf(u[k], u[k], fmaf(v[k], v[k], 1.0f)));
+  for (int k = 0; k < 2; k++) {
+    quad_box(u[k], v[k], active[k], wv + 2 * k, &wb);
+    p[k].u = active[k] ? u[k] : __builtin_nanf("");
+    p[k].v = v[k];
+    p[k].dt = dt[k];
+    p[k].dlen = 1.0f;
+    p[k].clip = 0.0f;
+    if (CLIP) {
+      if (active[k]) {
+        p[k].clip = clip[pix_base + (long long)(py0 + 8 * k) * cam.W + px];
+        p[k].dlen = sqrtf(fmaf(u[k], u[k], fmaf(v[k], v[k], 1.0f)));
+      }
+      quad_clip_max(p[k].clip, active[k], wv + 2 * k, &wb);
     }
-    wave_clip_max<2>(clipv, active, &wb);
+    p[k].T = 1.0f;
+    p[k].C[0] = p[k].C[1] = p[k].C[2] = 0.0;
+    p[k].last = 0u;
+    p[k].nev = active[k] ? len : 0u;
   }
+  // a block of one part walks only that quadrant of each wave, as p[0]
+  int qa = wv, py = py0;
+  bool two = true;
+  if (part >= 0) {
+    two = false;
+    if (part == 1) {
+      qa = wv + 2;
+      py = py0 + 8;
+      p[0] = p[1];
+      inside[0] = inside[1];
+    }
+    inside[1] = false;
+    p[1].u = __builtin_nanf("");
+  }
+  const unsigned quads = part < 0 ? 15u : part == 0 ? 3u : 12u;
 
-  const uint2 rg = ranges[cam.tile_base + tile];
-  const uint32_t len = __builtin_amdgcn_readfirstlane(rg.y - rg.x);
   // long lists first in the schedule, and their waves first at issue
   if (len >= 2048) __builtin_amdgcn_s_setprio(3);
   else if (len >= 1024) __builtin_amdgcn_s_setprio(2);
   else if (len >= 256) __builtin_amdgcn_s_setprio(1);
   else __builtin_amdgcn_s_setprio(0);
-  // Colour accumulates in FP64 (three FMAs per contributing entry) so that
-  // the backward can form suffix sums C - C_<=j without FP32 cancellation.
-  // A stopped pixel keeps -T (T >= t_min > 0 while it runs): the stop is
-  // then one select on T instead of a flag of its own.
-  float T[2] = {active[0] ? 1.0f : -1.0f, active[1] ? 1.0f : -1.0f};
-  double C[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-  uint32_t last[2] = {0u, 0u}, nev[2] = {active[0] ? len : 0u, active[1] ? len : 0u};
   for (uint32_t b = 0; b < len; b += kRBatch) {
-    // (also publishes wb before the first setup)
-    if (__syncthreads_count(T[0] > 0.0f || T[1] > 0.0f) == 0) break;
+    // (also publishes wb before the first setup; u == u: the pixel still runs)
+    if (__syncthreads_count(p[0].u == p[0].u || p[1].u == p[1].u) == 0) break;
     b = __builtin_amdgcn_readfirstlane(b);
     uint32_t fl = 0u;
     if (b + t < len) {
       uint32_t e = ids[rg.x + b + t];
       fl = pair_setup<RS, false, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n), F,
-                                      cam, F.umax, F.vmax, F.dtmax, th, F.l2amin, wb, kRThreads / 64,
+                                      cam, F.umax, F.vmax, F.dtmax, th, F.l2amin, wb, quads,
                                       &pd[t * S]);
     }
     pf[t] = fl;
     __syncthreads();
-    // the batch's pairs that may reach alpha_min somewhere in this wave's half-tile
-    const uint32_t f0 = pf[lane], f1 = pf[lane + 64];
-    const unsigned long long m0 = __builtin_amdgcn_ballot_w64((f0 >> wv) & 1u);
-    const unsigned long long m1 = __builtin_amdgcn_ballot_w64((f1 >> wv) & 1u);
-    const unsigned long long x0 = __builtin_amdgcn_ballot_w64((f0 & kMixedBit) != 0u);
-    const unsigned long long x1 = __builtin_amdgcn_ballot_w64((f1 & kMixedBit) != 0u);
-    bool wave_done = false;
-    for (int h = 0; h < 2 && !wave_done; h++) {
-      unsigned long long m = h ? m1 : m0;
-      const unsigned long long xm = h ? x1 : x0;
+    const bool run0 = wave_any(p[0].u == p[0].u), run1 = two && wave_any(p[1].u == p[1].u);
+#pragma unroll 1
+    for (int h = 0; h < 2; h++) {
+      // the batch's pairs that may reach alpha_min somewhere in the wave's quadrants
+      const uint32_t f = pf[lane + 64 * h];
+      unsigned long long ma = run0 ? __builtin_amdgcn_ballot_w64((f >> qa) & 1u) : 0ull;
+      unsigned long long mb = run1 ? __builtin_amdgcn_ballot_w64((f >> (wv + 2)) & 1u) : 0ull;
+      const unsigned long long xm = __builtin_amdgcn_ballot_w64((f & kMixedBit) != 0u);
+      unsigned long long m = ma | mb;
       while (m) {
-        if (!wave_any(T[0] > 0.0f || T[1] > 0.0f)) { wave_done = true; break; }
         const uint32_t ql = (uint32_t)__builtin_ctzll(m), q = 64u * h + ql;
         m &= m - 1ull;
         const uint32_t idx1 = b + q + 1;  // the entry's 1-based place in the list
         const float4* P = &pd[q * S];
         PairRegs<RS> r;
         load_pair<RS>(P, r);
-        r.mixed = (xm >> ql) & 1ull;  // (from the flags: no wait on the LDS read)
-        Eval ev[2];
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-          eval_test<RS>(r, P, u[k], v[k], dt[k], &ev[k]);
-          if (CLIP) ev[k].ok = ev[k].ok && !behind_clip<RS>(r, P, u[k], v[k], dt[k], dlen[k], clipv[k], ev[k].dd);
-        }
-        const bool live0 = ev[0].ok & (T[0] > 0.0f), live1 = ev[1].ok & (T[1] > 0.0f);
-        if (!wave_any(live0 | live1)) continue;  // nothing reaches alpha_min here
-        bool contrib[2];
-        float wgt[2];
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-          eval_alpha<RS, GEN>(r, th, &ev[k]);
-          const bool live = k ? live1 : live0;
-          const float Tn = fmaf(-ev[k].a, T[k], T[k]);  // T (1 - alpha)
-          const bool stop = live & (Tn < th.t_min);  // stop before adding this particle
-          contrib[k] = live ^ stop;
-          const float ae = contrib[k] ? ev[k].a : 0.0f;
-          wgt[k] = ae * T[k];
-          const float Tk = contrib[k] ? Tn : T[k];
-          T[k] = stop ? -T[k] : Tk;
-          last[k] = contrib[k] ? idx1 : last[k];
-          if (NE) nev[k] = stop ? idx1 : nev[k];
-        }
-        // some lane passed the alpha_min test, so almost always some lane
-        // contributes: accumulate unconditionally (zero weights add nothing)
-        double col[3];
-        pair_colour<RS>(P, col);
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-          const double w = (double)wgt[k];
-          C[k][0] = fma(w, col[0], C[k][0]);
-          C[k][1] = fma(w, col[1], C[k][1]);
-          C[k][2] = fma(w, col[2], C[k][2]);
-        }
+        r.mixed = (uint32_t)(xm >> ql) & 1u;  // (from the flags: no wait on the LDS read)
+        if ((ma >> ql) & 1ull)
+          if (pixel_step<RS, NE, GEN, CLIP>(r, P, idx1, th, p[0]) && !wave_any(p[0].u == p[0].u)) {
+            ma = 0ull;
+            m &= mb;
+          }
+        if ((mb >> ql) & 1ull)
+          if (pixel_step<RS, NE, GEN, CLIP>(r, P, idx1, th, p[1]) && !wave_any(p[1].u == p[1].u)) {
+            mb = 0ull;
+            m &= ma;
+          }
       }
     }
   }
 #pragma unroll
   for (int k = 0; k < 2; k++) {
     if (!inside[k]) continue;
-    const int py = py0 + 4 * k;
-    long long pix = pix_base + (long long)py * cam.W + px;
-    const float Tf = fabsf(T[k]);
-    out_rgb[3 * pix] = (float)fma((double)Tf, (double)th.bg[0], C[k][0]);
-    out_rgb[3 * pix + 1] = (float)fma((double)Tf, (double)th.bg[1], C[k][1]);
-    out_rgb[3 * pix + 2] = (float)fma((double)Tf, (double)th.bg[2], C[k][2]);
-    if (out_T) out_T[pix] = Tf;
-    if (out_nc) out_nc[pix] = last[k];
-    if (NE) out_ne[pix] = nev[k];
+    const long long pix = pix_base + (long long)(k ? py0 + 8 : py) * cam.W + px;
+    const double Tf = (double)p[k].T;
+    out_rgb[3 * pix] = (float)fma(Tf, (double)th.bg[0], p[k].C[0]);
+    out_rgb[3 * pix + 1] = (float)fma(Tf, (double)th.bg[1], p[k].C[1]);
+    out_rgb[3 * pix + 2] = (float)fma(Tf, (double)th.bg[2], p[k].C[2]);
+    if (out_T) out_T[pix] = p[k].T;
+    if (out_nc) out_nc[pix] = p[k].last;
+    if (NE) out_ne[pix] = p[k].nev;
   }
+}
+
+// The tile and part of block k of a camera's T + n_split blocks: its n_split
+// first tiles (the longest lists) take two blocks each.
+__device__ inline int block_tile(uint32_t k, uint32_t n_split, const uint32_t* __restrict__ order, int* part) {
+  if (k < 2u * n_split) {
+    *part = (int)(k & 1u);
+    return (int)order[k >> 1];
+  }
+  *part = -1;
+  return (int)order[k - n_split];
 }
 
 // One block per tile, taken in the render order (longest lists first).  NE:
 // also count each pixel's evaluated entries (out_ne non-null).
 template <bool RS, bool NE, bool GEN, bool CLIP>
 __global__ void __launch_bounds__(kRThreads, 5) render_kernel(
-    DevCam cam, Thresholds th, int n, int cam_idx, const uint2* __restrict__ ranges,
+    DevCam cam, Thresholds th, int n, int cam_idx, Split split, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ ids,
     const float4* __restrict__ record, const float* __restrict__ rgb, const float* __restrict__ clip,
     float* __restrict__ out_rgb,
@@ -191,10 +276,11 @@ __global__ void __launch_bounds__(kRThreads, 5) render_kernel(
   __shared__ float4 pd[kRBatch * Slots<RS, false>::N];
   __shared__ uint32_t pf[kRBatch];
   __shared__ TileFrameD F;
-  __shared__ WaveBoxes wb;
+  __shared__ QuadBoxes wb;
   __shared__ float red[6];
-  const int tile = (int)order[cam.tile_base + blockIdx.x];
-  render_tile<RS, NE, GEN, CLIP>(cam, th, n, cam_idx, tile, ranges, ids, record, rgb, clip, out_rgb,
+  int part;
+  const int tile = block_tile(blockIdx.x, (uint32_t)split.n, order + cam.tile_base, &part);
+  render_tile<RS, NE, GEN, CLIP>(cam, th, n, cam_idx, tile, part, split.len, ranges, ids, record, rgb, clip, out_rgb,
                                  out_T, out_nc, out_ne, cam.pixel_base, pd, pf, F, wb, red);
 }
 
@@ -213,6 +299,7 @@ struct MultiCams {
   DevCam cam[kMultiCams];
   int idx[kMultiCams];  // the cameras' indices in the call
   int n;
+  Split split;
 };
 
 template <bool RS, bool NE, bool GEN, bool CLIP>
@@ -225,12 +312,13 @@ __global__ void __launch_bounds__(kRThreads, 5) render_multi_kernel(
   __shared__ float4 pd[kRBatch * Slots<RS, false>::N];
   __shared__ uint32_t pf[kRBatch];
   __shared__ TileFrameD F;
-  __shared__ WaveBoxes wb;
+  __shared__ QuadBoxes wb;
   __shared__ float red[6];
   const int c = (int)(blockIdx.x % (unsigned)mc.n), k = (int)(blockIdx.x / (unsigned)mc.n);
   const DevCam& cam = mc.cam[c];
-  const int tile = (int)order[cam.tile_base + k];
-  render_tile<RS, NE, GEN, CLIP>(cam, th, n, mc.idx[c], tile, ranges, ids, record, rgb, clip, out_rgb,
+  int part;
+  const int tile = block_tile((uint32_t)k, (uint32_t)mc.split.n, order + cam.tile_base, &part);
+  render_tile<RS, NE, GEN, CLIP>(cam, th, n, mc.idx[c], tile, part, mc.split.len, ranges, ids, record, rgb, clip, out_rgb,
                                  out_T, out_nc, out_ne, cam.pixel_base, pd, pf, F, wb, red);
 }
 
@@ -242,7 +330,7 @@ __global__ void __launch_bounds__(kRThreads, 5) render_multi_kernel(
 // others, and leaves once every counter is past its share.  Images go to
 // outs[camera] ([H, W, 3]).
 template <bool RS, bool GEN>
-__global__ void __launch_bounds__(kRThreads, 4) render_batch_kernel(
+__global__ void __launch_bounds__(kRThreads, RS ? 3 : 4) render_batch_kernel(
     const DevCam* __restrict__ cams, const int* __restrict__ cam_list,
     const int* __restrict__ item_start, int n_list, int n_items, unsigned* __restrict__ counters,
     Thresholds th, int n, const uint2* __restrict__ ranges, const uint32_t* __restrict__ order,
@@ -251,7 +339,7 @@ __global__ void __launch_bounds__(kRThreads, 4) render_batch_kernel(
   __shared__ float4 pd[kRBatch * Slots<RS, false>::N];
   __shared__ uint32_t pf[kRBatch];
   __shared__ TileFrameD F;
-  __shared__ WaveBoxes wb;
+  __shared__ QuadBoxes wb;
   __shared__ float red[6];
   __shared__ int item_s;
   const int nx = 8;
@@ -281,7 +369,7 @@ __global__ void __launch_bounds__(kRThreads, 4) render_batch_kernel(
     const int c = __builtin_amdgcn_readfirstlane(cam_list[j]);
     const DevCam& cam = cams[c];
     const int tile = (int)order[cam.tile_base + (item - item_start[j])];
-    render_tile<RS, false, GEN, false>(cam, th, n, c, tile, ranges, ids, record, rgb, nullptr, outs[c],
+    render_tile<RS, false, GEN, false>(cam, th, n, c, tile, -1, 0u, ranges, ids, record, rgb, nullptr, outs[c],
                                        nullptr, nullptr, nullptr, 0, pd, pf, F, wb, red);
   }
 }
@@ -327,7 +415,7 @@ gut_status render_batch_launch(const DevCam* d_cams, const DevCam* h_cams, int n
 
 // "Ours (sorted)" (Sec. 4.3): multi-layer alpha blending with a per-ray
 // buffer of the kKBuf farthest hits.  One 256-thread block per tile, one pixel
-// per thread (wave w owns rows 4w .. 4w + 3), the tile's list consumed in
+// per thread (wave w owns quadrant w), the tile's list consumed in
 // batches of 256 pairs set up as in render_tile.  A hit is a list entry that
 // passes the alpha_min test; its distance along the ray is tau_max |d|.  Each
 // thread keeps its buffer sorted nearest first in registers: slot 0 holds the
@@ -446,13 +534,13 @@ __global__ void __launch_bounds__(kKThreads, 4) render_kbuffer_kernel(
   __shared__ uint32_t pf[kKThreads];
   __shared__ float cw[kKWin * 3];
   __shared__ TileFrameD F;
-  __shared__ WaveBoxes wb;
+  __shared__ QuadBoxes wb;
   __shared__ float red[12];
   const int tile = (int)order[cam.tile_base + blockIdx.x];
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
   const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
-  const int px = tx * kTile + (lane & (kTile - 1));
-  const int py = ty * kTile + 4 * wv + (lane >> 4);
+  const int px = tx * kTile + 8 * (wv & 1) + (lane & 7);
+  const int py = ty * kTile + 8 * (wv >> 1) + (lane >> 3);
   if (t == 0) tile_frame(cam, tx, ty, &F);
   __syncthreads();
   const bool inside = px < cam.W && py < cam.H;
@@ -461,12 +549,12 @@ __global__ void __launch_bounds__(kKThreads, 4) render_kbuffer_kernel(
   float umax, vmax, dtmax;
   tile_bounds<1>(&u, &v, &dt, &active, red, &umax, &vmax, &dtmax);
   const float l2amin = log2f(th.alpha_min);
-  wave_box<1>(&u, &v, &active, &wb);
+  quad_box(u, v, active, wv, &wb);
   const float dlen = sqrtf(fmaf(u, u, fmaf(v, v, 1.0f)));
   float clipv = 0.0f;  // hybrid rendering (Sec. 6.2), as in render_tile
   if (CLIP) {
     if (active) clipv = clip[cam.pixel_base + (long long)py * cam.W + px];
-    wave_clip_max<1>(&clipv, &active, &wb);
+    quad_clip_max(clipv, active, wv, &wb);
   }
 
   const uint2 rg = ranges[cam.tile_base + tile];
@@ -493,7 +581,7 @@ __global__ void __launch_bounds__(kKThreads, 4) render_kbuffer_kernel(
       float* c = cw + 3 * ((b + t) & (kKWin - 1));
       c[0] = rgb[3 * (size_t)e]; c[1] = rgb[3 * (size_t)e + 1]; c[2] = rgb[3 * (size_t)e + 2];
       fl = pair_setup<RS, false, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n),
-                                            F, cam, umax, vmax, dtmax, th, l2amin, wb, kKThreads / 64,
+                                            F, cam, umax, vmax, dtmax, th, l2amin, wb, 15u,
                                             &pd[t * S]);
     }
     pf[t] = fl;
@@ -510,8 +598,8 @@ __global__ void __launch_bounds__(kKThreads, 4) render_kbuffer_kernel(
         load_pair<RS>(P, r);
         Eval ev;
         eval_test<RS>(r, P, u, v, dt, &ev);
-        if (CLIP) ev.ok = ev.ok && !behind_clip<RS>(r, P, u, v, dt, dlen, clipv, ev.dd);
-        const bool live = ev.ok && done == 0u;
+        if (CLIP) clip_test<RS>(r, P, u, v, dt, dlen, clipv, &ev);
+        const bool live = eval_hit<RS>(r, ev) && done == 0u;
         if (!wave_any(live)) continue;
         eval_alpha<RS, GEN>(r, th, &ev);
         if (FULL) {
@@ -620,9 +708,11 @@ gut_status launch_render(const DevCam& cam, const Thresholds& th, int n, int cam
                          const uint32_t* ranges, const uint32_t* order, const uint32_t* ids,
                          const float* record, const float* rgb, const float* clip, float* out_rgb,
                          float* out_T, uint32_t* out_nc, uint32_t* out_ne, hipStream_t s) {
-  dim3 grid(cam.tiles_x * cam.tiles_y), block(kRThreads);
+  const int T = cam.tiles_x * cam.tiles_y;
+  const Split split = split_tiles(T, 1);
+  dim3 grid(T + split.n), block(kRThreads);
 #define GUT_RK(RS, NE, GEN, CLIP)                                                                  \
-  render_kernel<RS, NE, GEN, CLIP><<<grid, block, 0, s>>>(cam, th, n, cam_idx, (const uint2*)ranges, \
+  render_kernel<RS, NE, GEN, CLIP><<<grid, block, 0, s>>>(cam, th, n, cam_idx, split, (const uint2*)ranges, \
                                                           order, ids, (const float4*)record, rgb,     \
                                                           clip, out_rgb, out_T, out_nc, out_ne)
 #define GUT_RK1(RS, NE, GEN) \
@@ -655,7 +745,9 @@ static gut_status launch_render_group(const DevCam* dc, int c0, int c1, const Th
     mc.cam[k] = dc[c0 + k];
     mc.idx[k] = c0 + k;
   }
-  dim3 grid(mc.n * dc[c0].tiles_x * dc[c0].tiles_y), block(kRThreads);
+  const int T = dc[c0].tiles_x * dc[c0].tiles_y;
+  mc.split = split_tiles(T, mc.n);
+  dim3 grid(mc.n * (T + mc.split.n)), block(kRThreads);
 #define GUT_RM(RS, NE, GEN, CLIP)                                                                    \
   render_multi_kernel<RS, NE, GEN, CLIP><<<grid, block, 0, s>>>(mc, th, n, (const uint2*)ranges, order, \
                                                                 ids, (const float4*)record, rgb, clip,  \

@@ -91,16 +91,16 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
   __shared__ uint32_t pe[kBwBatch];
   __shared__ uint32_t pf[kBwBatch];
   __shared__ TileFrameD F;
-  __shared__ WaveBoxes wb;
+  __shared__ QuadBoxes wb;
   __shared__ float red[6];
   __shared__ uint32_t maxlast_s;
 
   const int tile = (int)order[cam.tile_base + blockIdx.x];  // longest lists first
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
   const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
-  // the forward's pixel layout: wave wv owns rows 8 wv .. 8 wv + 7
-  const int px = tx * kTile + (lane & (kTile - 1));
-  const int py0 = ty * kTile + 8 * wv + (lane >> 4);
+  // the forward's pixel layout: wave wv owns the quadrants wv and wv + 2
+  const int px = tx * kTile + 8 * wv + (lane & 7);
+  const int py0 = ty * kTile + (lane >> 3);
   if (t == 0) { tile_frame(cam, tx, ty, &F); maxlast_s = 0; }
   __syncthreads();
 
@@ -108,22 +108,22 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
   float u[2] = {0.f, 0.f}, v[2] = {0.f, 0.f}, dt[2] = {0.f, 0.f};
 #pragma unroll
   for (int k = 0; k < 2; k++) {
-    const int py = py0 + 4 * k;
+    const int py = py0 + 8 * k;
     active[k] = px < cam.W && py < cam.H && pixel_ray(cam, F, px, py, &u[k], &v[k], &dt[k]);
   }
   float umax, vmax, dtmax;
   tile_bounds<2>(u, v, dt, active, red, &umax, &vmax, &dtmax);
   const float l2amin = log2f(th.alpha_min);
-  wave_box<2>(u, v, active, &wb);
+  for (int k = 0; k < 2; k++) quad_box(u[k], v[k], active[k], wv + 2 * k, &wb);
   float clipv[2] = {0.f, 0.f}, dlen[2] = {1.f, 1.f};  // the forward's clip test operands
   if (CLIP) {
 #pragma unroll
     for (int k = 0; k < 2; k++) {
       if (!active[k]) continue;
-      clipv[k] = clip[cam.pixel_base + (long long)(py0 + 4 * k) * cam.W + px];
+      clipv[k] = clip[cam.pixel_base + (long long)(py0 + 8 * k) * cam.W + px];
       dlen[k] = sqrtf(fmaf(u[k], u[k], fmaf(v[k], v[k], 1.0f)));
     }
-    wave_clip_max<2>(clipv, active, &wb);
+    for (int k = 0; k < 2; k++) quad_clip_max(clipv[k], active[k], wv + 2 * k, &wb);
   }
 
   // Per pixel: the loss gradients, T_N gT, and Z = sum_c gC_c (C_c - C_<=j,c)
@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
 #pragma unroll
   for (int k = 0; k < 2; k++) {
     if (!active[k]) continue;
-    const long long pix = cam.pixel_base + (long long)(py0 + 4 * k) * cam.W + px;
+    const long long pix = cam.pixel_base + (long long)(py0 + 8 * k) * cam.W + px;
     last[k] = out_nc[pix];
     gTT[k] = (d_T ? d_T[pix] : 0.0f) * out_T[pix];
     for (int c = 0; c < 3; c++) {
@@ -160,13 +160,14 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
       uint32_t e = ids[rg.x + b + t];
       pe[t] = e;
       fl = pair_setup<RS, true, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n), F,
-                                     cam, umax, vmax, dtmax, th, l2amin, wb, kBwThreads / 64, &pd[t * S]);
+                                     cam, umax, vmax, dtmax, th, l2amin, wb, 15u, &pd[t * S]);
     }
     pf[t] = fl;
     __syncthreads();
-    // the same pairs the forward walked for this half-tile
-    const unsigned long long m0 = __builtin_amdgcn_ballot_w64((pf[lane] >> wv) & 1u);
-    const unsigned long long m1 = __builtin_amdgcn_ballot_w64((pf[lane + 64] >> wv) & 1u);
+    // the same pairs the forward walked for these quadrants
+    const uint32_t mine = 5u << wv;  // the wave's quadrants
+    const unsigned long long m0 = __builtin_amdgcn_ballot_w64((pf[lane] & mine) != 0u);
+    const unsigned long long m1 = __builtin_amdgcn_ballot_w64((pf[lane + 64] & mine) != 0u);
     bool wave_done = false;
     for (int hh = 0; hh < 2 && !wave_done; hh++) {
       unsigned long long m = hh ? m1 : m0;
@@ -182,11 +183,11 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
 #pragma unroll
         for (int k = 0; k < 2; k++) {
           eval_test<RS>(r, P, u[k], v[k], dt[k], &ev[k]);
-          if (CLIP) ev[k].ok = ev[k].ok && !behind_clip<RS>(r, P, u[k], v[k], dt[k], dlen[k], clipv[k], ev[k].dd);
+          if (CLIP) clip_test<RS>(r, P, u[k], v[k], dt[k], dlen[k], clipv[k], &ev[k]);
         }
         bool hit[2];
-        hit[0] = ev[0].ok && idx < last[0];
-        hit[1] = ev[1].ok && idx < last[1];
+        hit[0] = eval_hit<RS>(r, ev[0]) && idx < last[0];
+        hit[1] = eval_hit<RS>(r, ev[1]) && idx < last[1];
         if (!wave_any(hit[0] || hit[1])) continue;  // wave-uniform
         double cold[3];
         pair_colour<RS>(P, cold);
@@ -214,7 +215,8 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
           // 2 dL/domega^2; a degree-n response scales d alpha / d omega^2 by
           // 2 lambda (n/2) (omega^2)^(n/2 - 1) relative to the Gaussian's
           float c = -ev[k].a * gA;
-          if (GEN) c *= __builtin_amdgcn_exp2f(fmaf(th.k_h - 1.0f, ev[k].lq, th.k_f));
+          // (0 for a lane that is not hit, whose omega may be infinite)
+          if (GEN) c = geo ? c * __builtin_amdgcn_exp2f(fmaf(th.k_h - 1.0f, ev[k].lq, th.k_f)) : 0.0f;
           float3 dg, cr;
           pair_vectors<RS>(P, ev[k], u[k], v[k], &dg, &cr);
           float3 p = cross3f_fma(dg, cr);
@@ -385,13 +387,13 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   __shared__ uint32_t pew[kWin];
   __shared__ float accw[kWin * kRow];
   __shared__ TileFrameD F;
-  __shared__ WaveBoxes wb;
+  __shared__ QuadBoxes wb;
   __shared__ float red[12];
   const int tile = (int)order[cam.tile_base + blockIdx.x];
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
   const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
-  const int px = tx * kTile + (lane & (kTile - 1));
-  const int py = ty * kTile + 4 * wv + (lane >> 4);
+  const int px = tx * kTile + 8 * (wv & 1) + (lane & 7);
+  const int py = ty * kTile + 8 * (wv >> 1) + (lane >> 3);
   if (t == 0) tile_frame(cam, tx, ty, &F);
   for (int i = t; i < kWin * kRow; i += kKThreadsB) accw[i] = 0.0f;
   __syncthreads();
@@ -401,12 +403,12 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   float umax, vmax, dtmax;
   tile_bounds<1>(&u, &v, &dt, &active, red, &umax, &vmax, &dtmax);
   const float l2amin = log2f(th.alpha_min);
-  wave_box<1>(&u, &v, &active, &wb);
+  quad_box(u, v, active, wv, &wb);
   const float dlen = sqrtf(fmaf(u, u, fmaf(v, v, 1.0f)));
   float clipv = 0.0f;  // the forward's clip operands
   if (CLIP) {
     if (active) clipv = clip[cam.pixel_base + (long long)py * cam.W + px];
-    wave_clip_max<1>(&clipv, &active, &wb);
+    quad_clip_max(clipv, active, wv, &wb);
   }
 
   // the loss gradients and Z = gC . C_out (FP64), as in render_bwd_kernel
@@ -447,7 +449,7 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
       const uint32_t e = ids[rg.x + b + t];
       pew[half + t] = e;
       fl = pair_setup<RS, true, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n),
-                                           F, cam, umax, vmax, dtmax, th, l2amin, wb, kKThreadsB / 64,
+                                           F, cam, umax, vmax, dtmax, th, l2amin, wb, 15u,
                                            &pd[t * S]);
     }
     pf[t] = fl;
@@ -464,8 +466,8 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
         load_pair<RS>(P, r);
         Eval ev;
         eval_test<RS>(r, P, u, v, dt, &ev);
-        if (CLIP) ev.ok = ev.ok && !behind_clip<RS>(r, P, u, v, dt, dlen, clipv, ev.dd);
-        const bool live = ev.ok && done == 0u;
+        if (CLIP) clip_test<RS>(r, P, u, v, dt, dlen, clipv, &ev);
+        const bool live = eval_hit<RS>(r, ev) && done == 0u;
         if (!wave_any(live)) continue;
         eval_alpha<RS, GEN>(r, th, &ev);
         if (live) {

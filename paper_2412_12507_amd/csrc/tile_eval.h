@@ -104,7 +104,7 @@ constexpr double kHalfLog2e = 0.72134752044448170368;
 //   alpha = min(2^(lsig - omega'^2), alpha_max),  alpha >= alpha_min <=> omega'^2 <= Kp
 // with omega'^2 = omega^2 log2(e) / 2.
 // Bit of pair_setup's result set when the sign of o_g . d_g varies over the
-// tile (the per-pixel tau_max > 0 test is needed); the low bits are per wave.
+// tile (the per-pixel tau_max > 0 test is needed); the low bits are per quadrant.
 constexpr unsigned kMixedBit = 1u << 8;
 
 template <bool RS, bool BWD>
@@ -143,41 +143,43 @@ __device__ inline void affine_qr(d3 c0, d3 c1, d3 c2, double q[6]) {
 // x = (1, u, v), the pixels where omega^2 <= K' form {x : x^T N x <= 0} with
 // N_ij = (o_g x D_i).(o_g x D_j) - K' D_i.D_j  (Lagrange's identity on
 // |o_g|^2 |d_g|^2 - (o_g.d_g)^2 - K' |d_g|^2), i.e. an ellipse in (u, v)
-// that is tested exactly against each wave's pixel box.  K' carries a 1e-3
+// that is tested exactly against the pixel box of each quadrant of the tile
+// (8 x 8 pixels; quadrant k = column + 2 row).  K' carries a 1e-3
 // relative margin (and, under a rolling shutter, the distance the ray origin
 // moves within the tile, which bounds how far the line moves), so a culled
-// pair fails the per-pixel FP32 test for every pixel of the wave (that
+// pair fails the per-pixel FP32 test for every pixel of the quadrant (that
 // test's own rounding is ~1e-6 relative) and culling changes no result.
 // Forward and backward cull identically.
-struct WaveBoxes {
+struct QuadBoxes {
   float u0[4], u1[4], v0[4], v1[4];
-  float cmax[4];  // largest clip distance of the wave's pixels (hybrid rendering)
+  float cmax[4];  // largest clip distance of the quadrant's pixels (hybrid rendering)
 };
 
 // Does the ellipse qmin + [du dv] [[N11 N12] [N12 N22]] [du dv]^T <= 0
 // (qmin < 0, matrix positive definite; coordinates relative to its centre)
 // meet the box [a0, a1] x [b0, b1]?  The quadratic is convex, so its minimum
-// over the box is at the centre if the centre is inside, else on an edge,
-// where it is a 1D quadratic minimised in closed form and clamped.
+// over the box is at the centre if the centre is inside, else on an edge that
+// faces the centre, where it is a 1D quadratic minimised in closed form and
+// clamped.  (x, y) below is the box's point nearest the centre: the line at x
+// is the facing vertical edge, or runs through the box's inside if there is
+// none, and likewise the line at y.
 __device__ inline bool ellipse_meets_box(double qmin, double N11, double N12, double N22,
                                          double iN11, double iN22, double a0, double a1,
                                          double b0, double b1) {
-  if (a0 <= 0.0 && a1 >= 0.0 && b0 <= 0.0 && b1 >= 0.0) return true;
   const double slack = -1e-6 * qmin;
-  // edge with one offset x fixed; the other offset y ranges over [lo, hi]
-  auto edge = [&](double x, double lo, double hi, double Nxx, double Nyy, double iNyy) {
-    const double y = fmin(fmax(-N12 * x * iNyy, lo), hi);
-    return fma(Nyy * y, y, fma(2.0 * N12 * x, y, fma(Nxx * x, x, qmin))) <= slack;
-  };
-  return edge(a0, b0, b1, N11, N22, iN22) || edge(a1, b0, b1, N11, N22, iN22) ||
-         edge(b0, a0, a1, N22, N11, iN11) || edge(b1, a0, a1, N22, N11, iN11);
+  const double x = fmin(fmax(0.0, a0), a1), y = fmin(fmax(0.0, b0), b1);
+  const double ye = fmin(fmax(-N12 * x * iN22, b0), b1), xe = fmin(fmax(-N12 * y * iN11, a0), a1);
+  const double qx = fma(N22 * ye, ye, fma(2.0 * N12 * x, ye, fma(N11 * x, x, qmin)));
+  const double qy = fma(N11 * xe, xe, fma(2.0 * N12 * y, xe, fma(N22 * y, y, qmin)));
+  return (qx <= slack) | (qy <= slack);
 }
 
-// Forms a pair's slots (FP64 -> FP32) and returns one bit per wave of the
-// block: bit k set when wave k's pixel box may see alpha >= alpha_min.  GEN:
+// Forms a pair's slots (FP64 -> FP32) and returns one bit per quadrant: bit k
+// set when quadrant k's pixel box may see alpha >= alpha_min (only those set
+// in `quads`, which is uniform over the block, are tested).  GEN:
 // the response has degree th.kdeg > 2, and the threshold kept in Kp is the
 // one on omega'^2 where the degree-n exponent reaches log2(sigma / alpha_min).
-// CLIP (hybrid rendering): a wave whose largest clip distance (wb.cmax) lies
+// CLIP (hybrid rendering): a quadrant whose largest clip distance (wb.cmax) lies
 // before the particle's alpha_min ellipsoid loses its bit too -- every hit it
 // could see would be clipped.
 template <bool RS, bool BWD, bool GEN, bool CLIP>
@@ -185,7 +187,7 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
                                       const float* __restrict__ rgb, long long e, int i,
                                       const TileFrameD& F, const DevCam& cam, float umax,
                                       float vmax, float dtmax, const Thresholds& th,
-                                      float log2_amin, const WaveBoxes& wb, int nwaves, float4* out) {
+                                      float log2_amin, const QuadBoxes& wb, unsigned quads, float4* out) {
   const float amin = th.alpha_min;
   float4 r0 = record[4 * (long long)i], r1 = record[4 * (long long)i + 1];
   float4 r2 = record[4 * (long long)i + 2], r3 = record[4 * (long long)i + 3];
@@ -263,9 +265,8 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
   }
   unsigned flags = 0;
   if (Kp >= 0.0f) {
-    const unsigned all = (1u << nwaves) - 1u;
     if (oo <= Kc) {
-      flags = all;  // the ray origin is inside the particle's alpha_min ellipsoid
+      flags = quads;  // the ray origin is inside the particle's alpha_min ellipsoid
     } else {
       if (RS) {
         N00 = fma(-Kc, dot(dn, dn), dot(w, w));
@@ -277,7 +278,7 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
       }
       const double det = fma(N11, N22, -N12 * N12);
       if (!(N11 > 0.0) || !(N22 > 0.0) || !(det > 1e-9 * N11 * N22)) {
-        flags = all;  // not a well-conditioned ellipse in the tile plane: no culling
+        flags = quads;  // not a well-conditioned ellipse in the tile plane: no culling
       } else {
         // 1/det, 1/N11 and 1/N22 from one division
         const double p11 = N11 * N22, rq = 1.0 / (det * p11);
@@ -286,8 +287,9 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
         const double qmin = fma(N02, vc, fma(N01, uc, N00));
         if (qmin < 0.0) {
           const double iN11 = det * N22 * rq, iN22 = det * N11 * rq;
-          for (int k = 0; k < nwaves; k++)
-            if (ellipse_meets_box(qmin, N11, N12, N22, iN11, iN22, wb.u0[k] - uc, wb.u1[k] - uc,
+          for (int k = 0; k < 4; k++)
+            if ((quads >> k & 1u) &&
+                ellipse_meets_box(qmin, N11, N12, N22, iN11, iN22, wb.u0[k] - uc, wb.u1[k] - uc,
                                   wb.v0[k] - vc, wb.v1[k] - vc))
               flags |= 1u << k;
         }
@@ -307,7 +309,7 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
                                                       M[3 * k + 2] * M[3 * k + 2]);
     double lb = sqrt(dot(rel, rel)) - sqrt(Kc0 / rmin);
     if (RS) lb -= (double)dtmax * sqrt(cam.dc[0] * cam.dc[0] + cam.dc[1] * cam.dc[1] + cam.dc[2] * cam.dc[2]);
-    for (int k = 0; k < nwaves; k++)
+    for (int k = 0; k < 4; k++)
       if (lb > (double)wb.cmax[k] * (1.0 + 1e-4)) flags &= ~(1u << k);
   }
   if (mixed && flags) flags |= kMixedBit;
@@ -332,11 +334,10 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
 }
 
 struct Eval {
-  float a;       // alpha after the alpha_max clamp (0 when the pair is skipped)
+  float a;       // alpha after the alpha_max clamp
   float lq;      // degree-n responses: log2 of omega'^2
-  bool ok;       // tau_max > 0 and omega^2 <= K (alpha >= alpha_min)
   bool clamped;  // sigma rho > alpha_max
-  float cc;      // omega'^2 |d_g|^2 (omega'^2 = omega^2 log2(e) / 2)
+  float cc;      // omega'^2 |d_g|^2 (omega'^2 = omega^2 log2(e) / 2); +inf: no hit (tau_max <= 0, or clipped)
   float dd;      // |d_g|^2
   float idd;     // 1 / |d_g|^2
   float araw;    // sigma rho before the alpha_max clamp
@@ -348,7 +349,7 @@ template <bool RS>
 struct PairRegs {
   float4 p0, p1, p2, p3, p4, p5;
   float4 p7, p8, p9;
-  bool mixed;  // sign of o_g . d_g varies across the tile (wave-uniform)
+  uint32_t mixed;  // not 0: sign of o_g . d_g varies across the tile (wave-uniform)
   float lsig, Kp;
 };
 
@@ -359,20 +360,22 @@ __device__ __forceinline__ void load_pair(const float4* P, PairRegs<RS>& r) {
     r.p4 = P[4]; r.p5 = P[5]; r.p7 = P[7]; r.p8 = P[8]; r.p9 = P[9];
     r.lsig = r.p1.w; r.Kp = r.p2.w;
     // every lane reads the same pair: move the flag to a scalar register
-    r.mixed = __builtin_amdgcn_readfirstlane(__float_as_int(r.p0.w)) < 0;
+    r.mixed = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(r.p0.w)) & 0x80000000u;
   } else {
     r.lsig = r.p1.w; r.Kp = r.p0.w;
-    r.mixed = __builtin_amdgcn_readfirstlane(__float_as_int(r.p2.w)) < 0;
+    r.mixed = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(r.p2.w)) & 0x80000000u;
   }
 }
 
 // Stage 1 of the response on one pixel ray (Eq. 11): omega'^2 |d_g|^2 and
-// |d_g|^2, and the test omega'^2 <= Kp (<=> alpha >= alpha_min) without any
-// transcendental.
+// |d_g|^2, for eval_hit's test omega'^2 <= Kp (<=> alpha >= alpha_min)
+// without any transcendental.  Where the tau_max > 0 test (and clip_test's
+// clip) discards the hit it sets cc to +inf, so that eval_hit stays one
+// bare compare: a ballot of a combined lane flag goes through a vector
+// register, two instructions more.
 template <bool RS>
 __device__ __forceinline__ void eval_test(const PairRegs<RS>& r, const float4* P, float u, float v,
                                           float dt, Eval* o) {
-  bool ok = true;
   if (!RS) {
     const float t1 = fmaf(v, r.p0.z, fmaf(u, r.p0.y, r.p0.x));
     const float t2 = fmaf(v, r.p1.y, r.p1.x);
@@ -382,7 +385,7 @@ __device__ __forceinline__ void eval_test(const PairRegs<RS>& r, const float4* P
     o->dd = fmaf(e1, e1, fmaf(e2, e2, r.p3.z));
     if (r.mixed) {  // rare, and uniform across the wave
       const float4 p5 = P[5];
-      ok = fmaf(v, p5.z, fmaf(u, p5.y, p5.x)) < 0.0f;
+      o->cc = fmaf(v, p5.z, fmaf(u, p5.y, p5.x)) < 0.0f ? o->cc : INFINITY;
     }
   } else {
     float3 dg = f3(fmaf(v, r.p2.x, fmaf(u, r.p1.x, r.p0.x)), fmaf(v, r.p2.y, fmaf(u, r.p1.y, r.p0.y)),
@@ -392,17 +395,20 @@ __device__ __forceinline__ void eval_test(const PairRegs<RS>& r, const float4* P
     float3 m = f3(fmaf(v, r.p9.x, fmaf(u, r.p8.x, r.p7.x)), fmaf(v, r.p9.y, fmaf(u, r.p8.y, r.p7.y)),
                   fmaf(v, r.p9.z, fmaf(u, r.p8.z, r.p7.z)));
     cr = f3(fmaf(dt, m.x, cr.x), fmaf(dt, m.y, cr.y), fmaf(dt, m.z, cr.z));
+    o->dd = fmaf(dg.z, dg.z, fmaf(dg.y, dg.y, dg.x * dg.x));
+    o->cc = fmaf(cr.z, cr.z, fmaf(cr.y, cr.y, cr.x * cr.x)) * (float)kHalfLog2e;
     if (r.mixed) {
       float sg = fmaf(v, r.p4.w, fmaf(u, r.p3.w, r.p5.w));
       sg = fmaf(dt, fmaf(v, r.p9.w, fmaf(u, r.p8.w, r.p7.w)), sg);
-      ok = sg < 0.0f;
+      o->cc = sg < 0.0f ? o->cc : INFINITY;
     }
-    o->dd = fmaf(dg.z, dg.z, fmaf(dg.y, dg.y, dg.x * dg.x));
-    o->cc = fmaf(cr.z, cr.z, fmaf(cr.y, cr.y, cr.x * cr.x)) * (float)kHalfLog2e;
     o->dg = dg;
     o->cr = cr;
   }
-  o->ok = ok & (o->cc <= r.Kp * o->dd);
+}
+template <bool RS>
+__device__ __forceinline__ bool eval_hit(const PairRegs<RS>& r, const Eval& o) {
+  return o.cc <= r.Kp * o.dd;
 }
 
 // Stage 2 (only for waves where some pixel passed): alpha = min(sigma rho, alpha_max)
@@ -423,7 +429,7 @@ __device__ __forceinline__ void eval_alpha(const PairRegs<RS>& r, const Threshol
   o->araw = araw;
   o->clamped = araw > amax;
   // araw >= 0, so med3(araw, 0, amax) = min(araw, amax) in one instruction;
-  // callers use a only where ok holds (their live / hit masks include it)
+  // callers use a only where eval_hit holds
   o->a = __builtin_amdgcn_fmed3f(araw, 0.0f, amax);
 }
 
@@ -435,8 +441,8 @@ __device__ __forceinline__ void eval_alpha(const PairRegs<RS>& r, const Threshol
 // (bilinear under a rolling shutter) form as the tau_max sign test.  Forward
 // and backward call this with the same operands.
 template <bool RS>
-__device__ __forceinline__ bool behind_clip(const PairRegs<RS>& r, const float4* P, float u, float v,
-                                            float dt, float dlen, float clip, float dd) {
+__device__ __forceinline__ void clip_test(const PairRegs<RS>& r, const float4* P, float u, float v,
+                                          float dt, float dlen, float clip, Eval* o) {
   float odg;
   if (!RS) {
     const float4 p5 = P[5];
@@ -445,7 +451,7 @@ __device__ __forceinline__ bool behind_clip(const PairRegs<RS>& r, const float4*
     odg = fmaf(v, r.p4.w, fmaf(u, r.p3.w, r.p5.w));
     odg = fmaf(dt, fmaf(v, r.p9.w, fmaf(u, r.p8.w, r.p7.w)), odg);
   }
-  return -odg * dlen > clip * dd;
+  o->cc = -odg * dlen > clip * o->dd ? INFINITY : o->cc;
 }
 
 // Colour of a pair (FP64 slots).
@@ -510,17 +516,10 @@ __device__ inline void tile_bounds(const float* u, const float* v, const float* 
   *dtmax = Cc * 1.0001f + 1e-7f;
 }
 
-// Pixel box (u, v) of each wave's pixels, written to LDS by lane 0 of each
-// wave (NP pixels per thread).
-template <int NP>
-__device__ inline void wave_box(const float* u, const float* v, const bool* valid, WaveBoxes* wb) {
-  float a0 = 3e38f, a1 = -3e38f, b0 = 3e38f, b1 = -3e38f;
-#pragma unroll
-  for (int k = 0; k < NP; k++)
-    if (valid[k]) {
-      a0 = fminf(a0, u[k]); a1 = fmaxf(a1, u[k]);
-      b0 = fminf(b0, v[k]); b1 = fmaxf(b1, v[k]);
-    }
+// Pixel box (u, v) of quadrant k, whose pixels the calling wave's lanes hold,
+// written to LDS by lane 0.
+__device__ inline void quad_box(float u, float v, bool valid, int k, QuadBoxes* wb) {
+  float a0 = valid ? u : 3e38f, a1 = valid ? u : -3e38f, b0 = valid ? v : 3e38f, b1 = valid ? v : -3e38f;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     a0 = fminf(a0, __shfl_xor(a0, o, 64));
@@ -529,22 +528,17 @@ __device__ inline void wave_box(const float* u, const float* v, const bool* vali
     b1 = fmaxf(b1, __shfl_xor(b1, o, 64));
   }
   if ((threadIdx.x & 63) == 0) {
-    const int w = threadIdx.x >> 6;
-    wb->u0[w] = a0; wb->u1[w] = a1; wb->v0[w] = b0; wb->v1[w] = b1;
+    wb->u0[k] = a0; wb->u1[k] = a1; wb->v0[k] = b0; wb->v1[k] = b1;
   }
 }
 
-// Largest clip distance over each wave's valid pixels (+inf if any is
-// unclipped; -inf if the wave has no valid pixel).
-template <int NP>
-__device__ inline void wave_clip_max(const float* clip, const bool* valid, WaveBoxes* wb) {
-  float c = -INFINITY;
-#pragma unroll
-  for (int k = 0; k < NP; k++)
-    if (valid[k]) c = fmaxf(c, clip[k]);
+// Largest clip distance over quadrant k's valid pixels (+inf if any is
+// unclipped; -inf if the quadrant has no valid pixel).
+__device__ inline void quad_clip_max(float clip, bool valid, int k, QuadBoxes* wb) {
+  float c = valid ? clip : -INFINITY;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) c = fmaxf(c, __shfl_xor(c, o, 64));
-  if ((threadIdx.x & 63) == 0) wb->cmax[threadIdx.x >> 6] = c;
+  if ((threadIdx.x & 63) == 0) wb->cmax[k] = c;
 }
 
 // True when pred holds on some active lane (the wave's lane mask, without a
