@@ -1,65 +1,49 @@
 // K5 -- per-tile front-to-back compositing (Eq. 5) with each particle's
 // response evaluated in 3D at its maximum along the pixel ray (Eq. 11).
 //
-// One 128-thread block (2 wave64s) per 16x16 tile; each wave owns two 8x8
-// quadrants, one above the other, and each thread one pixel of either, so a
-// pair read from LDS serves up to two evaluations.  The tile's sorted list is
-// consumed in batches of 128: each thread gathers one pair's 64-byte render
-// record, forms the pair's FP64 tile-frame terms (tile_eval.h), including
-// which quadrants the particle's alpha_min ellipse can reach, and stores
-// them in LDS.  Each wave then walks only the pairs flagged for one of its
-// quadrants (a scalar bit loop), reading each pair as an LDS broadcast, and
-// evaluates a quadrant only if the pair is flagged for it; per pixel the cheap
-// test omega^2 <= K comes first and the reciprocal and exponential run only
-// when some lane of the quadrant passes it.  A quadrant drops out of the walk
-// as soon as all its pixels have stopped, and the block stops when no pixel
-// is still going.
-// Blocks take tiles in the render order from gut_bin (longest lists first), the
-// longest as two blocks of two quadrants each (split_tiles below), and waves of
-// long lists raise their issue priority, so that the longest tiles neither
-// start last nor crawl behind short ones.
+// A block takes one 16x16 tile, whose sorted list it consumes in batches: each
+// thread gathers one pair's 64-byte render record, forms the pair's FP64
+// tile-frame terms (tile_eval.h), including which 8x8 quadrants the particle's
+// alpha_min ellipse can reach, and stores them in LDS.  The waves then walk
+// the pairs, in one of two ways:
 //
-// What bounds it: the vector ALUs on a full chip (two 1920x1080 views of 1M
-// particles: 0.53 ms, 0.59 with 16 x 8 half-tiles per wave, whose walk
-// evaluated 8.3M half-quadrants of which 6.0M can be hit), else the longest
-// list.  Quadrants hold 8 x 8 pixels because the particles are about that
-// size: of the (part, pair) combinations with a live pixel, 5.6M 8 x 8
-// quadrants have a third more live lanes than 3.7M 16 x 8 halves.  The
-// global-shutter kernels ask for five waves per SIMD (96 VGPRs; the FP64 pair
-// setup keeps a few values in scratch): with 16 x 8 halves that was 8% faster
-// than four waves without spills.
-#include <algorithm>
-
+// NQ = 1: 256 threads, a wave per quadrant, a pixel per thread.  A wave makes
+//   one list per 4x4 pixel block of the pairs that can reach it (build_lists)
+//   and walks the four lists side by side, one row of 16 lanes per block; a
+//   step reads its pairs from LDS a step ahead (a broadcast within each row)
+//   and evaluates them without a branch, since almost every pair of a list
+//   hits some pixel of its block.
+// NQ = 2: 128 threads, two quadrants per wave, a pixel of either per thread.
+//   A wave walks the pairs flagged for its quadrants one at a time (a scalar
+//   bit loop), reads each once (a broadcast to all lanes) and evaluates a
+//   quadrant only if the pair is flagged for it, and past the cheap test only
+//   if some lane passes.
+//
+// Lists take half the steps where the particles are small against a quadrant,
+// and a tile's walk, which is serial, is spread over twice the waves; but the
+// four waves of a block wait for each other at every batch.  See
+// quads_per_wave for where the line lies.
+//
+// Blocks take tiles in the render order from gut_bin (longest lists first), and
+// waves of long lists raise their issue priority, so that the longest tiles
+// neither start last nor crawl behind short ones.  The global-shutter kernels
+// ask for five waves per SIMD (96 VGPRs; the FP64 pair setup keeps a few values
+// in scratch), the rolling-shutter ones for three.
 #include "tile_eval.h"
 
 namespace gut {
 
-constexpr int kRThreads = 128;
-constexpr int kRBatch = kRThreads;
+template <int NQ>
+constexpr int kRThreads = 256 / NQ;
+// Pairs per batch: one per thread, but under a rolling shutter, whose pairs
+// take 192 bytes of LDS, 128 (three blocks of 256 a CU hold 12 waves, as many
+// as their registers allow).
+template <bool RS, int NQ>
+constexpr int kRBatch = RS ? 128 : 256 / NQ;
 
-// Tiles of a camera that take two blocks, each with one quadrant per wave: the
-// count n (the longest lists) and the list length from which they do.  A tile
-// is a serial walk, so below some 2500 blocks (256 CUs at ten blocks each) a
-// launch ends with its longest list and not with the chip full; two blocks
-// halve the walk and pay the pair setup twice.  So every tile takes two while
-// both fit at once, as many of the longest as fit after that, and an eighth
-// of them always, from 256 entries on: an eighth of 8160 tiles shortens the
-// end of the launch and costs 2% more setup.  Per launch, one quadrant a wave
-// against two (and the 16 x 8 half-tiles before quadrants): 3M particles,
-// 1600x1200 rolling 0.64 (1.66) ms, 300k, 800x600 rolling 0.52 (1.10) ms,
-// 1M fisheye 1920x1080 0.28 (0.60) ms, 1k particles, 128x128 17 (25) us.
-struct Split {
-  int n;
-  uint32_t len;
-};
-inline Split split_tiles(int T, int n_cams) {
-  const int fill = 2560 / n_cams;
-  return 2 * T <= fill ? Split{T, 1u} : Split{std::max(T / 8, std::min(T, fill - T)), 256u};
-}
-
-// One pixel of a thread: its ray in tile coordinates, transmittance and
-// running sums.  A pixel that has stopped (or is outside the image) has
-// u = NaN: its omega^2 <= K test then fails by itself.
+// A thread's pixel: its ray in tile coordinates, transmittance and running
+// sums.  A pixel that has stopped (or is outside the image) has u = NaN: its
+// omega^2 <= K test then fails by itself.
 struct Pixel {
   float u, v, dt, dlen, clip, T;
   // Colour accumulates in FP64 (three FMAs per contributing entry) so that
@@ -68,30 +52,38 @@ struct Pixel {
   uint32_t last, nev;
 };
 
-// One list entry (its 1-based place in the list is idx1) against one pixel
-// per lane.  Returns true when a lane stopped at it.  A lane the entry does
-// not hit takes alpha = 0, which changes neither T nor C, so only the last
-// contributor and the rare stop need lane flags.
-template <bool RS, bool NE, bool GEN, bool CLIP>
-__device__ __forceinline__ bool pixel_step(const PairRegs<RS>& r, const float4* P, uint32_t idx1,
-                                           const Thresholds& th, Pixel& p) {
-  Eval ev;
-  eval_test<RS>(r, P, p.u, p.v, p.dt, &ev);
-  if (CLIP) clip_test<RS>(r, P, p.u, p.v, p.dt, p.dlen, p.clip, &ev);
-  const bool live = eval_hit<RS>(r, ev);
-  if (!wave_any(live)) return false;  // nothing reaches alpha_min here
-  eval_alpha<RS, GEN>(r, th, &ev);
+// A lane's list entry, read from LDS one step ahead of its use.
+template <bool RS>
+struct Entry {
+  PairRegs<RS> r;
   double col[3];
-  pair_colour<RS>(P, col);
-  float a = live ? ev.a : 0.0f;
+  const float4* P;
+  uint32_t i;  // its place in the chunk
+};
+template <bool RS>
+__device__ __forceinline__ void fetch(const float4* pd, uint32_t i, Entry<RS>& e) {
+  e.P = pd + i * Slots<RS, false>::N;
+  e.i = i;
+  load_pair<RS>(e.P, e.r);
+  pair_colour<RS>(e.P, e.col);
+}
+
+// Blends alpha (0 on a lane that is not hit, which changes neither T nor C, so
+// only the last contributor and the rare stop need lane flags).  i: the
+// entry's place, kept in last if it contributes; idx1: its 1-based place in
+// the list.  Returns true when a lane stopped.
+template <bool NE>
+__device__ __forceinline__ bool pixel_blend(bool live, float a, const double (&col)[3], uint32_t i, uint32_t idx1,
+                                            const Thresholds& th, Pixel& p, uint32_t& last) {
   float Tn = fmaf(-a, p.T, p.T);  // T (1 - alpha)
-  uint32_t last = live ? idx1 : p.last;
+  const uint32_t last0 = last;
+  last = live ? i : last0;
   bool stopped = false;
   if (wave_any(Tn < th.t_min)) {  // these stop before adding this particle
     const bool stop = Tn < th.t_min;
     a = stop ? 0.0f : a;
     Tn = stop ? p.T : Tn;
-    last = stop ? p.last : last;
+    last = stop ? last0 : last;
     p.u = stop ? __builtin_nanf("") : p.u;
     if (NE) p.nev = stop ? idx1 : p.nev;
     stopped = true;
@@ -101,50 +93,83 @@ __device__ __forceinline__ bool pixel_step(const PairRegs<RS>& r, const float4* 
   p.C[1] = fma(w, col[1], p.C[1]);
   p.C[2] = fma(w, col[2], p.C[2]);
   p.T = Tn;
-  p.last = last;
   return stopped;
 }
 
-// One tile of one camera, or (part = 0 or 1) its upper or lower two
-// quadrants, one per wave.  pd, pf, F, wb and red are the block's LDS; out_*
-// are indexed by pix_base + y * W + x.  GEN: response of degree th.kdeg > 2.
-// CLIP: per-pixel clip distances (hybrid rendering, Sec. 6.2), indexed as
-// the outputs; hits beyond them are discarded.
+// NQ = 1, one step: each lane's own list entry (the chunk starts at list
+// position base) against its pixel, without a branch but for a stop.
 template <bool RS, bool NE, bool GEN, bool CLIP>
+__device__ __forceinline__ bool list_step(const Entry<RS>& e, uint32_t base, bool mixed, const Thresholds& th,
+                                          Pixel& p, uint32_t& last) {
+  Eval ev;
+  eval_test<RS>(e.r, e.P, p.u, p.v, p.dt, mixed, &ev);
+  if (CLIP) clip_test<RS>(e.r, e.P, p.u, p.v, p.dt, p.dlen, p.clip, &ev);
+  const bool live = eval_hit<RS>(e.r, ev);
+  eval_alpha<RS, GEN>(e.r, th, &ev);
+  return pixel_blend<NE>(live, live ? ev.a : 0.0f, e.col, e.i, base + e.i + 1, th, p, last);
+}
+
+// NQ = 2, one step: one pair (1-based place idx1) against one quadrant.
+template <bool RS, bool NE, bool GEN, bool CLIP>
+__device__ __forceinline__ bool pair_step(const PairRegs<RS>& r, const float4* P, uint32_t idx1, bool mixed,
+                                          const Thresholds& th, Pixel& p) {
+  Eval ev;
+  eval_test<RS>(r, P, p.u, p.v, p.dt, mixed, &ev);
+  if (CLIP) clip_test<RS>(r, P, p.u, p.v, p.dt, p.dlen, p.clip, &ev);
+  const bool live = eval_hit<RS>(r, ev);
+  if (!wave_any(live)) return false;  // nothing reaches alpha_min here
+  eval_alpha<RS, GEN>(r, th, &ev);
+  double col[3];
+  pair_colour<RS>(P, col);
+  return pixel_blend<NE>(live, live ? ev.a : 0.0f, col, idx1, idx1, th, p, p.last);
+}
+
+// A block's LDS.
+template <bool RS, int NQ>
+struct TileSmem {
+  float4 pd[batch_rows(kRBatch<RS, NQ>) * Slots<RS, false>::N];
+  unsigned short pf[kRBatch<RS, NQ>];
+  WaveLists lists[NQ == 1 ? 4 : 1];
+  TileFrameD F;
+  QuadBoxes wb;
+  float red[12 / NQ];
+};
+
+// One tile of one camera.  out_* are indexed by pix_base + y * W + x.  GEN:
+// response of degree th.kdeg > 2.  CLIP: per-pixel clip distances (hybrid
+// rendering, Sec. 6.2), indexed as the outputs; hits beyond them are discarded.
+template <bool RS, bool NE, bool GEN, bool CLIP, int NQ>
 __device__ __forceinline__ void render_tile(
-    const DevCam& cam, const Thresholds& th, int n, int cam_idx, int tile, int part, uint32_t split_len,
+    const DevCam& cam, const Thresholds& th, int n, int cam_idx, int tile,
     const uint2* __restrict__ ranges, const uint32_t* __restrict__ ids,
     const float4* __restrict__ record, const float* __restrict__ rgb, const float* __restrict__ clip,
     float* __restrict__ out_rgb,
     float* __restrict__ out_T, uint32_t* __restrict__ out_nc, uint32_t* __restrict__ out_ne,
-    long long pix_base, float4* pd, uint32_t* pf, TileFrameD& F, QuadBoxes& wb, float* red) {
-  constexpr int S = Slots<RS, false>::N;
-  const uint2 rg = ranges[cam.tile_base + tile];
-  const uint32_t len = __builtin_amdgcn_readfirstlane(rg.y - rg.x);
-  if (part >= 0 && len < split_len) {  // too short to be worth two setups: the first block takes it all
-    if (part == 1) return;
-    part = -1;
-  }
+    long long pix_base, TileSmem<RS, NQ>& sm) {
+  constexpr int S = Slots<RS, false>::N, B = kRBatch<RS, NQ>;
+  TileFrameD& F = sm.F;
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
   const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-  // wave wv owns the quadrants wv and wv + 2: a thread has the pixels (px, py0) and (px, py0 + 8)
-  const int px = tx * kTile + 8 * wv + (lane & 7);
-  const int py0 = ty * kTile + (lane >> 3);
+  int px, py0;  // the thread's first pixel; its second lies 8 rows below
+  lane_pixel(wv, lane, &px, &py0);
+  px += tx * kTile;
+  py0 += ty * kTile;
   if (t == 0) tile_frame(cam, tx, ty, &F);
+  write_dummies<RS, false>(sm.pd, B);
+  const uint2 rg = ranges[cam.tile_base + tile];
+  const uint32_t len = __builtin_amdgcn_readfirstlane(rg.y - rg.x);
   __syncthreads();
 
-  bool inside[2], active[2];
-  float u[2] = {0.f, 0.f}, v[2] = {0.f, 0.f}, dt[2] = {0.f, 0.f};
+  bool inside[NQ], active[NQ];
+  float u[NQ], v[NQ], dt[NQ];
 #pragma unroll
-  for (int k = 0; k < 2; k++) {
-    const int py = py0 + 8 * k;
-    inside[k] = px < cam.W && py < cam.H;
-    active[k] = inside[k] && pixel_ray(cam, F, px, py, &u[k], &v[k], &dt[k]);
+  for (int k = 0; k < NQ; k++) {
+    u[k] = v[k] = dt[k] = 0.0f;
+    inside[k] = px < cam.W && py0 + 8 * k < cam.H;
+    active[k] = inside[k] && pixel_ray(cam, F, px, py0 + 8 * k, &u[k], &v[k], &dt[k]);
   }
-  // (a block of one part takes the whole tile's bounds too: the pair setup's
-  // sign classification, and with it every result, is that of the whole tile)
   float umax, vmax, dtmax;
-  tile_bounds<2>(u, v, dt, active, red, &umax, &vmax, &dtmax);
+  tile_bounds<NQ>(u, v, dt, active, sm.red, &umax, &vmax, &dtmax);
   // The pair setup reads the tile's bounds from LDS at each batch (published
   // by the batch's first barrier): kept in registers across the walk, they
   // were among the values the setup spilled at five waves per SIMD.
@@ -154,95 +179,106 @@ __device__ __forceinline__ void render_tile(
     F.dtmax = dtmax;
     F.l2amin = log2f(th.alpha_min);
   }
-  Pixel p[2];
+  Pixel p[NQ];
+  BlockBox box[NQ];
 #pragma unroll
-  for (int k = 0; k < 2; k++) {
-    quad_box(u[k], v[k], active[k], wv + 2 * k, &wb);
-    p[k].u = active[k] ? u[k] : __builtin_nanf("");
-    p[k].v = v[k];
-    p[k].dt = dt[k];
-    p[k].dlen = 1.0f;
-    p[k].clip = 0.0f;
+  for (int k = 0; k < NQ; k++) {
+    const int q = wv + 2 * k;
+    box[k] = block_box(u[k], v[k], active[k], 5e-7f * (umax + vmax), q, &sm.wb);
+    p[k] = Pixel{active[k] ? u[k] : __builtin_nanf(""), v[k], dt[k], 1.0f, 0.0f, 1.0f, {0.0, 0.0, 0.0}, 0u,
+                 active[k] ? len : 0u};
     if (CLIP) {
       if (active[k]) {
         p[k].clip = clip[pix_base + (long long)(py0 + 8 * k) * cam.W + px];
         p[k].dlen = sqrtf(fmaf(u[k], u[k], fmaf(v[k], v[k], 1.0f)));
       }
-      quad_clip_max(p[k].clip, active[k], wv + 2 * k, &wb);
+      quad_clip_max(p[k].clip, active[k], q, &sm.wb);
     }
-    p[k].T = 1.0f;
-    p[k].C[0] = p[k].C[1] = p[k].C[2] = 0.0;
-    p[k].last = 0u;
-    p[k].nev = active[k] ? len : 0u;
   }
-  // a block of one part walks only that quadrant of each wave, as p[0]
-  int qa = wv, py = py0;
-  bool two = true;
-  if (part >= 0) {
-    two = false;
-    if (part == 1) {
-      qa = wv + 2;
-      py = py0 + 8;
-      p[0] = p[1];
-      inside[0] = inside[1];
-    }
-    inside[1] = false;
-    p[1].u = __builtin_nanf("");
-  }
-  const unsigned quads = part < 0 ? 15u : part == 0 ? 3u : 12u;
 
   // long lists first in the schedule, and their waves first at issue
   if (len >= 2048) __builtin_amdgcn_s_setprio(3);
   else if (len >= 1024) __builtin_amdgcn_s_setprio(2);
   else if (len >= 256) __builtin_amdgcn_s_setprio(1);
   else __builtin_amdgcn_s_setprio(0);
-  for (uint32_t b = 0; b < len; b += kRBatch) {
+  for (uint32_t b = 0; b < len; b += B) {
     // (also publishes wb before the first setup; u == u: the pixel still runs)
-    if (__syncthreads_count(p[0].u == p[0].u || p[1].u == p[1].u) == 0) break;
+    if (__syncthreads_count(p[0].u == p[0].u || p[NQ - 1].u == p[NQ - 1].u) == 0) break;
     b = __builtin_amdgcn_readfirstlane(b);
-    uint32_t fl = 0u;
-    if (b + t < len) {
-      uint32_t e = ids[rg.x + b + t];
-      fl = pair_setup<RS, false, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n), F,
-                                      cam, F.umax, F.vmax, F.dtmax, th, F.l2amin, wb, quads,
-                                      &pd[t * S]);
+    if (t < B) {
+      uint32_t fl = 0u;
+      if (b + t < len) {
+        uint32_t e = ids[rg.x + b + t];
+        fl = pair_setup<RS, false, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n), F,
+                                              cam, F.umax, F.vmax, F.dtmax, th, F.l2amin, sm.wb,
+                                              &sm.pd[batch_row(t) * S]);
+      }
+      sm.pf[t] = (unsigned short)fl;
     }
-    pf[t] = fl;
     __syncthreads();
-    const bool run0 = wave_any(p[0].u == p[0].u), run1 = two && wave_any(p[1].u == p[1].u);
+    if constexpr (NQ == 1) {
 #pragma unroll 1
-    for (int h = 0; h < 2; h++) {
-      // the batch's pairs that may reach alpha_min somewhere in the wave's quadrants
-      const uint32_t f = pf[lane + 64 * h];
-      unsigned long long ma = run0 ? __builtin_amdgcn_ballot_w64((f >> qa) & 1u) : 0ull;
-      unsigned long long mb = run1 ? __builtin_amdgcn_ballot_w64((f >> (wv + 2)) & 1u) : 0ull;
-      const unsigned long long xm = __builtin_amdgcn_ballot_w64((f & kMixedBit) != 0u);
-      unsigned long long m = ma | mb;
-      while (m) {
-        const uint32_t ql = (uint32_t)__builtin_ctzll(m), q = 64u * h + ql;
-        m &= m - 1ull;
-        const uint32_t idx1 = b + q + 1;  // the entry's 1-based place in the list
-        const float4* P = &pd[q * S];
-        PairRegs<RS> r;
-        load_pair<RS>(P, r);
-        r.mixed = (uint32_t)(xm >> ql) & 1u;  // (from the flags: no wait on the LDS read)
-        if ((ma >> ql) & 1ull)
-          if (pixel_step<RS, NE, GEN, CLIP>(r, P, idx1, th, p[0]) && !wave_any(p[0].u == p[0].u)) {
-            ma = 0ull;
-            m &= mb;
-          }
-        if ((mb >> ql) & 1ull)
-          if (pixel_step<RS, NE, GEN, CLIP>(r, P, idx1, th, p[1]) && !wave_any(p[1].u == p[1].u)) {
-            mb = 0ull;
-            m &= ma;
-          }
+      for (int c = 0; c < B && b + c < len; c += kChunk) {
+        if (!wave_any(p[0].u == p[0].u)) break;
+        const float4* pd = &sm.pd[batch_row(c) * S];
+        const uint32_t lm = build_lists<RS, false>(pd, sm.pf + c, wv, box[0], p[0].u == p[0].u, sm.lists[wv]);
+        const int cnt = (int)(lm & ~kMixed);
+        if (cnt == 0) continue;
+        const bool mixed = (lm & kMixed) != 0u;
+        const unsigned char* mine = sm.lists[wv].row[lane >> 4];
+        // places are read two steps ahead and pairs one (the lists end in a
+        // few dummies)
+        uint32_t last = kChunk;  // the last contributor's place
+        Entry<RS> e0, e1;
+        fetch<RS>(pd, mine[0], e0);
+        uint32_t i1 = mine[1];
+        for (int k = 0; k < cnt; k += 2) {
+          fetch<RS>(pd, i1, e1);
+          i1 = mine[k + 2];
+          if (list_step<RS, NE, GEN, CLIP>(e0, b + c, mixed, th, p[0], last) && !wave_any(p[0].u == p[0].u)) break;
+          fetch<RS>(pd, i1, e0);
+          i1 = mine[k + 3];
+          if (list_step<RS, NE, GEN, CLIP>(e1, b + c, mixed, th, p[0], last) && !wave_any(p[0].u == p[0].u)) break;
+        }
+        p[0].last = last != (uint32_t)kChunk ? b + c + last + 1 : p[0].last;
+      }
+    } else {
+      const bool run0 = wave_any(p[0].u == p[0].u), run1 = wave_any(p[NQ - 1].u == p[NQ - 1].u);
+#pragma unroll 1
+      for (int h = 0; h < 2; h++) {
+        // the batch's pairs that may reach alpha_min somewhere in the wave's quadrants
+        const uint32_t f = sm.pf[lane + 64 * h];
+        unsigned long long ma = run0 ? __builtin_amdgcn_ballot_w64((f >> wv & 1u) != 0u) : 0ull;
+        unsigned long long mb = run1 ? __builtin_amdgcn_ballot_w64((f >> (wv + 2) & 1u) != 0u) : 0ull;
+        const unsigned long long xm = __builtin_amdgcn_ballot_w64((f & kMixedBit) != 0u);
+        unsigned long long m = ma | mb;
+        while (m) {
+          const uint32_t ql = (uint32_t)__builtin_ctzll(m), q = 64u * h + ql;
+          m &= m - 1ull;
+          const uint32_t idx1 = b + q + 1;  // the entry's 1-based place in the list
+          const float4* P = &sm.pd[q * S];
+          PairRegs<RS> r;
+          load_pair<RS>(P, r);
+          const bool mixed = ((uint32_t)(xm >> ql) & 1u) != 0u;
+          if ((ma >> ql) & 1ull)
+            if (pair_step<RS, NE, GEN, CLIP>(r, P, idx1, mixed, th, p[0]) && !wave_any(p[0].u == p[0].u)) {
+              ma = 0ull;
+              m &= mb;
+            }
+          if ((mb >> ql) & 1ull)
+            if (pair_step<RS, NE, GEN, CLIP>(r, P, idx1, mixed, th, p[NQ - 1]) &&
+                !wave_any(p[NQ - 1].u == p[NQ - 1].u)) {
+              mb = 0ull;
+              m &= ma;
+            }
+        }
       }
     }
   }
 #pragma unroll
-  for (int k = 0; k < 2; k++) {
+  for (int k = 0; k < NQ; k++) {
     if (!inside[k]) continue;
-    const long long pix = pix_base + (long long)(k ? py0 + 8 : py) * cam.W + px;
+    const long long pix = pix_base + (long long)(py0 + 8 * k) * cam.W + px;
     const double Tf = (double)p[k].T;
     out_rgb[3 * pix] = (float)fma(Tf, (double)th.bg[0], p[k].C[0]);
     out_rgb[3 * pix + 1] = (float)fma(Tf, (double)th.bg[1], p[k].C[1]);
@@ -253,35 +289,19 @@ __device__ __forceinline__ void render_tile(
   }
 }
 
-// The tile and part of block k of a camera's T + n_split blocks: its n_split
-// first tiles (the longest lists) take two blocks each.
-__device__ inline int block_tile(uint32_t k, uint32_t n_split, const uint32_t* __restrict__ order, int* part) {
-  if (k < 2u * n_split) {
-    *part = (int)(k & 1u);
-    return (int)order[k >> 1];
-  }
-  *part = -1;
-  return (int)order[k - n_split];
-}
-
 // One block per tile, taken in the render order (longest lists first).  NE:
 // also count each pixel's evaluated entries (out_ne non-null).
-template <bool RS, bool NE, bool GEN, bool CLIP>
-__global__ void __launch_bounds__(kRThreads, 5) render_kernel(
-    DevCam cam, Thresholds th, int n, int cam_idx, Split split, const uint2* __restrict__ ranges,
+template <bool RS, bool NE, bool GEN, bool CLIP, int NQ>
+__global__ void __launch_bounds__(kRThreads<NQ>, RS ? 3 : 5) render_kernel(
+    DevCam cam, Thresholds th, int n, int cam_idx, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ ids,
     const float4* __restrict__ record, const float* __restrict__ rgb, const float* __restrict__ clip,
     float* __restrict__ out_rgb,
     float* __restrict__ out_T, uint32_t* __restrict__ out_nc, uint32_t* __restrict__ out_ne) {
-  __shared__ float4 pd[kRBatch * Slots<RS, false>::N];
-  __shared__ uint32_t pf[kRBatch];
-  __shared__ TileFrameD F;
-  __shared__ QuadBoxes wb;
-  __shared__ float red[6];
-  int part;
-  const int tile = block_tile(blockIdx.x, (uint32_t)split.n, order + cam.tile_base, &part);
-  render_tile<RS, NE, GEN, CLIP>(cam, th, n, cam_idx, tile, part, split.len, ranges, ids, record, rgb, clip, out_rgb,
-                                 out_T, out_nc, out_ne, cam.pixel_base, pd, pf, F, wb, red);
+  __shared__ TileSmem<RS, NQ> sm;
+  const int tile = (int)order[cam.tile_base + blockIdx.x];
+  render_tile<RS, NE, GEN, CLIP, NQ>(cam, th, n, cam_idx, tile, ranges, ids, record, rgb, clip, out_rgb,
+                                 out_T, out_nc, out_ne, cam.pixel_base, sm);
 }
 
 // Several cameras of one shutter type and one tile count in one launch
@@ -299,27 +319,21 @@ struct MultiCams {
   DevCam cam[kMultiCams];
   int idx[kMultiCams];  // the cameras' indices in the call
   int n;
-  Split split;
 };
 
-template <bool RS, bool NE, bool GEN, bool CLIP>
-__global__ void __launch_bounds__(kRThreads, 5) render_multi_kernel(
+template <bool RS, bool NE, bool GEN, bool CLIP, int NQ>
+__global__ void __launch_bounds__(kRThreads<NQ>, RS ? 3 : 5) render_multi_kernel(
     MultiCams mc, Thresholds th, int n, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ ids,
     const float4* __restrict__ record, const float* __restrict__ rgb, const float* __restrict__ clip,
     float* __restrict__ out_rgb,
     float* __restrict__ out_T, uint32_t* __restrict__ out_nc, uint32_t* __restrict__ out_ne) {
-  __shared__ float4 pd[kRBatch * Slots<RS, false>::N];
-  __shared__ uint32_t pf[kRBatch];
-  __shared__ TileFrameD F;
-  __shared__ QuadBoxes wb;
-  __shared__ float red[6];
+  __shared__ TileSmem<RS, NQ> sm;
   const int c = (int)(blockIdx.x % (unsigned)mc.n), k = (int)(blockIdx.x / (unsigned)mc.n);
   const DevCam& cam = mc.cam[c];
-  int part;
-  const int tile = block_tile((uint32_t)k, (uint32_t)mc.split.n, order + cam.tile_base, &part);
-  render_tile<RS, NE, GEN, CLIP>(cam, th, n, mc.idx[c], tile, part, mc.split.len, ranges, ids, record, rgb, clip, out_rgb,
-                                 out_T, out_nc, out_ne, cam.pixel_base, pd, pf, F, wb, red);
+  const int tile = (int)order[cam.tile_base + k];
+  render_tile<RS, NE, GEN, CLIP, NQ>(cam, th, n, mc.idx[c], tile, ranges, ids, record, rgb, clip, out_rgb,
+                                 out_T, out_nc, out_ne, cam.pixel_base, sm);
 }
 
 // Persistent render of the cameras of one shutter type in a multi-camera
@@ -329,18 +343,16 @@ __global__ void __launch_bounds__(kRThreads, 5) render_multi_kernel(
 // share longest-first; a block that drains its XCD's share steals from the
 // others, and leaves once every counter is past its share.  Images go to
 // outs[camera] ([H, W, 3]).
+template <bool RS>
+constexpr int kBatchNQ = RS ? 1 : 2;
 template <bool RS, bool GEN>
-__global__ void __launch_bounds__(kRThreads, RS ? 3 : 4) render_batch_kernel(
+__global__ void __launch_bounds__(kRThreads<kBatchNQ<RS>>, RS ? 3 : 4) render_batch_kernel(
     const DevCam* __restrict__ cams, const int* __restrict__ cam_list,
     const int* __restrict__ item_start, int n_list, int n_items, unsigned* __restrict__ counters,
     Thresholds th, int n, const uint2* __restrict__ ranges, const uint32_t* __restrict__ order,
     const uint32_t* __restrict__ ids,
     const float4* __restrict__ record, const float* __restrict__ rgb, float* const* __restrict__ outs) {
-  __shared__ float4 pd[kRBatch * Slots<RS, false>::N];
-  __shared__ uint32_t pf[kRBatch];
-  __shared__ TileFrameD F;
-  __shared__ QuadBoxes wb;
-  __shared__ float red[6];
+  __shared__ TileSmem<RS, kBatchNQ<RS>> sm;
   __shared__ int item_s;
   const int nx = 8;
   const int my = blockIdx.x % nx;
@@ -369,8 +381,8 @@ __global__ void __launch_bounds__(kRThreads, RS ? 3 : 4) render_batch_kernel(
     const int c = __builtin_amdgcn_readfirstlane(cam_list[j]);
     const DevCam& cam = cams[c];
     const int tile = (int)order[cam.tile_base + (item - item_start[j])];
-    render_tile<RS, false, GEN, false>(cam, th, n, c, tile, -1, 0u, ranges, ids, record, rgb, nullptr, outs[c],
-                                       nullptr, nullptr, nullptr, 0, pd, pf, F, wb, red);
+    render_tile<RS, false, GEN, false, kBatchNQ<RS>>(cam, th, n, c, tile, ranges, ids, record, rgb, nullptr, outs[c],
+                                       nullptr, nullptr, nullptr, 0, sm);
   }
 }
 
@@ -401,7 +413,7 @@ gut_status render_batch_launch(const DevCam* d_cams, const DevCam* h_cams, int n
     int* dl = d_lists + type * (2 * kMaxCams + 1);
     GUT_HIP(hipMemcpyAsync(dl, hl, (2 * kMaxCams + 1) * sizeof(int), hipMemcpyHostToDevice, s));
 #define GUT_RB(RS, GEN)                                                                          \
-  render_batch_kernel<RS, GEN><<<n_blocks, kRThreads, 0, s>>>(                                    \
+  render_batch_kernel<RS, GEN><<<n_blocks, kRThreads<kBatchNQ<RS>>, 0, s>>>(                                    \
       d_cams, dl, dl + kMaxCams, m, items, d_counters + 8 * type, th, n, (const uint2*)ranges, order, \
       ids, (const float4*)record, rgb, d_outs)
     const bool gen = th.kdeg != 2;
@@ -530,18 +542,22 @@ __global__ void __launch_bounds__(kKThreads, 4) render_kbuffer_kernel(
     float* __restrict__ out_rgb,
     float* __restrict__ out_T, uint32_t* __restrict__ out_nc, uint32_t* __restrict__ out_ne) {
   constexpr int S = Slots<RS, false>::N;
-  __shared__ float4 pd[kKThreads * S];
-  __shared__ uint32_t pf[kKThreads];
+  __shared__ float4 pd[batch_rows(kKThreads) * S];
+  __shared__ unsigned short pf[kKThreads];
+  __shared__ WaveLists lists[kKThreads / 64];
   __shared__ float cw[kKWin * 3];
   __shared__ TileFrameD F;
   __shared__ QuadBoxes wb;
   __shared__ float red[12];
   const int tile = (int)order[cam.tile_base + blockIdx.x];
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
-  const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
-  const int px = tx * kTile + 8 * (wv & 1) + (lane & 7);
-  const int py = ty * kTile + 8 * (wv >> 1) + (lane >> 3);
+  const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  int px, py;
+  lane_pixel(wv, lane, &px, &py);
+  px += tx * kTile;
+  py += ty * kTile;
   if (t == 0) tile_frame(cam, tx, ty, &F);
+  write_dummies<RS, false>(pd, kKThreads);
   __syncthreads();
   const bool inside = px < cam.W && py < cam.H;
   float u = 0.f, v = 0.f, dt = 0.f;
@@ -549,7 +565,7 @@ __global__ void __launch_bounds__(kKThreads, 4) render_kbuffer_kernel(
   float umax, vmax, dtmax;
   tile_bounds<1>(&u, &v, &dt, &active, red, &umax, &vmax, &dtmax);
   const float l2amin = log2f(th.alpha_min);
-  quad_box(u, v, active, wv, &wb);
+  const BlockBox box = block_box(u, v, active, 5e-7f * (umax + vmax), wv, &wb);
   const float dlen = sqrtf(fmaf(u, u, fmaf(v, v, 1.0f)));
   float clipv = 0.0f;  // hybrid rendering (Sec. 6.2), as in render_tile
   if (CLIP) {
@@ -581,23 +597,27 @@ __global__ void __launch_bounds__(kKThreads, 4) render_kbuffer_kernel(
       float* c = cw + 3 * ((b + t) & (kKWin - 1));
       c[0] = rgb[3 * (size_t)e]; c[1] = rgb[3 * (size_t)e + 1]; c[2] = rgb[3 * (size_t)e + 2];
       fl = pair_setup<RS, false, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n),
-                                            F, cam, umax, vmax, dtmax, th, l2amin, wb, 15u,
-                                            &pd[t * S]);
+                                            F, cam, umax, vmax, dtmax, th, l2amin, wb,
+                                            &pd[batch_row(t) * S]);
     }
-    pf[t] = fl;
+    pf[t] = (unsigned short)fl;
     __syncthreads();
-    bool wave_done = false;
-    for (int h = 0; h < kKThreads / 64 && !wave_done; h++) {
-      unsigned long long m = __builtin_amdgcn_ballot_w64((pf[lane + 64 * h] >> wv) & 1u);
-      while (m) {
-        if (!wave_any(done == 0u)) { wave_done = true; break; }
-        const uint32_t q = 64u * h + (uint32_t)__builtin_ctzll(m);
-        m &= m - 1ull;
-        const float4* P = &pd[q * S];
+#pragma unroll 1
+    for (int c = 0; c < kKThreads && b + c < len; c += kChunk) {
+      if (!wave_any(done == 0u)) break;
+      const float4* pc = &pd[batch_row(c) * S];
+      const uint32_t lm = build_lists<RS, false>(pc, pf + c, wv, box, done == 0u, lists[wv]);
+      const int cnt = (int)(lm & ~kMixed);
+      const bool mixed = (lm & kMixed) != 0u;
+      const unsigned char* mine = lists[wv].row[lane >> 4];
+      for (int k = 0; k < cnt; k++) {
+        if (!wave_any(done == 0u)) break;
+        const uint32_t i = mine[k], q = c + i;  // (per row of lanes)
+        const float4* P = pc + i * S;
         PairRegs<RS> r;
         load_pair<RS>(P, r);
         Eval ev;
-        eval_test<RS>(r, P, u, v, dt, &ev);
+        eval_test<RS>(r, P, u, v, dt, mixed, &ev);
         if (CLIP) clip_test<RS>(r, P, u, v, dt, dlen, clipv, &ev);
         const bool live = eval_hit<RS>(r, ev) && done == 0u;
         if (!wave_any(live)) continue;
@@ -704,17 +724,28 @@ static gut_status launch_render_kbuffer(const DevCam& cam, const Thresholds& th,
   return GUT_OK;
 }
 
+// Quadrants per wave of a launch over this many tiles.  Up to 10000 tiles a
+// launch ends with its longest lists or has few waves to hide a step's latency
+// behind, and the lists win (ms per render, lists against pairs): 1k particles
+// 128x128 0.014 (0.017), 300k 800x600 rolling 0.32 (0.51), 1M 1280x720 0.33
+// (0.38), 3M 1600x1200 rolling (7500 tiles) 0.53 (0.64), one 1M fisheye
+// 1920x1080 view (8160) 0.30 (0.29).  Beyond, the vector ALUs are full either
+// way (250M instructions) and the pairs' shorter waits win: two 1M 1920x1080
+// views (16320) 0.60 (0.55).
+static int quads_per_wave(unsigned tiles) { return tiles < 10000u ? 1 : 2; }
+
 gut_status launch_render(const DevCam& cam, const Thresholds& th, int n, int cam_idx,
                          const uint32_t* ranges, const uint32_t* order, const uint32_t* ids,
                          const float* record, const float* rgb, const float* clip, float* out_rgb,
                          float* out_T, uint32_t* out_nc, uint32_t* out_ne, hipStream_t s) {
-  const int T = cam.tiles_x * cam.tiles_y;
-  const Split split = split_tiles(T, 1);
-  dim3 grid(T + split.n), block(kRThreads);
-#define GUT_RK(RS, NE, GEN, CLIP)                                                                  \
-  render_kernel<RS, NE, GEN, CLIP><<<grid, block, 0, s>>>(cam, th, n, cam_idx, split, (const uint2*)ranges, \
+  dim3 grid(cam.tiles_x * cam.tiles_y);
+  const int nq = quads_per_wave(grid.x);
+#define GUT_RKQ(RS, NE, GEN, CLIP, NQ)                                                             \
+  render_kernel<RS, NE, GEN, CLIP, NQ><<<grid, kRThreads<NQ>, 0, s>>>(cam, th, n, cam_idx, (const uint2*)ranges, \
                                                           order, ids, (const float4*)record, rgb,     \
                                                           clip, out_rgb, out_T, out_nc, out_ne)
+#define GUT_RK(RS, NE, GEN, CLIP) \
+  do { if (nq == 1) GUT_RKQ(RS, NE, GEN, CLIP, 1); else GUT_RKQ(RS, NE, GEN, CLIP, 2); } while (0)
 #define GUT_RK1(RS, NE, GEN) \
   if (clip) GUT_RK(RS, NE, GEN, true); else GUT_RK(RS, NE, GEN, false)
 #define GUT_RK2(RS, NE) \
@@ -725,6 +756,7 @@ gut_status launch_render(const DevCam& cam, const Thresholds& th, int n, int cam
 #undef GUT_RK2
 #undef GUT_RK1
 #undef GUT_RK
+#undef GUT_RKQ
   GUT_LAUNCH_CHECK();
   return GUT_OK;
 }
@@ -745,13 +777,14 @@ static gut_status launch_render_group(const DevCam* dc, int c0, int c1, const Th
     mc.cam[k] = dc[c0 + k];
     mc.idx[k] = c0 + k;
   }
-  const int T = dc[c0].tiles_x * dc[c0].tiles_y;
-  mc.split = split_tiles(T, mc.n);
-  dim3 grid(mc.n * (T + mc.split.n)), block(kRThreads);
-#define GUT_RM(RS, NE, GEN, CLIP)                                                                    \
-  render_multi_kernel<RS, NE, GEN, CLIP><<<grid, block, 0, s>>>(mc, th, n, (const uint2*)ranges, order, \
+  dim3 grid(mc.n * dc[c0].tiles_x * dc[c0].tiles_y);
+  const int nq = quads_per_wave(grid.x);
+#define GUT_RMQ(RS, NE, GEN, CLIP, NQ)                                                               \
+  render_multi_kernel<RS, NE, GEN, CLIP, NQ><<<grid, kRThreads<NQ>, 0, s>>>(mc, th, n, (const uint2*)ranges, order, \
                                                                 ids, (const float4*)record, rgb, clip,  \
                                                                 out_rgb, out_T, out_nc, out_ne)
+#define GUT_RM(RS, NE, GEN, CLIP) \
+  do { if (nq == 1) GUT_RMQ(RS, NE, GEN, CLIP, 1); else GUT_RMQ(RS, NE, GEN, CLIP, 2); } while (0)
 #define GUT_RM1(RS, NE, GEN) \
   if (clip) GUT_RM(RS, NE, GEN, true); else GUT_RM(RS, NE, GEN, false)
 #define GUT_RM2(RS, NE) \
@@ -762,6 +795,7 @@ static gut_status launch_render_group(const DevCam* dc, int c0, int c1, const Th
 #undef GUT_RM2
 #undef GUT_RM1
 #undef GUT_RM
+#undef GUT_RMQ
   GUT_LAUNCH_CHECK();
   return GUT_OK;
 }

@@ -15,11 +15,11 @@
 // in canonical space, d omega^2/d o_g = 2p and d omega^2/d d_g = 2 tau p
 // (Supp. B), so with M = S^-1 R^T the per-pixel gradients are
 //   dL/dmu = -M^T c p,   dL/dM = c p (M^-1 p)^T,   c = 2 dL/domega^2.
-// They only depend on G = sum c p p^T (6 values) and h = sum c p (3): each
-// wave sums those plus dL/dsigma and dL/dc over its lanes (FP32, one
-// reduce-scatter for all 13) and issues one FP64 atomic per value per
-// (wave, particle) from 13 lanes at once, so the per-particle totals carry no
-// order-dependent FP32 rounding.
+// They only depend on G = sum c p p^T (6 values) and h = sum c p (3): those
+// plus dL/dsigma and dL/dc are summed over the pixels of a 4 x 4 block in FP32
+// (one reduce-scatter for all 13), over the tile in FP64 in LDS, and over the
+// tiles by one FP64 atomic per value and (tile, particle), so the
+// per-particle totals carry no order-dependent FP32 rounding.
 //
 // K7 (per particle) then applies M = S^-1 R^T:
 //   dL/ds_k = -G_kk / s_k,   dL/dR = R S G S^-1,   dL/dmu = -R S^-1 h,
@@ -34,49 +34,122 @@ namespace gut {
 
 constexpr int kAcc = 10;  // G xx,xy,xz,yy,yz,zz ; h x,y,z ; dL/dsigma
 
-// Sums 16 per-lane values over the wave as a reduce-scatter: at each of the
-// first four butterfly steps a lane keeps half of its values and adds its
-// partner's copy of that half, then two plain steps finish the sum.  The
-// 32- and 16-lane steps use the half-wave and row swaps (one instruction
-// exchanges a lane's kept and sent values with its partner's), the 8- and
-// 4-lane steps DPP row rotate and half-mirror, the last two DPP quad
-// permutes: no LDS traffic.  Afterwards lane l holds the total of value
-// (l >> 2) & 15.
+// Sums 16 per-lane values over each row of 16 lanes as a reduce-scatter (DPP
+// only): at each step a lane keeps half of its values and adds its partner's
+// copy of that half.  Lane l then holds its row's total of value l mod 16.
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
-__device__ inline float wave_reduce16(const float* g) {
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ float row_reduce16(const float (&g)[16], int lane) {
   float h8[8], h4[4], h2[2];
+  const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2, b0 = lane & 1;
 #pragma unroll
-  for (int j = 0; j < 8; j++) {  // lanes 0-31 keep g[j], lanes 32-63 keep g[j + 8]
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(g[j]), __float_as_uint(g[j + 8]),
-                                                   false, false);
-    h8[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
+  for (int j = 0; j < 8; j++)  // partner lane ^ 8 (row rotate by 8)
+    h8[j] = (b3 ? g[j + 8] : g[j]) + dpp<0x128>(b3 ? g[j] : g[j + 8]);
 #pragma unroll
-  for (int j = 0; j < 4; j++) {  // even rows keep h8[j], odd rows h8[j + 4]
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(h8[j]), __float_as_uint(h8[j + 4]),
-                                                   false, false);
-    h4[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  const bool b3 = lane & 8, b2 = lane & 4;
+  for (int j = 0; j < 4; j++)  // partner 7 - (lane mod 8) (row half-mirror): differs in bit 2
+    h4[j] = (b2 ? h8[j + 4] : h8[j]) + dpp<0x141>(b2 ? h8[j] : h8[j + 4]);
 #pragma unroll
-  for (int j = 0; j < 2; j++) {  // partner lane ^ 8 (row rotate by 8)
-    const float keep = b3 ? h4[j + 2] : h4[j], send = b3 ? h4[j] : h4[j + 2];
-    h2[j] = keep + dpp<0x128>(send);
-  }
-  // partner 7 - (lane mod 8) within each 8 (row half-mirror): differs in bit 2
-  float h = (b2 ? h2[1] : h2[0]) + dpp<0x141>(b2 ? h2[0] : h2[1]);
-  h += dpp<0x1B>(h);  // quad mirror (0,3) (1,2)
-  h += dpp<0xB1>(h);  // quad xor 1
-  return h;
+  for (int j = 0; j < 2; j++)  // partner 3 - (lane mod 4) (quad mirror): differs in bit 1
+    h2[j] = (b1 ? h4[j + 2] : h4[j]) + dpp<0x1B>(b1 ? h4[j] : h4[j + 2]);
+  return (b0 ? h2[1] : h2[0]) + dpp<0xB1>(b0 ? h2[0] : h2[1]);  // partner lane ^ 1
 }
 
-constexpr int kBwThreads = 128;
-constexpr int kBwBatch = kBwThreads;
+constexpr int kBwThreads = 256;
+constexpr int kBwBatch = 128;  // pairs of 192 bytes: three blocks a CU, as many waves as the registers allow
+constexpr int kRow = kAcc + 3;  // sums per pair
 
+// A thread's pixel.  Its contributors lie before list position `last` (0:
+// none, or outside the image).  T and Z run along the list: the transmittance,
+// and Z = sum_c gC_c (C_c - C_<=j,c) in FP64 (C the output colour, C_<=j the
+// running colour including entry j), which is all the suffix sums S_after
+// enter the gradient through; gTT = T_N gT.
+struct BwPixel {
+  float u, v, dt, dlen, clip, T, gC[3], gTT;
+  double Z;
+  uint32_t last;
+};
+
+// One step: each lane's own list entry (at list position idx) against its
+// pixel: the pixel's terms of the entry's sums, G = sum c p p^T (symmetric,
+// 6), h = sum c p (3), dL/dsigma, dL/dc (3), zero where it is not hit.
+// Returns false when no lane is hit (g is then not written).
+template <bool RS, bool GEN, bool CLIP>
+__device__ __forceinline__ bool bwd_step(const float4* P, uint32_t idx, bool mixed, const Thresholds& th,
+                                         BwPixel& p, float (&g)[16]) {
+  PairRegs<RS> r;
+  load_pair<RS>(P, r);
+  Eval ev;
+  eval_test<RS>(r, P, p.u, p.v, p.dt, mixed, &ev);
+  if (CLIP) clip_test<RS>(r, P, p.u, p.v, p.dt, p.dlen, p.clip, &ev);
+  const bool in = idx < p.last, on = eval_hit<RS>(r, ev);
+  if ((__builtin_amdgcn_ballot_w64(on) & __builtin_amdgcn_ballot_w64(in)) == 0ull) return false;
+  const bool hit = on && in;
+  double cold[3];
+  pair_colour<RS>(P, cold);
+  eval_alpha<RS, GEN>(r, th, &ev);
+  const float Tb = p.T;
+  const float ae = hit ? ev.a : 0.0f;
+  const float wgt = ae * Tb;
+  p.T = fmaf(-ae, Tb, Tb);  // the forward's update, bit for bit
+  // D = gC . c_j; after this entry Z = sum_c gC_c (C_c - C_<=j,c)
+  const double D = fma((double)p.gC[0], cold[0], fma((double)p.gC[1], cold[1], (double)p.gC[2] * cold[2]));
+  p.Z = fma(-(double)wgt, D, p.Z);
+  // dL/dalpha = T_j gC.c_j - (gC.(C - C_<=j) + gT T_N) / (1 - alpha_j)
+  const float inv1m = __builtin_amdgcn_rcpf(1.0f - ev.a);
+  float gA = fmaf(Tb, (float)D, -inv1m * ((float)p.Z + p.gTT));
+  const bool geo = hit && !ev.clamped;  // alpha = alpha_max carries no gradient
+  gA = geo ? gA : 0.0f;
+  // 2 dL/domega^2; a degree-n response scales d alpha / d omega^2 by
+  // 2 lambda (n/2) (omega^2)^(n/2 - 1) relative to the Gaussian's
+  // (0 for a lane that is not hit, whose omega may be infinite)
+  float c = -ev.a * gA;
+  if (GEN) c = geo ? c * __builtin_amdgcn_exp2f(fmaf(th.k_h - 1.0f, ev.lq, th.k_f)) : 0.0f;
+  float3 dg, cr;
+  pair_vectors<RS>(P, ev, p.u, p.v, &dg, &cr);
+  float3 q = cross3f_fma(dg, cr);
+  q = f3(q.x * ev.idd, q.y * ev.idd, q.z * ev.idd);
+  const float3 cq = f3(c * q.x, c * q.y, c * q.z);
+  g[0] = cq.x * q.x;
+  g[1] = cq.x * q.y;
+  g[2] = cq.x * q.z;
+  g[3] = cq.y * q.y;
+  g[4] = cq.y * q.z;
+  g[5] = cq.z * q.z;
+  g[6] = cq.x;
+  g[7] = cq.y;
+  g[8] = cq.z;
+  g[9] = gA * (ev.araw * __builtin_amdgcn_exp2f(-r.lsig));  // rho = (sigma rho) / sigma
+  g[10] = wgt * p.gC[0];
+  g[11] = wgt * p.gC[1];
+  g[12] = wgt * p.gC[2];
+  g[13] = g[14] = g[15] = 0.0f;
+  return true;
+}
+
+// Adds the batch's rows to the per-particle sums and clears them: 16 lanes per
+// row, so that a particle's values go out together.
+__device__ inline void bwd_flush(double* rows, const uint32_t* pe, int m, int n, int cam_idx,
+                                 double* __restrict__ acc, double* __restrict__ acc_rgb) {
+  const int k = threadIdx.x & 15;
+  if (k >= kRow) return;
+  for (int r = threadIdx.x >> 4; r < m; r += kBwThreads / 16) {
+    const double x = rows[r * kRow + k];
+    if (x == 0.0) continue;
+    rows[r * kRow + k] = 0.0;
+    const uint32_t e = pe[r];
+    const long long i = (long long)(e - (uint32_t)cam_idx * (uint32_t)n);
+    if (k < kAcc) atomicAdd(&acc[i * kAcc + k], x);
+    else atomicAdd(&acc_rgb[3 * (long long)e + (k - kAcc)], x);
+  }
+}
+
+// The forward's blocks, pixels, pair setup and lists.  A step sums its pixels'
+// terms over each row of lanes (up to four different pairs at once) and adds
+// the rows' totals to the pairs' rows in LDS, in FP64; a row goes to the
+// per-particle sums when its batch is done, one atomic per value and (tile,
+// particle).
 template <bool RS, bool GEN, bool CLIP>
 __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
     DevCam cam, Thresholds th, int n, int cam_idx, const uint2* __restrict__ ranges,
@@ -87,173 +160,95 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
     const float* __restrict__ d_rgb, const float* __restrict__ d_T, double* __restrict__ acc,
     double* __restrict__ acc_rgb) {
   constexpr int S = Slots<RS, true>::N;
-  __shared__ float4 pd[kBwBatch * S];
-  __shared__ uint32_t pe[kBwBatch];
-  __shared__ uint32_t pf[kBwBatch];
+  __shared__ float4 pd[batch_rows(kBwBatch) * S];
+  __shared__ double rows[kBwBatch * kRow];
+  __shared__ uint32_t pe[2][kBwBatch];  // the entries of this batch and of the one before
+  __shared__ unsigned short pf[kBwBatch];
+  __shared__ WaveLists lists[kBwThreads / 64];
   __shared__ TileFrameD F;
   __shared__ QuadBoxes wb;
-  __shared__ float red[6];
+  __shared__ float red[12];
   __shared__ uint32_t maxlast_s;
 
   const int tile = (int)order[cam.tile_base + blockIdx.x];  // longest lists first
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
-  const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
-  // the forward's pixel layout: wave wv owns the quadrants wv and wv + 2
-  const int px = tx * kTile + 8 * wv + (lane & 7);
-  const int py0 = ty * kTile + (lane >> 3);
+  const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  int px, py;
+  lane_pixel(wv, lane, &px, &py);
+  px += tx * kTile;
+  py += ty * kTile;
   if (t == 0) { tile_frame(cam, tx, ty, &F); maxlast_s = 0; }
+  write_dummies<RS, true>(pd, kBwBatch);
+  for (int i = t; i < kBwBatch * kRow; i += kBwThreads) rows[i] = 0.0;
   __syncthreads();
 
-  bool active[2];
-  float u[2] = {0.f, 0.f}, v[2] = {0.f, 0.f}, dt[2] = {0.f, 0.f};
-#pragma unroll
-  for (int k = 0; k < 2; k++) {
-    const int py = py0 + 8 * k;
-    active[k] = px < cam.W && py < cam.H && pixel_ray(cam, F, px, py, &u[k], &v[k], &dt[k]);
-  }
+  BwPixel p = {};
+  const bool active = px < cam.W && py < cam.H && pixel_ray(cam, F, px, py, &p.u, &p.v, &p.dt);
   float umax, vmax, dtmax;
-  tile_bounds<2>(u, v, dt, active, red, &umax, &vmax, &dtmax);
+  tile_bounds<1>(&p.u, &p.v, &p.dt, &active, red, &umax, &vmax, &dtmax);
   const float l2amin = log2f(th.alpha_min);
-  for (int k = 0; k < 2; k++) quad_box(u[k], v[k], active[k], wv + 2 * k, &wb);
-  float clipv[2] = {0.f, 0.f}, dlen[2] = {1.f, 1.f};  // the forward's clip test operands
-  if (CLIP) {
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-      if (!active[k]) continue;
-      clipv[k] = clip[cam.pixel_base + (long long)(py0 + 8 * k) * cam.W + px];
-      dlen[k] = sqrtf(fmaf(u[k], u[k], fmaf(v[k], v[k], 1.0f)));
+  const BlockBox box = block_box(p.u, p.v, active, 5e-7f * (umax + vmax), wv, &wb);
+  const long long pix = cam.pixel_base + (long long)py * cam.W + px;
+  if (CLIP) {  // the forward's clip test operands
+    if (active) {
+      p.clip = clip[pix];
+      p.dlen = sqrtf(fmaf(p.u, p.u, fmaf(p.v, p.v, 1.0f)));
     }
-    for (int k = 0; k < 2; k++) quad_clip_max(clipv[k], active[k], wv + 2 * k, &wb);
+    quad_clip_max(p.clip, active, wv, &wb);
   }
-
-  // Per pixel: the loss gradients, T_N gT, and Z = sum_c gC_c (C_c - C_<=j,c)
-  // in FP64 (C the output colour, C_<=j the running colour including entry
-  // j), which is all the suffix sums S_after enter the gradient through.
-  uint32_t last[2] = {0u, 0u};
-  float gC[2][3] = {{0, 0, 0}, {0, 0, 0}}, gTT[2] = {0.f, 0.f};
-  double gCd[2][3] = {{0, 0, 0}, {0, 0, 0}}, Z[2] = {0.0, 0.0};
-#pragma unroll
-  for (int k = 0; k < 2; k++) {
-    if (!active[k]) continue;
-    const long long pix = cam.pixel_base + (long long)(py0 + 8 * k) * cam.W + px;
-    last[k] = out_nc[pix];
-    gTT[k] = (d_T ? d_T[pix] : 0.0f) * out_T[pix];
+  p.T = 1.0f;
+  if (active) {
+    p.last = out_nc[pix];
+    p.gTT = (d_T ? d_T[pix] : 0.0f) * out_T[pix];
     for (int c = 0; c < 3; c++) {
-      gC[k][c] = d_rgb[3 * pix + c];
-      gCd[k][c] = gC[k][c];
-      Z[k] = fma(gCd[k][c], (double)out_rgb[3 * pix + c], Z[k]);
+      p.gC[c] = d_rgb[3 * pix + c];
+      p.Z = fma((double)p.gC[c], (double)out_rgb[3 * pix + c], p.Z);
     }
   }
-  atomicMax(&maxlast_s, max(last[0], last[1]));
+  atomicMax(&maxlast_s, p.last);
   __syncthreads();  // (also publishes wb)
   const uint2 rg = ranges[cam.tile_base + tile];
-  const uint32_t maxlast = min(maxlast_s, rg.y - rg.x);  // never past the tile's list
+  // never past the tile's list
+  const uint32_t maxlast = __builtin_amdgcn_readfirstlane(min(maxlast_s, rg.y - rg.x));
   if (maxlast >= 2048) __builtin_amdgcn_s_setprio(3);
   else if (maxlast >= 1024) __builtin_amdgcn_s_setprio(2);
   else if (maxlast >= 256) __builtin_amdgcn_s_setprio(1);
 
-  float T[2] = {1.0f, 1.0f};
+  int par = 0, m = 0;  // pairs of the batch in rows
   for (uint32_t b = 0; b < maxlast; b += kBwBatch) {
-    __syncthreads();
-    uint32_t fl = 0u;
-    if (b + t < maxlast) {
-      uint32_t e = ids[rg.x + b + t];
-      pe[t] = e;
-      fl = pair_setup<RS, true, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n), F,
-                                     cam, umax, vmax, dtmax, th, l2amin, wb, 15u, &pd[t * S]);
+    if (b) {
+      __syncthreads();
+      bwd_flush(rows, pe[par], m, n, cam_idx, acc, acc_rgb);
+      par ^= 1;
     }
-    pf[t] = fl;
-    __syncthreads();
-    // the same pairs the forward walked for these quadrants
-    const uint32_t mine = 5u << wv;  // the wave's quadrants
-    const unsigned long long m0 = __builtin_amdgcn_ballot_w64((pf[lane] & mine) != 0u);
-    const unsigned long long m1 = __builtin_amdgcn_ballot_w64((pf[lane + 64] & mine) != 0u);
-    bool wave_done = false;
-    for (int hh = 0; hh < 2 && !wave_done; hh++) {
-      unsigned long long m = hh ? m1 : m0;
-      while (m) {
-        const uint32_t q = 64u * hh + (uint32_t)__builtin_ctzll(m);
-        m &= m - 1ull;
-        const uint32_t idx = b + q;
-        if (!wave_any(idx < last[0] || idx < last[1])) { wave_done = true; break; }
-        const float4* P = &pd[q * S];
-        PairRegs<RS> r;
-        load_pair<RS>(P, r);
-        Eval ev[2];
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-          eval_test<RS>(r, P, u[k], v[k], dt[k], &ev[k]);
-          if (CLIP) clip_test<RS>(r, P, u[k], v[k], dt[k], dlen[k], clipv[k], &ev[k]);
-        }
-        bool hit[2];
-        hit[0] = eval_hit<RS>(r, ev[0]) && idx < last[0];
-        hit[1] = eval_hit<RS>(r, ev[1]) && idx < last[1];
-        if (!wave_any(hit[0] || hit[1])) continue;  // wave-uniform
-        double cold[3];
-        pair_colour<RS>(P, cold);
-        const float isig = __builtin_amdgcn_exp2f(-r.lsig);  // 1 / sigma, shared by both pixels
-        float gk[2][9], wfk[2], gAk[2], rhok[2];
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-          eval_alpha<RS, GEN>(r, th, &ev[k]);
-          const float Tb = T[k];
-          const float ae = hit[k] ? ev[k].a : 0.0f;
-          const float wgt = ae * Tb;
-          T[k] = fmaf(-ae, Tb, Tb);  // the forward's update, bit for bit
-          wfk[k] = wgt;
-          // D = gC . c_j; after this entry Z = sum_c gC_c (C_c - C_<=j,c)
-          const double D = fma(gCd[k][0], cold[0], fma(gCd[k][1], cold[1], gCd[k][2] * cold[2]));
-          Z[k] = fma(-(double)wgt, D, Z[k]);
-          // dL/dalpha = T_j gC.c_j - (gC.(C - C_<=j) + gT T_N) / (1 - alpha_j)
-          const float inv1m = __builtin_amdgcn_rcpf(1.0f - ev[k].a);
-          float gA = fmaf(Tb, (float)D, -inv1m * ((float)Z[k] + gTT[k]));
-          const bool geo = hit[k] && !ev[k].clamped;  // alpha = alpha_max carries no gradient
-          gA = geo ? gA : 0.0f;
-          // rho = exp(-omega^2 / 2) = (sigma rho) / sigma
-          gAk[k] = gA;
-          rhok[k] = ev[k].araw * isig;
-          // 2 dL/domega^2; a degree-n response scales d alpha / d omega^2 by
-          // 2 lambda (n/2) (omega^2)^(n/2 - 1) relative to the Gaussian's
-          float c = -ev[k].a * gA;
-          // (0 for a lane that is not hit, whose omega may be infinite)
-          if (GEN) c = geo ? c * __builtin_amdgcn_exp2f(fmaf(th.k_h - 1.0f, ev[k].lq, th.k_f)) : 0.0f;
-          float3 dg, cr;
-          pair_vectors<RS>(P, ev[k], u[k], v[k], &dg, &cr);
-          float3 p = cross3f_fma(dg, cr);
-          p = f3(p.x * ev[k].idd, p.y * ev[k].idd, p.z * ev[k].idd);
-          const float3 cp = f3(c * p.x, c * p.y, c * p.z);
-          // G terms are cp p^T: kept as factors so the two pixels combine in fmas
-          gk[k][0] = p.x; gk[k][1] = p.y; gk[k][2] = p.z;
-          gk[k][6] = cp.x; gk[k][7] = cp.y; gk[k][8] = cp.z;
-        }
-        float g[16];  // kAcc + 3 values, padded for the reduction
-        // G (symmetric, 6), h = sum c p (3), dL/dsigma, dL/dc (3)
-        g[0] = fmaf(gk[0][6], gk[0][0], gk[1][6] * gk[1][0]);
-        g[1] = fmaf(gk[0][6], gk[0][1], gk[1][6] * gk[1][1]);
-        g[2] = fmaf(gk[0][6], gk[0][2], gk[1][6] * gk[1][2]);
-        g[3] = fmaf(gk[0][7], gk[0][1], gk[1][7] * gk[1][1]);
-        g[4] = fmaf(gk[0][7], gk[0][2], gk[1][7] * gk[1][2]);
-        g[5] = fmaf(gk[0][8], gk[0][2], gk[1][8] * gk[1][2]);
-        g[6] = gk[0][6] + gk[1][6];
-        g[7] = gk[0][7] + gk[1][7];
-        g[8] = gk[0][8] + gk[1][8];
-        g[9] = fmaf(gAk[0], rhok[0], gAk[1] * rhok[1]);
-#pragma unroll
-        for (int c = 0; c < 3; c++) g[kAcc + c] = fmaf(wfk[0], gC[0][c], wfk[1] * gC[1][c]);
-#pragma unroll
-        for (int j = kAcc + 3; j < 16; j++) g[j] = 0.0f;
-        // one lane per value issues its atomic: lanes 4k hold value k
-        const float tot = wave_reduce16(g);
-        const int k = lane >> 2;
-        if ((lane & 3) == 0 && k < kAcc + 3 && tot != 0.0f) {
-          const uint32_t e = pe[q];
-          const int i = (int)(e - (uint32_t)cam_idx * (uint32_t)n);
-          if (k < kAcc) atomicAdd(&acc[(long long)i * kAcc + k], (double)tot);
-          else atomicAdd(&acc_rgb[3 * (long long)e + (k - kAcc)], (double)tot);
-        }
+    m = (int)min(maxlast - b, (uint32_t)kBwBatch);
+    if (t < kBwBatch) {
+      uint32_t fl = 0u;
+      if (t < m) {
+        const uint32_t e = ids[rg.x + b + t];
+        pe[par][t] = e;
+        fl = pair_setup<RS, true, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n), F,
+                                             cam, umax, vmax, dtmax, th, l2amin, wb, &pd[t * S]);
       }
+      pf[t] = (unsigned short)fl;
+    }
+    __syncthreads();
+    if (!wave_any(b < p.last)) continue;
+    // (the blocks' pixels that still have contributors: a subset of the forward's)
+    const uint32_t lm = build_lists<RS, true>(pd, pf, wv, box, b < p.last, lists[wv]);
+    const int cnt = (int)(lm & ~kMixed);
+    const bool mixed = (lm & kMixed) != 0u;
+    const unsigned char* mine = lists[wv].row[lane >> 4];
+    for (int k = 0; k < cnt; k++) {
+      const uint32_t i = mine[k];
+      float g[16];
+      if (!bwd_step<RS, GEN, CLIP>(pd + i * S, b + i, mixed, th, p, g)) continue;
+      const float tot = row_reduce16(g, lane);
+      if ((lane & 15) < kRow && tot != 0.0f) atomicAdd(&rows[i * kRow + (lane & 15)], (double)tot);
     }
   }
+  __syncthreads();
+  bwd_flush(rows, pe[par], m, n, cam_idx, acc, acc_rgb);
 }
 
 // Backward of the k-buffer render ("Ours (sorted)", Sec. 4.3).  It replays
@@ -284,8 +279,7 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
 // sums itself.
 constexpr int kKBufB = 16;
 constexpr int kKThreadsB = 256;
-constexpr int kWin = 2 * kKThreadsB;  // list positions with an LDS row
-constexpr int kRow = kAcc + 3;        // values per row (13: an odd stride spreads rows over the banks)
+constexpr int kWin = 2 * kKThreadsB;  // list positions with an LDS row (of 13 values: an odd stride spreads them over the banks)
 
 struct KBufGrad {
   double* acc;
@@ -382,8 +376,9 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
     const float* __restrict__ out_T, const float* __restrict__ d_rgb, const float* __restrict__ d_T,
     double* __restrict__ acc, double* __restrict__ acc_rgb) {
   constexpr int S = Slots<RS, true>::N;
-  __shared__ float4 pd[kKThreadsB * S];
-  __shared__ uint32_t pf[kKThreadsB];
+  __shared__ float4 pd[batch_rows(kKThreadsB) * S];
+  __shared__ unsigned short pf[kKThreadsB];
+  __shared__ WaveLists lists[kKThreadsB / 64];
   __shared__ uint32_t pew[kWin];
   __shared__ float accw[kWin * kRow];
   __shared__ TileFrameD F;
@@ -391,10 +386,13 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   __shared__ float red[12];
   const int tile = (int)order[cam.tile_base + blockIdx.x];
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
-  const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
-  const int px = tx * kTile + 8 * (wv & 1) + (lane & 7);
-  const int py = ty * kTile + 8 * (wv >> 1) + (lane >> 3);
+  const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  int px, py;
+  lane_pixel(wv, lane, &px, &py);
+  px += tx * kTile;
+  py += ty * kTile;
   if (t == 0) tile_frame(cam, tx, ty, &F);
+  write_dummies<RS, true>(pd, kKThreadsB);
   for (int i = t; i < kWin * kRow; i += kKThreadsB) accw[i] = 0.0f;
   __syncthreads();
   const bool inside = px < cam.W && py < cam.H;
@@ -403,7 +401,7 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   float umax, vmax, dtmax;
   tile_bounds<1>(&u, &v, &dt, &active, red, &umax, &vmax, &dtmax);
   const float l2amin = log2f(th.alpha_min);
-  quad_box(u, v, active, wv, &wb);
+  const BlockBox box = block_box(u, v, active, 5e-7f * (umax + vmax), wv, &wb);
   const float dlen = sqrtf(fmaf(u, u, fmaf(v, v, 1.0f)));
   float clipv = 0.0f;  // the forward's clip operands
   if (CLIP) {
@@ -449,23 +447,26 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
       const uint32_t e = ids[rg.x + b + t];
       pew[half + t] = e;
       fl = pair_setup<RS, true, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n),
-                                           F, cam, umax, vmax, dtmax, th, l2amin, wb, 15u,
-                                           &pd[t * S]);
+                                           F, cam, umax, vmax, dtmax, th, l2amin, wb, &pd[batch_row(t) * S]);
     }
-    pf[t] = fl;
+    pf[t] = (unsigned short)fl;
     __syncthreads();
-    bool wave_done = false;
-    for (int h = 0; h < kKThreadsB / 64 && !wave_done; h++) {
-      unsigned long long m = __builtin_amdgcn_ballot_w64((pf[lane + 64 * h] >> wv) & 1u);
-      while (m) {
-        if (!wave_any(done == 0u)) { wave_done = true; break; }
-        const uint32_t q = 64u * h + (uint32_t)__builtin_ctzll(m);
-        m &= m - 1ull;
-        const float4* P = &pd[q * S];
+#pragma unroll 1
+    for (int c = 0; c < kKThreadsB && b + c < len; c += kChunk) {
+      if (!wave_any(done == 0u)) break;
+      const float4* pc = &pd[batch_row(c) * S];
+      const uint32_t lm = build_lists<RS, true>(pc, pf + c, wv, box, done == 0u, lists[wv]);
+      const int cnt = (int)(lm & ~kMixed);
+      const bool mixed = (lm & kMixed) != 0u;
+      const unsigned char* mine = lists[wv].row[lane >> 4];
+      for (int k = 0; k < cnt; k++) {
+        if (!wave_any(done == 0u)) break;
+        const uint32_t i = mine[k], q = c + i;  // (per row of lanes)
+        const float4* P = pc + i * S;
         PairRegs<RS> r;
         load_pair<RS>(P, r);
         Eval ev;
-        eval_test<RS>(r, P, u, v, dt, &ev);
+        eval_test<RS>(r, P, u, v, dt, mixed, &ev);
         if (CLIP) clip_test<RS>(r, P, u, v, dt, dlen, clipv, &ev);
         const bool live = eval_hit<RS>(r, ev) && done == 0u;
         if (!wave_any(live)) continue;
@@ -763,8 +764,8 @@ static gut_status render_bwd_run(const gut_scene* scene, const gut_projected* pr
     dim3 grid(dc[c].tiles_x * dc[c].tiles_y), block(kBwThreads);
 #define GUT_RBW(RS, GEN, CLIP)                                                                      \
   render_bwd_kernel<RS, GEN, CLIP><<<grid, block, 0, s>>>(                                           \
-      dc[c], th, (int)n, c, (const uint2*)tile_ranges, order, sorted_ids, (const float4*)proj->record, \
-      clip_depth, proj->rgb, rgb, T_final, n_contrib, d_rgb, d_T, acc, acc_rgb)
+      dc[c], th, (int)n, c, (const uint2*)tile_ranges, order, sorted_ids,                         \
+      (const float4*)proj->record, clip_depth, proj->rgb, rgb, T_final, n_contrib, d_rgb, d_T, acc, acc_rgb)
 #define GUT_RBW1(RS, GEN) \
   if (clip_depth) GUT_RBW(RS, GEN, true); else GUT_RBW(RS, GEN, false)
     const bool gen = th.kdeg != 2;

@@ -83,33 +83,35 @@ constexpr double kHalfLog2e = 0.72134752044448170368;
 //   |d_g|^2                 = (g1 + h11 u + h12 v)^2 + (g2 + h22 v)^2 + g3
 // so a pixel needs 10 FMAs for both and no term cancels beyond what the
 // affine maps themselves carry.
-//   0: f1 r11 r12 Kp    1: f2 r22 f3 lsig    2: g1 h11 h12 mixed
-//   3: g2 h22 g3 -      4: colour r g (FP64)  5: s ta tb -
-//   6: colour b (FP64), -
+//   0: f1 r11 r12 Kp    1: f2 r22 f3 lsig    2: g1 h11 h12 E11
+//   3: g2 h22 g3 E12    4: colour r g (FP64)  5: s ta tb E22
+//   6: colour b (FP64), uc vc
 // and, for the backward only, the vectors for the closest point p:
 //   7: d_g(n).xyz w.x   8: d_g(e1).xyz w.y   9: d_g(e2).xyz w.z
 //  10: A.xyz B.x       11: B.y B.z - -
 // Rolling shutter.  The origin moves with the row, so the cross product is
 // bilinear in (u, v) and dt and is formed from its vectors per pixel:
-//   0: d_g(n).xyz mixed  1: d_g(e1).xyz lsig  2: d_g(e2).xyz Kp
+//   0: d_g(n).xyz E11    1: d_g(e1).xyz lsig  2: d_g(e2).xyz Kp
 //   3: w.xyz ta          4: A.xyz tb          5: B.xyz s
 //   6: colour r g (FP64) 7: (m x d_g(n)).xyz m.d_g(n)
 //   8: (m x d_g(e1)).xyz m.d_g(e1)               9: (m x d_g(e2)).xyz m.d_g(e2)
-//  10: colour b (FP64), -
+//  10: colour b (FP64), uc vc  11: E12 E22 - -
 // (colours are kept in FP64 because the compositing accumulates in FP64)
 // Here w = o_g x d_g(n), A = o_g x d_g(e1), B = o_g x d_g(e2),
 // s, ta, tb = o_g . d_g(.) (the tau_max > 0 test, needed per pixel only when
-// its sign varies over the tile: mixed = -1), lsig = log2(sigma) and
+// its sign varies over the tile: then E11 carries a minus sign), lsig = log2(sigma) and
 // Kp = log2(sigma / alpha_min) (-1: never contributes), so that
 //   alpha = min(2^(lsig - omega'^2), alpha_max),  alpha >= alpha_min <=> omega'^2 <= Kp
-// with omega'^2 = omega^2 log2(e) / 2.
+// with omega'^2 = omega^2 log2(e) / 2.  E11, E12, E22 and (uc, vc) are the
+// culling ellipse's matrix, scaled so that it reads E11 x^2 + 2 E12 xy + E22
+// y^2 <= 1, and its centre, for build_lists (E = 0: no culling).
 // Bit of pair_setup's result set when the sign of o_g . d_g varies over the
 // tile (the per-pixel tau_max > 0 test is needed); the low bits are per quadrant.
 constexpr unsigned kMixedBit = 1u << 8;
 
 template <bool RS, bool BWD>
 struct Slots {
-  static constexpr int N = RS ? 11 : (BWD ? 12 : 7);
+  static constexpr int N = RS ? 12 : (BWD ? 12 : 7);
 };
 
 // 1 / sqrt(x) for a normal x > 0: the hardware estimate (relative error
@@ -175,8 +177,7 @@ __device__ inline bool ellipse_meets_box(double qmin, double N11, double N12, do
 }
 
 // Forms a pair's slots (FP64 -> FP32) and returns one bit per quadrant: bit k
-// set when quadrant k's pixel box may see alpha >= alpha_min (only those set
-// in `quads`, which is uniform over the block, are tested).  GEN:
+// set when quadrant k's pixel box may see alpha >= alpha_min.  GEN:
 // the response has degree th.kdeg > 2, and the threshold kept in Kp is the
 // one on omega'^2 where the degree-n exponent reaches log2(sigma / alpha_min).
 // CLIP (hybrid rendering): a quadrant whose largest clip distance (wb.cmax) lies
@@ -187,7 +188,7 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
                                       const float* __restrict__ rgb, long long e, int i,
                                       const TileFrameD& F, const DevCam& cam, float umax,
                                       float vmax, float dtmax, const Thresholds& th,
-                                      float log2_amin, const QuadBoxes& wb, unsigned quads, float4* out) {
+                                      float log2_amin, const QuadBoxes& wb, float4* out) {
   const float amin = th.alpha_min;
   float4 r0 = record[4 * (long long)i], r1 = record[4 * (long long)i + 1];
   float4 r2 = record[4 * (long long)i + 2], r3 = record[4 * (long long)i + 3];
@@ -223,7 +224,6 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
   float Kp = (!never && sigma >= amin) ? lsig - log2_amin : -1.0f;
   // degree n: 2^(k_h log2 q + k_l) <= Kp  <=>  q <= 2^((log2 Kp - k_l) / k_h)
   if (GEN && Kp > 0.0f) Kp = exp2f((log2f(Kp) - th.k_l) * th.k_inv_h);
-  const float mflag = mixed ? -1.0f : 1.0f;
   // the per-pixel test uses this FP32 Kp; cull with it in natural units
   double Kc = (double)Kp / kHalfLog2e * (1.0 + 1e-3) + 1e-5;
   if (RS) {
@@ -245,7 +245,7 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
     affine_qr(dn, da, db, qd);
     out[0] = make_float4((float)qc[0], (float)qc[1], (float)qc[2], Kp);
     out[1] = make_float4((float)qc[3], (float)qc[4], (float)qc[5], lsig);
-    out[2] = make_float4((float)qd[0], (float)qd[1], (float)qd[2], mflag);
+    out[2] = make_float4((float)qd[0], (float)qd[1], (float)qd[2], 0.0f);
     out[3] = make_float4((float)qd[3], (float)qd[4], (float)qd[5], 0.0f);
     out[5] = make_float4((float)s, (float)ta, (float)tb, 0.0f);
     if (BWD) {
@@ -264,9 +264,10 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
     N22 = fma(-K2, fma(qd[2], qd[2], qd[4] * qd[4]), fma(qc[2], qc[2], qc[4] * qc[4]));
   }
   unsigned flags = 0;
+  float E11 = 0.0f, E12 = 0.0f, E22 = 0.0f, ecu = 0.0f, ecv = 0.0f;
   if (Kp >= 0.0f) {
     if (oo <= Kc) {
-      flags = quads;  // the ray origin is inside the particle's alpha_min ellipsoid
+      flags = 15u;  // the ray origin is inside the particle's alpha_min ellipsoid
     } else {
       if (RS) {
         N00 = fma(-Kc, dot(dn, dn), dot(w, w));
@@ -278,7 +279,7 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
       }
       const double det = fma(N11, N22, -N12 * N12);
       if (!(N11 > 0.0) || !(N22 > 0.0) || !(det > 1e-9 * N11 * N22)) {
-        flags = quads;  // not a well-conditioned ellipse in the tile plane: no culling
+        flags = 15u;  // not a well-conditioned ellipse in the tile plane: no culling
       } else {
         // 1/det, 1/N11 and 1/N22 from one division
         const double p11 = N11 * N22, rq = 1.0 / (det * p11);
@@ -287,9 +288,14 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
         const double qmin = fma(N02, vc, fma(N01, uc, N00));
         if (qmin < 0.0) {
           const double iN11 = det * N22 * rq, iN22 = det * N11 * rq;
+          const double sc = -__builtin_amdgcn_rcp(qmin);
+          E11 = (float)(N11 * sc);
+          E12 = (float)(N12 * sc);
+          E22 = (float)(N22 * sc);
+          ecu = (float)uc;
+          ecv = (float)vc;
           for (int k = 0; k < 4; k++)
-            if ((quads >> k & 1u) &&
-                ellipse_meets_box(qmin, N11, N12, N22, iN11, iN22, wb.u0[k] - uc, wb.u1[k] - uc,
+            if (ellipse_meets_box(qmin, N11, N12, N22, iN11, iN22, wb.u0[k] - uc, wb.u1[k] - uc,
                                   wb.v0[k] - vc, wb.v1[k] - vc))
               flags |= 1u << k;
         }
@@ -312,13 +318,20 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
     for (int k = 0; k < 4; k++)
       if (lb > (double)wb.cmax[k] * (1.0 + 1e-4)) flags &= ~(1u << k);
   }
-  if (mixed && flags) flags |= kMixedBit;
+  if (mixed && flags) {
+    flags |= kMixedBit;
+    E11 = -E11;  // (also -0)
+  }
   const float* c = rgb + 3 * e;
   if (!RS) {
     reinterpret_cast<double2*>(out + 4)[0] = make_double2(c[0], c[1]);
-    reinterpret_cast<double2*>(out + 6)[0] = make_double2(c[2], 0.0);
+    reinterpret_cast<double*>(out + 6)[0] = c[2];
+    out[2].w = E11;
+    out[3].w = E12;
+    out[5].w = E22;
+    reinterpret_cast<float2*>(out + 6)[1] = make_float2(ecu, ecv);
   } else {
-    out[0] = make_float4((float)dn.x, (float)dn.y, (float)dn.z, mflag);
+    out[0] = make_float4((float)dn.x, (float)dn.y, (float)dn.z, E11);
     out[1] = make_float4((float)da.x, (float)da.y, (float)da.z, lsig);
     out[2] = make_float4((float)db.x, (float)db.y, (float)db.z, Kp);
     out[3] = make_float4((float)w.x, (float)w.y, (float)w.z, (float)ta);
@@ -328,7 +341,9 @@ __device__ inline unsigned pair_setup(const float4* __restrict__ record,
     out[7] = make_float4((float)w2.x, (float)w2.y, (float)w2.z, (float)s2);
     out[8] = make_float4((float)A2.x, (float)A2.y, (float)A2.z, (float)ta2);
     out[9] = make_float4((float)B2.x, (float)B2.y, (float)B2.z, (float)tb2);
-    reinterpret_cast<double2*>(out + 10)[0] = make_double2(c[2], 0.0);
+    reinterpret_cast<double*>(out + 10)[0] = c[2];
+    reinterpret_cast<float2*>(out + 10)[1] = make_float2(ecu, ecv);
+    out[11] = make_float4(E12, E22, 0.0f, 0.0f);
   }
   return flags;
 }
@@ -344,13 +359,12 @@ struct Eval {
   float3 dg, cr; // rolling shutter only: d_g and o_g x d_g
 };
 
-// One pair's decision terms, loaded from LDS once and shared by the pixels a thread owns.
+// One pair's decision terms, loaded from LDS.
 template <bool RS>
 struct PairRegs {
   float4 p0, p1, p2, p3, p4, p5;
   float4 p7, p8, p9;
-  uint32_t mixed;  // not 0: sign of o_g . d_g varies across the tile (wave-uniform)
-  float lsig, Kp;
+  float lsig, Kp, flag;  // flag: a minus sign if the sign of o_g . d_g varies over the tile
 };
 
 template <bool RS>
@@ -358,24 +372,22 @@ __device__ __forceinline__ void load_pair(const float4* P, PairRegs<RS>& r) {
   r.p0 = P[0]; r.p1 = P[1]; r.p2 = P[2]; r.p3 = P[3];
   if (RS) {
     r.p4 = P[4]; r.p5 = P[5]; r.p7 = P[7]; r.p8 = P[8]; r.p9 = P[9];
-    r.lsig = r.p1.w; r.Kp = r.p2.w;
-    // every lane reads the same pair: move the flag to a scalar register
-    r.mixed = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(r.p0.w)) & 0x80000000u;
+    r.lsig = r.p1.w; r.Kp = r.p2.w; r.flag = r.p0.w;
   } else {
-    r.lsig = r.p1.w; r.Kp = r.p0.w;
-    r.mixed = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(r.p2.w)) & 0x80000000u;
+    r.lsig = r.p1.w; r.Kp = r.p0.w; r.flag = r.p2.w;
   }
 }
 
 // Stage 1 of the response on one pixel ray (Eq. 11): omega'^2 |d_g|^2 and
 // |d_g|^2, for eval_hit's test omega'^2 <= Kp (<=> alpha >= alpha_min)
-// without any transcendental.  Where the tau_max > 0 test (and clip_test's
+// without any transcendental (mixed: the chunk holds pairs whose tau_max sign
+// varies over the tile).  Where the tau_max > 0 test (and clip_test's
 // clip) discards the hit it sets cc to +inf, so that eval_hit stays one
 // bare compare: a ballot of a combined lane flag goes through a vector
 // register, two instructions more.
 template <bool RS>
 __device__ __forceinline__ void eval_test(const PairRegs<RS>& r, const float4* P, float u, float v,
-                                          float dt, Eval* o) {
+                                          float dt, bool mixed, Eval* o) {
   if (!RS) {
     const float t1 = fmaf(v, r.p0.z, fmaf(u, r.p0.y, r.p0.x));
     const float t2 = fmaf(v, r.p1.y, r.p1.x);
@@ -383,9 +395,10 @@ __device__ __forceinline__ void eval_test(const PairRegs<RS>& r, const float4* P
     const float e1 = fmaf(v, r.p2.z, fmaf(u, r.p2.y, r.p2.x));
     const float e2 = fmaf(v, r.p3.y, r.p3.x);
     o->dd = fmaf(e1, e1, fmaf(e2, e2, r.p3.z));
-    if (r.mixed) {  // rare, and uniform across the wave
+    if (mixed) {  // rare, and uniform across the wave
       const float4 p5 = P[5];
-      o->cc = fmaf(v, p5.z, fmaf(u, p5.y, p5.x)) < 0.0f ? o->cc : INFINITY;
+      const float sg = fmaf(v, p5.z, fmaf(u, p5.y, p5.x));
+      o->cc = sg < 0.0f || !__builtin_signbitf(r.flag) ? o->cc : INFINITY;
     }
   } else {
     float3 dg = f3(fmaf(v, r.p2.x, fmaf(u, r.p1.x, r.p0.x)), fmaf(v, r.p2.y, fmaf(u, r.p1.y, r.p0.y)),
@@ -397,10 +410,10 @@ __device__ __forceinline__ void eval_test(const PairRegs<RS>& r, const float4* P
     cr = f3(fmaf(dt, m.x, cr.x), fmaf(dt, m.y, cr.y), fmaf(dt, m.z, cr.z));
     o->dd = fmaf(dg.z, dg.z, fmaf(dg.y, dg.y, dg.x * dg.x));
     o->cc = fmaf(cr.z, cr.z, fmaf(cr.y, cr.y, cr.x * cr.x)) * (float)kHalfLog2e;
-    if (r.mixed) {
+    if (mixed) {
       float sg = fmaf(v, r.p4.w, fmaf(u, r.p3.w, r.p5.w));
       sg = fmaf(dt, fmaf(v, r.p9.w, fmaf(u, r.p8.w, r.p7.w)), sg);
-      o->cc = sg < 0.0f ? o->cc : INFINITY;
+      o->cc = sg < 0.0f || !__builtin_signbitf(r.flag) ? o->cc : INFINITY;
     }
     o->dg = dg;
     o->cr = cr;
@@ -458,10 +471,9 @@ __device__ __forceinline__ void clip_test(const PairRegs<RS>& r, const float4* P
 template <bool RS>
 __device__ __forceinline__ void pair_colour(const float4* P, double c[3]) {
   const double2 rg = reinterpret_cast<const double2*>(P + (RS ? 6 : 4))[0];
-  const double2 b = reinterpret_cast<const double2*>(P + (RS ? 10 : 6))[0];
   c[0] = rg.x;
   c[1] = rg.y;
-  c[2] = b.x;
+  c[2] = reinterpret_cast<const double*>(P + (RS ? 10 : 6))[0];
 }
 
 // Backward only: d_g and o_g x d_g on the pixel ray (unscaled), for the
@@ -481,31 +493,72 @@ __device__ __forceinline__ void pair_vectors(const float4* P, const Eval& ev, fl
   }
 }
 
-// Block-wide maxima of |u|, |v|, |dt| over the tile's valid pixels (NP per thread).
-template <int NP>
-__device__ inline void tile_bounds(const float* u, const float* v, const float* dt,
-                                   const bool* valid, float* red, float* umax, float* vmax,
-                                   float* dtmax) {
+// ---- a wave's quadrant, its four 4 x 4 blocks and their lists of pairs
+//
+// A tile is four 8 x 8 quadrants, each walked by one wave, and a wave is four
+// rows of 16 lanes, one 4 x 4 pixel block each.  A row walks its own list of
+// pairs, so one step of a wave takes up to four different pairs, one per
+// block, and a pair costs a step only for the blocks it can reach.  The
+// particles are a few pixels wide: of the 8 x 8 quadrants that a pair reaches,
+// half the 4 x 4 blocks are missed (1M particles, 1920x1080: 3.27M quadrants
+// against 10.2M blocks, 2.5M steps, pinhole; 2.35M against 5.4M, 1.35M steps,
+// fisheye; 300k, 800x600 rolling: 0.52M against 0.90M, 0.22M steps).
+__device__ inline void lane_pixel(int q, int lane, int* x, int* y) {  // of quadrant q
+  *x = 8 * (q & 1) + 4 * ((lane >> 4) & 1) + (lane & 3);
+  *y = 8 * (q >> 1) + 4 * (lane >> 5) + ((lane >> 2) & 3);
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_or_self(float x) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, ROWS, 0xF, false));
+}
+// (med3 against an infinity: a max or min that does not quieten its operands first)
+struct OpMax {
+  __device__ float operator()(float a, float b) const { return __builtin_amdgcn_fmed3f(a, b, INFINITY); }
+};
+struct OpMin {
+  __device__ float operator()(float a, float b) const { return __builtin_amdgcn_fmed3f(a, b, -INFINITY); }
+};
+// Reduction over each row of 16 lanes, in all its lanes (DPP rotations: two
+// instructions a step, where a shuffle through LDS takes about six).
+template <class Op>
+__device__ __forceinline__ float row_reduce(float x) {
+  Op op;
+  x = op(x, dpp_or_self<0x128, 0xF>(x));
+  x = op(x, dpp_or_self<0x124, 0xF>(x));
+  x = op(x, dpp_or_self<0x122, 0xF>(x));
+  return op(x, dpp_or_self<0x121, 0xF>(x));
+}
+// From there over the wave's four rows, in lane 63 (row broadcasts).
+template <class Op>
+__device__ __forceinline__ float rows_reduce63(float x) {
+  Op op;
+  x = op(x, dpp_or_self<0x142, 0xA>(x));
+  return op(x, dpp_or_self<0x143, 0xC>(x));
+}
+
+// Block-wide maxima of |u|, |v|, |dt| over the tile's valid pixels (NQ per
+// thread, in a block of 256 / NQ).
+template <int NQ>
+__device__ inline void tile_bounds(const float* u, const float* v, const float* dt, const bool* valid,
+                                   float* red, float* umax, float* vmax, float* dtmax) {
   float a = 0.0f, b = 0.0f, c = 0.0f;
 #pragma unroll
-  for (int k = 0; k < NP; k++) {
-    if (valid[k]) {
-      a = fmaxf(a, fabsf(u[k]));
-      b = fmaxf(b, fabsf(v[k]));
-      c = fmaxf(c, fabsf(dt[k]));
-    }
+  for (int k = 0; k < NQ; k++) {
+    a = valid[k] ? fmaxf(a, fabsf(u[k])) : a;
+    b = valid[k] ? fmaxf(b, fabsf(v[k])) : b;
+    c = valid[k] ? fmaxf(c, fabsf(dt[k])) : c;
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    a = fmaxf(a, __shfl_xor(a, o, 64));
-    b = fmaxf(b, __shfl_xor(b, o, 64));
-    c = fmaxf(c, __shfl_xor(c, o, 64));
-  }
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if ((threadIdx.x & 63) == 0) { red[3 * w] = a; red[3 * w + 1] = b; red[3 * w + 2] = c; }
+  a = rows_reduce63<OpMax>(row_reduce<OpMax>(a));
+  b = rows_reduce63<OpMax>(row_reduce<OpMax>(b));
+  c = rows_reduce63<OpMax>(row_reduce<OpMax>(c));
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 63) { red[3 * w] = a; red[3 * w + 1] = b; red[3 * w + 2] = c; }
   __syncthreads();
   float A = 0, B = 0, Cc = 0;
-  for (int k = 0; k < nw; k++) {
+#pragma unroll
+  for (int k = 0; k < 4 / NQ; k++) {
     A = fmaxf(A, red[3 * k]);
     B = fmaxf(B, red[3 * k + 1]);
     Cc = fmaxf(Cc, red[3 * k + 2]);
@@ -516,46 +569,126 @@ __device__ inline void tile_bounds(const float* u, const float* v, const float* 
   *dtmax = Cc * 1.0001f + 1e-7f;
 }
 
-// Pixel box (u, v) of quadrant k, whose pixels the calling wave's lanes hold,
-// written to LDS by lane 0.
-__device__ inline void quad_box(float u, float v, bool valid, int k, QuadBoxes* wb) {
-  float a0 = valid ? u : 3e38f, a1 = valid ? u : -3e38f, b0 = valid ? v : 3e38f, b1 = valid ? v : -3e38f;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    a0 = fminf(a0, __shfl_xor(a0, o, 64));
-    a1 = fmaxf(a1, __shfl_xor(a1, o, 64));
-    b0 = fminf(b0, __shfl_xor(b0, o, 64));
-    b1 = fmaxf(b1, __shfl_xor(b1, o, 64));
-  }
-  if ((threadIdx.x & 63) == 0) {
+// Pixel box of the lane's 4 x 4 block, a little larger than the pixels (by
+// more than FP32 rounding of an ellipse's centre within the tile).
+struct BlockBox {
+  float u0, u1, v0, v1;
+};
+// The lane's block box; the box of the wave's quadrant k goes to LDS.
+__device__ inline BlockBox block_box(float u, float v, bool valid, float slack, int k, QuadBoxes* wb) {
+  BlockBox b;
+  b.u0 = row_reduce<OpMin>(valid ? u : 3e38f);
+  b.u1 = row_reduce<OpMax>(valid ? u : -3e38f);
+  b.v0 = row_reduce<OpMin>(valid ? v : 3e38f);
+  b.v1 = row_reduce<OpMax>(valid ? v : -3e38f);
+  const float a0 = rows_reduce63<OpMin>(b.u0), a1 = rows_reduce63<OpMax>(b.u1);
+  const float b0 = rows_reduce63<OpMin>(b.v0), b1 = rows_reduce63<OpMax>(b.v1);
+  if ((threadIdx.x & 63) == 63) {
     wb->u0[k] = a0; wb->u1[k] = a1; wb->v0[k] = b0; wb->v1[k] = b1;
   }
+  b.u0 -= slack; b.u1 += slack; b.v0 -= slack; b.v1 += slack;
+  return b;
 }
 
 // Largest clip distance over quadrant k's valid pixels (+inf if any is
 // unclipped; -inf if the quadrant has no valid pixel).
 __device__ inline void quad_clip_max(float clip, bool valid, int k, QuadBoxes* wb) {
-  float c = valid ? clip : -INFINITY;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) c = fmaxf(c, __shfl_xor(c, o, 64));
-  if ((threadIdx.x & 63) == 0) wb->cmax[k] = c;
+  const float c = rows_reduce63<OpMax>(row_reduce<OpMax>(valid ? clip : -INFINITY));
+  if ((threadIdx.x & 63) == 63) wb->cmax[k] = c;
+}
+
+// A batch's pairs lie in LDS in chunks of kChunk rows, each followed by a row
+// for a pair that hits nothing (kChunk as a place in the chunk).
+constexpr int kChunk = 128;
+__host__ __device__ constexpr int batch_rows(int batch) { return batch + (batch + kChunk - 1) / kChunk; }
+__device__ __forceinline__ int batch_row(int t) { return t + t / kChunk; }
+// omega^2 = 0, |d_g| = 1, Kp = -1, at the rows behind each chunk.
+template <bool RS, bool BWD>
+__device__ inline void write_dummies(float4* pd, int batch) {
+  constexpr int S = Slots<RS, BWD>::N;
+  for (int i = threadIdx.x; i < (batch + kChunk - 1) / kChunk * S; i += blockDim.x) {
+    const int t = i % S;
+    pd[((i / S + 1) * (kChunk + 1) - 1) * S + t] =
+        RS ? make_float4(t == 0 ? 1.0f : 0.0f, 0.0f, 0.0f, t == 2 ? -1.0f : 0.0f)
+           : make_float4(0.0f, 0.0f, t == 3 ? 1.0f : 0.0f, t == 0 ? -1.0f : 0.0f);
+  }
+}
+
+// A wave's lists: of each of its blocks, the places in the chunk of the pairs
+// that may reach it, in order, padded to the longest and by four more with
+// kChunk.
+constexpr int kListStride = kChunk + 4;
+struct WaveLists {
+  unsigned char row[4][kListStride];
+  unsigned char quad[kChunk];  // the pairs that reach the quadrant
+};
+
+// Builds the wave's lists for one chunk (pd: its first row, pf: its pairs'
+// flags) of quadrant q and returns the longest's length, with kMixed set if
+// the sign of o_g . d_g varies over the tile for one of their pairs.  The pairs flagged for quadrant q
+// are packed first; then each row of lanes tests 16 of them at a time against
+// its own block (a convex quadratic over a box as in ellipse_meets_box, here
+// in FP32 with slack for its rounding, relative to the quadratic's own terms
+// and 1e-4 of the ellipse, whose K' already carries 1e-3), so the test costs
+// about three instructions per pair and quadrant.  run: the lane's pixel has
+// not stopped; a block without such a pixel takes no pairs.
+constexpr uint32_t kMixed = 1u << 31;
+template <bool RS, bool BWD>
+__device__ inline uint32_t build_lists(const float4* pd, const unsigned short* pf, int q, const BlockBox& box,
+                                       bool run,                                       WaveLists& L) {
+  constexpr int S = Slots<RS, BWD>::N;
+  const int lane = threadIdx.x & 63, j0 = lane & 15;
+  const uint32_t f0 = pf[lane], f1 = pf[lane + 64];
+  const unsigned long long m0 = __builtin_amdgcn_ballot_w64((f0 >> q & 1u) != 0u);
+  const unsigned long long m1 = __builtin_amdgcn_ballot_w64((f1 >> q & 1u) != 0u);
+  const int c0 = __builtin_popcountll(m0), F = c0 + __builtin_popcountll(m1);
+  if (F == 0) return 0u;
+  const unsigned long long x0 = __builtin_amdgcn_ballot_w64((f0 & kMixedBit) != 0u);
+  const unsigned long long x1 = __builtin_amdgcn_ballot_w64((f1 & kMixedBit) != 0u);
+  const uint32_t mixed = ((m0 & x0) | (m1 & x1)) != 0ull ? kMixed : 0u;
+  auto below = [](unsigned long long m) __attribute__((always_inline)) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  };
+  if (f0 >> q & 1u) L.quad[below(m0)] = (unsigned char)lane;
+  if (f1 >> q & 1u) L.quad[c0 + below(m1)] = (unsigned char)(lane + 64);
+  __builtin_amdgcn_wave_barrier();  // (one wave's LDS accesses stay in order)
+  auto row_bits = [&](unsigned long long m) __attribute__((always_inline)) {
+    return (lane & 32 ? (uint32_t)(m >> 32) : (uint32_t)m) >> (lane & 16) & 0xffffu;
+  };
+  const bool alive = row_bits(__builtin_amdgcn_ballot_w64(run)) != 0u;
+  unsigned char* mine = L.row[lane >> 4];
+  uint32_t cnt = 0;
+  for (int it = 0; it < F; it += 16) {
+    const int j = it + j0;
+    const uint32_t i = L.quad[min(j, F - 1)];
+    const float4* P = pd + i * S;
+    const float2 c = reinterpret_cast<const float2*>(P + (RS ? 10 : 6))[1];
+    const float E11 = fabsf(P[RS ? 0 : 2].w), E12 = RS ? P[11].x : P[3].w, E22 = RS ? P[11].y : P[5].w;
+    const float a0 = box.u0 - c.x, a1 = box.u1 - c.x, b0 = box.v0 - c.y, b1 = box.v1 - c.y;
+    const float x = __builtin_amdgcn_fmed3f(0.0f, a0, a1), y = __builtin_amdgcn_fmed3f(0.0f, b0, b1);
+    const float ye = __builtin_amdgcn_fmed3f(-E12 * x * __builtin_amdgcn_rcpf(E22), b0, b1);
+    const float xe = __builtin_amdgcn_fmed3f(-E12 * y * __builtin_amdgcn_rcpf(E11), a0, a1);
+    auto meets = [&](float X, float Y) __attribute__((always_inline)) {
+      const float d = fmaf(E11 * X, X, E22 * Y * Y);
+      return !(fmaf(2.0f * E12 * X, Y, d) > fmaf(4e-6f, d, 1.0001f));  // (a NaN counts as a hit)
+    };
+    const bool keep = j < F && alive && (meets(x, ye) || meets(xe, y));
+    const uint32_t bits = row_bits(__builtin_amdgcn_ballot_w64(keep));
+    if (keep) mine[cnt + __builtin_popcount(bits & ((1u << j0) - 1u))] = (unsigned char)i;
+    cnt += __builtin_popcount(bits);
+  }
+  const uint32_t n0 = __builtin_amdgcn_readlane(cnt, 0), n1 = __builtin_amdgcn_readlane(cnt, 16);
+  const uint32_t n2 = __builtin_amdgcn_readlane(cnt, 32), n3 = __builtin_amdgcn_readlane(cnt, 48);
+  const uint32_t most = max(max(n0, n1), max(n2, n3));
+  for (uint32_t k = cnt + j0; k < most + 4; k += 16) mine[k] = (unsigned char)kChunk;
+  __builtin_amdgcn_wave_barrier();
+  return __builtin_amdgcn_readfirstlane(most | mixed);
 }
 
 // True when pred holds on some active lane (the wave's lane mask, without a
 // round trip through a vector register).
 __device__ __forceinline__ bool wave_any(bool pred) {
   return __builtin_amdgcn_ballot_w64(pred) != 0ull;
-}
-
-// Tile visited by block b: blocks are dealt round-robin to the 8 XCDs, so
-// give each XCD a contiguous run of tiles (neighbouring tiles share most of
-// their particles, and each XCD has its own L2).
-__device__ inline int xcd_tile(int b, int n) {
-  const int nx = 8;
-  int x = b % nx, j = b / nx;
-  int q = n / nx, r = n % nx;
-  int start = x * q + min(x, r);
-  return start + j;
 }
 
 }  // namespace gut
