@@ -6,7 +6,7 @@
 // tile's list, and each list is ordered by (depth, entry id).  Instead of a
 // global sort of all pairs by a (tile, depth) key, the lists are built by a
 // counting sort over tiles followed by one small sort per list:
-//   K1 bin_count_kernel     each block of up to 8192 entries (128 units of 64
+//   K1 bin_count_kernel     each block of 1024 to 8192 entries (units of 64
 //                           neighbouring ones, strided over the camera)
 //                           counts its pairs per tile in LDS and writes the
 //                           counts as one row of a (block x tile) matrix
@@ -47,8 +47,7 @@ struct CamTiles {
 static size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
 constexpr int kBinThreads = 1024;
-constexpr int kBinItems = 8;
-constexpr int kBinChunk = kBinThreads * kBinItems;  // entries per block, at most
+constexpr int kBinChunk = 8192;  // entries per block, at most
 constexpr int kLdsTiles = 16000;  // tiles counted in LDS at once (64 KB); larger cameras go in windows
 
 // Small per-call values after the count matrix: per-camera pair totals, the
@@ -66,12 +65,26 @@ struct SmallLayout {
 constexpr size_t kSmallBytes = 4096;
 static_assert(SmallLayout::bytes <= kSmallBytes, "small workspace");
 
-static int64_t blocks_per_cam(int64_t n) { return n > 0 ? (n + kBinChunk - 1) / kBinChunk : 0; }
+int64_t bin_blocks_min(int64_t n) { return n > 0 ? (n + kBinChunk - 1) / kBinChunk : 0; }
 
-// Count phase: the (block x tile) matrix (blocks_per_cam x tiles of every
-// camera, u32), the small values and the radix sort's list of tiles.
-size_t bin_count_bytes(int64_t n, int64_t T) {
-  return al((size_t)(blocks_per_cam(n) * T) * 4) + kSmallBytes + al((size_t)T * 4);
+// Blocks per camera.  A block of 16 waves takes its entries a unit (64) per
+// wave at a time, and a unit is a chain of dependent loads, FP64 row ranges and
+// LDS atomics, so what counts is how many waves the chip has at it: two blocks
+// a CU (512) while they keep a unit per wave (1024 entries), and never more
+// than 8192 entries in one.  The count matrix grows with the blocks, so
+// beyond 4M words it stays at blocks of 8192.  Count and scatter, us, against
+// blocks of 8192: 30k particles (627 tiles) 18 (51), 300k (1900) 33 (60), 1M
+// (8160) 81 (88), 3M (7500) 134 (162), two views of 1M (16320) 177 (173).
+int64_t bin_blocks(int64_t n, int n_cams, int64_t T) {
+  const int64_t lo = bin_blocks_min(n);
+  const int64_t hi = std::min((n + kBinThreads - 1) / kBinThreads, (int64_t)(512 + n_cams - 1) / n_cams);
+  return std::max(lo, std::min(hi, T > 0 ? (int64_t(4) << 20) / T : hi));
+}
+
+// Count phase: the (block x tile) matrix (bpc blocks per camera x tiles of
+// every camera, u32), the small values and the fallback sort's list of tiles.
+size_t bin_count_bytes(int64_t bpc, int64_t T) {
+  return al((size_t)(bpc * T) * 4) + kSmallBytes + al((size_t)T * 4);
 }
 // Pair phase: the pairs' keys and a ping-pong copy for lists longer than one
 // LDS chunk.
@@ -229,14 +242,24 @@ __device__ inline void lds_row_scan(uint32_t* h, int nrow, int txc, int stride) 
   }
 }
 
+// Clears the per-camera totals K2 adds into and the count of lists left to
+// the fallback sort.
+__device__ inline void bin_init(unsigned long long* __restrict__ sw) {
+  if (threadIdx.x < kMaxCams) sw[SmallLayout::cam_pairs / 8 + threadIdx.x] = 0ull;
+  if (threadIdx.x == 0) *(uint32_t*)((char*)sw + SmallLayout::nfall) = 0u;
+}
+__global__ void bin_init_kernel(unsigned long long* __restrict__ sw) { bin_init(sw); }  // (no entries)
+
 // K1: one row of the count matrix per block (camera c, the units of it that
 // the block owns).  Each visible entry adds, per
 // tile row, +1 at its first kept column and -1 after its last to an LDS
 // difference array of the camera's tiles (in windows of tile rows); prefix
 // sums along the rows then give the counts.
-__global__ void __launch_bounds__(kBinThreads) bin_count_kernel(BinArgs a, uint32_t* __restrict__ M) {
+__global__ void __launch_bounds__(kBinThreads) bin_count_kernel(BinArgs a, uint32_t* __restrict__ M,
+                                                                unsigned long long* __restrict__ sw) {
   extern __shared__ uint32_t h[];
   __shared__ int next;
+  if (blockIdx.x == 0) bin_init(sw);
   const int c = blockIdx.x / a.bpc, b = blockIdx.x % a.bpc;
   const int txc = a.ct.tx[c], Tc = a.ct.count[c], tyc = Tc / txc, S = txc + 1;
   const int64_t e0 = (int64_t)c * a.n;
@@ -274,10 +297,10 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(BinArgs a, uint3
 // a thread sums its segment, the segments' sums are scanned in LDS, and the
 // thread writes its segment's prefixes, so a long column (many blocks of
 // entries) is not walked by one thread alone.
-constexpr int kColThreads = 256;
+constexpr int kColThreads = 512;
 constexpr int kColTiles = 32;
 constexpr int kColSegs = kColThreads / kColTiles;
-constexpr int kColUnroll = 4;
+constexpr int kColUnroll = 8;
 __global__ void __launch_bounds__(kColThreads) bin_colscan_kernel(uint32_t* __restrict__ M, CamTiles ct,
                                                                   int n_cams, int bpc, int64_t T,
                                                                   uint2* __restrict__ ranges,
@@ -332,13 +355,6 @@ __global__ void __launch_bounds__(kColThreads) bin_colscan_kernel(uint32_t* __re
   }
   __syncthreads();
   if (threadIdx.x < n_cams && cs[threadIdx.x]) atomicAdd(&cam_pairs[threadIdx.x], cs[threadIdx.x]);
-}
-
-// Clears the per-camera totals K2 adds into and the count of lists left to
-// the radix sort.
-__global__ void bin_init_kernel(unsigned long long* __restrict__ sw) {
-  if (threadIdx.x < kMaxCams) sw[SmallLayout::cam_pairs / 8 + threadIdx.x] = 0ull;
-  if (threadIdx.x == 0) *(uint32_t*)((char*)sw + SmallLayout::nfall) = 0u;
 }
 
 // K4: each pair's key at its place: the tile's list start plus the block's
@@ -1384,7 +1400,7 @@ static CamTiles cam_tiles(const DevCam* dc, int n_cams) {
   return ct;
 }
 
-static BinArgs bin_args(const gut_projected* proj, int n, const DevCam* dc, int n_cams, bool cull,
+static BinArgs bin_args(const gut_projected* proj, int n, int64_t bpc, const DevCam* dc, int n_cams, bool cull,
                         size_t* lds_bytes) {
   BinArgs a;
   a.rect = (const short4*)proj->rect;
@@ -1393,7 +1409,7 @@ static BinArgs bin_args(const gut_projected* proj, int n, const DevCam* dc, int 
   a.mean2d = (const float2*)proj->mean2d;
   a.extent = (const float4*)proj->extent;
   a.n = n;
-  a.bpc = (int)blocks_per_cam(n);
+  a.bpc = (int)bpc;
   a.cull = cull ? 1 : 0;
   a.n_cams = n_cams;
   a.ct = cam_tiles(dc, n_cams);
@@ -1406,7 +1422,7 @@ static BinArgs bin_args(const gut_projected* proj, int n, const DevCam* dc, int 
   return a;
 }
 
-gut_status bin_count_launch(const gut_projected* proj, int n, const DevCam* dc, int n_cams, int64_t T,
+gut_status bin_count_launch(const gut_projected* proj, int n, int64_t bpc, const DevCam* dc, int n_cams, int64_t T,
                             bool cull, char* cws, uint32_t* tile_ranges, hipStream_t s) {
   if (!g_readback.p) {
     GUT_HIP(hipHostMalloc(&g_readback.p, 4 * (2 + kMaxCams), hipHostMallocMapped | hipHostMallocCoherent));
@@ -1416,18 +1432,18 @@ gut_status bin_count_launch(const gut_projected* proj, int n, const DevCam* dc, 
   std::memset(g_readback.p, 0xff, 8);  // a sentinel no total can equal
   g_readback.n_cams = n_cams;
   size_t lds = 0;
-  const BinArgs a = bin_args(proj, n, dc, n_cams, cull, &lds);
+  const BinArgs a = bin_args(proj, n, bpc, dc, n_cams, cull, &lds);
   uint32_t* M = (uint32_t*)cws;
   unsigned long long* sw = (unsigned long long*)(cws + al((size_t)((int64_t)a.bpc * T) * 4));
-  bin_init_kernel<<<1, 64, 0, s>>>(sw);
-  GUT_LAUNCH_CHECK();
   if (n > 0) {
-    bin_count_kernel<<<(unsigned)(a.bpc * n_cams), kBinThreads, lds, s>>>(a, M);
+    bin_count_kernel<<<(unsigned)(a.bpc * n_cams), kBinThreads, lds, s>>>(a, M, sw);
     GUT_LAUNCH_CHECK();
     bin_colscan_kernel<<<grid_for(T, kColTiles), kColThreads, 0, s>>>(
         M, a.ct, n_cams, a.bpc, T, (uint2*)tile_ranges, sw + SmallLayout::cam_pairs / 8);
     GUT_LAUNCH_CHECK();
   } else {  // no entries: every count is zero
+    bin_init_kernel<<<1, 64, 0, s>>>(sw);
+    GUT_LAUNCH_CHECK();
     gut_status st = fill_u32(tile_ranges, 2 * T, 0u, s);
     if (st != GUT_OK) return st;
   }
@@ -1456,11 +1472,12 @@ gut_status bin_count_wait(uint64_t* P, uint32_t* n_long) {
   return GUT_OK;
 }
 
-gut_status bin_sort_launch(const gut_projected* proj, int n, const DevCam* dc, int n_cams, int64_t T, bool cull,
+gut_status bin_sort_launch(const gut_projected* proj, int n, int64_t bpc, const DevCam* dc, int n_cams, int64_t T,
+                           bool cull,
                            char* cws, int64_t cap, char* pws, uint32_t* tile_ranges, uint32_t* sorted_ids,
                            hipStream_t s, int phases) {
   size_t lds = 0;
-  const BinArgs a = bin_args(proj, n, dc, n_cams, cull, &lds);
+  const BinArgs a = bin_args(proj, n, bpc, dc, n_cams, cull, &lds);
   const uint32_t* M = (const uint32_t*)cws;
   char* swb = cws + al((size_t)((int64_t)a.bpc * T) * 4);
   const unsigned long long* P_dev = (const unsigned long long*)(swb + SmallLayout::total);
@@ -1516,7 +1533,7 @@ extern "C" size_t gut_bin_workspace_bytes(int64_t n, const gut_camera* cams, int
     if (cams[c].width <= 0 || cams[c].height <= 0) return 0;
     T += (int64_t)((cams[c].width + kTile - 1) / kTile) * ((cams[c].height + kTile - 1) / kTile);
   }
-  return bin_count_bytes(n, T) + bin_pair_bytes(pair_capacity);
+  return bin_count_bytes(bin_blocks(n, n_cams, T), T) + bin_pair_bytes(pair_capacity);
 }
 
 extern "C" gut_status gut_bin(const gut_projected* proj, int64_t n, const gut_camera* cams,
@@ -1552,7 +1569,11 @@ extern "C" gut_status gut_bin(const gut_projected* proj, int64_t n, const gut_ca
   if ((st = prepare_cams(cams, n_cams, *p, dc, &T, nullptr)) != GUT_OK) return st;
   const int64_t E = n * n_cams;
   if (E >= (int64_t(1) << 31)) { set_error("n * n_cams must be below 2^31"); return GUT_E_INVALID; }
-  const size_t cb = bin_count_bytes(n, T), need = cb + bin_pair_bytes(pair_capacity);
+  // (a workspace of ceil(n / 8192) matrix rows will do, with fewer blocks)
+  const int64_t blo = bin_blocks_min(n), bhi = bin_blocks(n, n_cams, T);
+  const size_t pb = bin_pair_bytes(pair_capacity), need = bin_count_bytes(blo, T) + pb;
+  const int64_t bpc = ws_bytes >= bin_count_bytes(bhi, T) + pb ? bhi : blo;
+  const size_t cb = bin_count_bytes(bpc, T);
   if (!ws || ws_bytes < need || ((uintptr_t)ws & 255)) {
     set_error("workspace must be 256-byte aligned and hold %zu bytes (got %zu)", need, ws_bytes);
     return GUT_E_INVALID;
@@ -1560,17 +1581,17 @@ extern "C" gut_status gut_bin(const gut_projected* proj, int64_t n, const gut_ca
   hipStream_t s = (hipStream_t)stream;
   char* cws = (char*)ws;
   char* pws = cws + cb;
-  if ((st = bin_count_launch(proj, (int)n, dc, n_cams, T, cull, cws, tile_ranges, s)) != GUT_OK) return st;
+  if ((st = bin_count_launch(proj, (int)n, bpc, dc, n_cams, T, cull, cws, tile_ranges, s)) != GUT_OK) return st;
   // The scatter and the sorts up to 4095 entries are queued before the one
   // wait (they check the capacity on the device); the long lists' sort is
   // queued after it, only if there are long lists, and the fallback last.
-  if ((st = bin_sort_launch(proj, (int)n, dc, n_cams, T, cull, cws, pair_capacity, pws, tile_ranges, sorted_ids, s,
+  if ((st = bin_sort_launch(proj, (int)n, bpc, dc, n_cams, T, cull, cws, pair_capacity, pws, tile_ranges, sorted_ids, s,
                             kSortLists)) != GUT_OK)
     return st;
   uint64_t P = 0;
   uint32_t n_long = 0;
   if ((st = bin_count_wait(&P, &n_long)) != GUT_OK) return st;
-  if ((st = bin_sort_launch(proj, (int)n, dc, n_cams, T, cull, cws, pair_capacity, pws, tile_ranges, sorted_ids, s,
+  if ((st = bin_sort_launch(proj, (int)n, bpc, dc, n_cams, T, cull, cws, pair_capacity, pws, tile_ranges, sorted_ids, s,
                             (n_long ? kSortLong : 0) | kSortFallback)) != GUT_OK)
     return st;
   if (n_pairs) *n_pairs = (int64_t)P;

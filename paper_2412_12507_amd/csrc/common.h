@@ -107,15 +107,18 @@ gut_status render_batch_launch(const DevCam* d_cams, const DevCam* h_cams, int n
                                const float* rgb, float* const* d_outs, unsigned* d_counters,
                                int* d_lists, int* h_lists, int n_blocks, hipStream_t s);
 gut_status record_launch(const gut_scene* scene, float* record, hipStream_t s);
-// Binning in two phases.  The count phase (bin_count_bytes(n, T) of
-// workspace for n particles and T tiles over the cameras) queues the
+// Binning in two phases, with bpc blocks of entries per camera (bin_blocks, or
+// as few as bin_blocks_min).  The count phase (bin_count_bytes(bpc, T) of
+// workspace for T tiles over the cameras) queues the
 // per-tile counts, the list starts, the render order and the pair total P,
 // whose read-back bin_count_wait waits for; the sort phase (with
 // bin_pair_bytes(cap) more) queues the pairs' scatter and the per-list
 // sorts, which write nothing when P exceeds cap.
-size_t bin_count_bytes(int64_t n, int64_t T);
+int64_t bin_blocks_min(int64_t n);
+int64_t bin_blocks(int64_t n, int n_cams, int64_t T);
+size_t bin_count_bytes(int64_t bpc, int64_t T);
 size_t bin_pair_bytes(int64_t cap);
-gut_status bin_count_launch(const gut_projected* proj, int n, const DevCam* dc, int n_cams, int64_t T,
+gut_status bin_count_launch(const gut_projected* proj, int n, int64_t bpc, const DevCam* dc, int n_cams, int64_t T,
                             bool cull, char* cws, uint32_t* tile_ranges, hipStream_t s);
 // bin_count_wait also returns the number of lists of 4096 entries or more
 // (n_long, when not null); the sort phase's parts can be queued separately:
@@ -123,7 +126,8 @@ gut_status bin_count_launch(const gut_projected* proj, int n, const DevCam* dc, 
 // fallback sort of lists whose buckets came out too large, in that order.
 gut_status bin_count_wait(uint64_t* P, uint32_t* n_long = nullptr);
 constexpr int kSortLists = 1, kSortLong = 2, kSortFallback = 4, kSortAll = 7;
-gut_status bin_sort_launch(const gut_projected* proj, int n, const DevCam* dc, int n_cams, int64_t T, bool cull,
+gut_status bin_sort_launch(const gut_projected* proj, int n, int64_t bpc, const DevCam* dc, int n_cams, int64_t T,
+                           bool cull,
                            char* cws, int64_t cap, char* pws, uint32_t* tile_ranges, uint32_t* sorted_ids,
                            hipStream_t s, int phases = kSortAll);
 
