@@ -267,19 +267,23 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
 // one wave per SIMD leaves the SIMD idle.
 //
 // Sums.  A lane blends the nearest hit of its own buffer, so the hits one
-// step blends are mostly different particles across the wave (about seven
-// per step on a 1M-particle view), and summing them across the wave one
-// particle at a time cost more than the rest of the kernel.  Instead every
-// blended value goes to an FP32 LDS row of its hit's list position, with LDS
-// atomics, over a window of the two latest batches (positions [b - 256,
-// b + 256) while batch b runs).  A row is added to the FP64 per-particle sums
-// when its batch leaves the window, 13 atomics per (tile, particle).  The
+// step blends are a few different particles.  Their 13 values go to FP32 LDS
+// rows by list position, over a window of the six latest batches (768
+// positions); a row is added to the FP64 per-particle sums when its batch
+// leaves the window, 13 atomics per (tile, particle).  Lanes that blend the
+// same hit would meet on one LDS address, one after the other (with every
+// lane adding its own values, LDS was busy 58% of the kernel, at 43 cycles an
+// atomic), so each row of 16 lanes first sums the lanes that share its first
+// lane's hit (the reduce-scatter of the tile-order backward) and adds the
+// totals with one atomic; the lanes left over add their own.  (Going on to
+// the second or fourth hit that lanes share costs more instructions than it
+// saves: 1.95 and 2.08 ms a training step against 1.92.)  The
 // buffer holds list positions; a hit that has stayed longer than the window
-// (a buffer usually turns over within a batch) adds its values to the FP64
-// sums itself.
+// (a buffer usually turns over within a batch) goes to the FP64 sums at once.
 constexpr int kKBufB = 16;
 constexpr int kKThreadsB = 256;
-constexpr int kWin = 2 * kKThreadsB;  // list positions with an LDS row (of 13 values: an odd stride spreads them over the banks)
+constexpr int kKBatchB = 128;
+constexpr int kWin = 6 * kKBatchB;  // list positions with an LDS row (of 13 values: an odd stride spreads them over the banks)
 
 struct KBufGrad {
   double* acc;
@@ -287,36 +291,55 @@ struct KBufGrad {
   const float* rgb;
   const uint32_t* lids;  // the tile's sorted entry ids
   const uint32_t* pew;   // entry ids of the window's positions (LDS)
+  const float* cw;       // their colours (LDS rows of 3)
   float* accw;           // the window's rows (LDS)
   int n, cam_idx;
   float t_min;
-  uint32_t wlo;  // lowest list position in the window
+  uint32_t wlo, w0;  // lowest list position in the window; a multiple of kWin up to 2 kWin below its end
 };
 
-__device__ __forceinline__ uint32_t kbuf_entry(uint32_t pos, const KBufGrad& K) {
-  // the LDS copy is read in any case and an older hit's entry then replaces
-  // it; the empty register constraint keeps the compiler from folding the two
-  // reads into one flat read through a selected pointer
-  uint32_t e = K.pew[pos & (kWin - 1)];
-  asm volatile("" : "+v"(e));
-  if (pos < K.wlo) e = K.lids[pos];
-  return e;
+// The row of list position pos, pos mod kWin, for wlo <= pos < wlo + kWin.
+__device__ __forceinline__ uint32_t kbuf_row(uint32_t pos, const KBufGrad& K) {
+  const uint32_t r = pos - K.w0;
+  return min(r, r - (uint32_t)kWin);
 }
 
-// Adds one lane's blended values (hit at list position pos, entry e) to the
-// sums: its LDS row inside the window, else the FP64 sums.
-__device__ __forceinline__ void kbuf_add(uint32_t pos, uint32_t e, const float (&v)[kRow],
-                                         const KBufGrad& K) {
+// Value k of the 13 into the FP64 sums of entry e.
+__device__ __forceinline__ void kbuf_add64(uint32_t e, int k, double x, const KBufGrad& K) {
+  const long long i = (long long)(e - (uint32_t)K.cam_idx * (uint32_t)K.n);
+  if (k < kAcc) atomicAdd(&K.acc[i * kAcc + k], x);
+  else atomicAdd(&K.acc_rgb[3 * (long long)e + (k - kAcc)], x);
+}
+
+// Adds the blended values of the lanes with act set (hit at list position
+// pos) to the sums.
+__device__ __forceinline__ void kbuf_add(bool act, uint32_t pos, const float (&v)[kRow], const KBufGrad& K) {
+  const int lane = threadIdx.x & 63, k0 = lane & 15;
+  const unsigned long long A = __builtin_amdgcn_ballot_w64(act);
+  if (A == 0ull) return;
+  const uint32_t bits = (lane & 32 ? (uint32_t)(A >> 32) : (uint32_t)A) >> (lane & 16) & 0xffffu;
+  const int lead = bits ? (lane & 48) + __builtin_ctz(bits) : lane;
+  const uint32_t pl = (uint32_t)__shfl((int)pos, lead, 64);
+  const bool match = act && pos == pl;
+  float g[16];
+#pragma unroll
+  for (int k = 0; k < kRow; k++) g[k] = match ? v[k] : 0.0f;
+  g[13] = g[14] = g[15] = 0.0f;
+  const float tot = row_reduce16(g, lane);
+  if (k0 < kRow && tot != 0.0f) {
+    if (pl >= K.wlo) atomicAdd(&K.accw[kbuf_row(pl, K) * kRow + k0], tot);
+    else kbuf_add64(K.lids[pl], k0, (double)tot, K);
+  }
+  act = act && !match;
+  if (!act) return;
   if (pos >= K.wlo) {
-    float* row = K.accw + (pos & (kWin - 1)) * kRow;
+    float* row = K.accw + kbuf_row(pos, K) * kRow;
 #pragma unroll
     for (int k = 0; k < kRow; k++) atomicAdd(&row[k], v[k]);
   } else {
-    const long long i = (long long)(e - (uint32_t)K.cam_idx * (uint32_t)K.n);
+    const uint32_t e = K.lids[pos];
 #pragma unroll
-    for (int k = 0; k < kAcc; k++) atomicAdd(&K.acc[i * kAcc + k], (double)v[k]);
-#pragma unroll
-    for (int k = 0; k < 3; k++) atomicAdd(&K.acc_rgb[3 * (long long)e + k], (double)v[kAcc + k]);
+    for (int k = 0; k < kRow; k++) kbuf_add64(e, k, (double)v[k], K);
   }
 }
 
@@ -324,47 +347,59 @@ __device__ __forceinline__ void kbuf_add(uint32_t pos, uint32_t e, const float (
 __device__ __forceinline__ void kbuf_flush_row(int r, const KBufGrad& K) {
   float* row = K.accw + r * kRow;
   const uint32_t e = K.pew[r];
-  const long long i = (long long)(e - (uint32_t)K.cam_idx * (uint32_t)K.n);
 #pragma unroll
   for (int k = 0; k < kRow; k++) {
     const float x = row[k];
     if (x != 0.0f) {
-      if (k < kAcc) atomicAdd(&K.acc[i * kAcc + k], (double)x);
-      else atomicAdd(&K.acc_rgb[3 * (long long)e + (k - kAcc)], (double)x);
+      kbuf_add64(e, k, (double)x, K);
       row[k] = 0.0f;
     }
   }
 }
 
-// One blend of the replay (Eq. 5 with the t_min stop, as kbuf_blend) of the
-// hit at list position pos, and its 13 gradient values into the sums: G (6),
-// h (3), dL/dsigma, then dL/dc (3).  Nothing for a sentinel, a wall, a
-// stopped pixel or a hit that would cross t_min.
-__device__ __forceinline__ void kbuf_blend_bwd(float a, uint32_t pos, float px_, float py_, float pz_,
+// One blend of the replay (Eq. 5 with the t_min stop, as kbuf_blend) on the
+// lanes with on set, of the hit at list position pos, and its 13 gradient
+// values into the sums: G (6), h (3), dL/dsigma, then dL/dc (3).  Nothing for
+// a sentinel, a wall, a stopped pixel or a hit that would cross t_min.  The
+// whole wave calls it.
+__device__ __forceinline__ void kbuf_blend_bwd(bool on, float a, uint32_t pos, float px_, float py_, float pz_,
                                                float rho, float fg, const KBufGrad& K, const float (&gC)[3],
                                                const double (&gCd)[3], float gTT, float& T, double& Z,
                                                uint32_t& done) {
-  if (a <= 0.0f || done) return;
+  on = on && a > 0.0f && done == 0u;
+  if (!wave_any(on)) return;
   const float Tb = T;
   const float Tn = fmaf(-a, Tb, Tb);
-  if (Tn < K.t_min) { done = 1u; return; }
-  T = Tn;
-  const float wgt = a * Tb;
-  const uint32_t e = kbuf_entry(pos, K);
-  const double c0 = K.rgb[3 * (size_t)e], c1 = K.rgb[3 * (size_t)e + 1], c2 = K.rgb[3 * (size_t)e + 2];
-  const double D = fma(gCd[0], c0, fma(gCd[1], c1, gCd[2] * c2));
-  Z = fma(-(double)wgt, D, Z);
-  const float inv1m = __builtin_amdgcn_rcpf(1.0f - a);
-  float gA = fmaf(Tb, (float)D, -inv1m * ((float)Z + gTT));
-  if (rho < 0.0f) gA = 0.0f;  // alpha = alpha_max carries no gradient
-  const float c = -a * gA * fg;  // 2 dL/domega^2 (fg: a degree-n response's chain factor, else 1)
+  const bool stop = on && Tn < K.t_min;
+  done = stop ? 1u : done;
+  on = on && !stop;
   float v[kRow];
-  v[0] = c * px_ * px_; v[1] = c * px_ * py_; v[2] = c * px_ * pz_;
-  v[3] = c * py_ * py_; v[4] = c * py_ * pz_; v[5] = c * pz_ * pz_;
-  v[6] = c * px_; v[7] = c * py_; v[8] = c * pz_;
-  v[9] = gA * fabsf(rho);
-  v[10] = wgt * gC[0]; v[11] = wgt * gC[1]; v[12] = wgt * gC[2];
-  kbuf_add(pos, e, v, K);
+  if (on) {
+    T = Tn;
+    const float wgt = a * Tb;
+    // an LDS row is read in any case and an older hit's colour then replaces
+    // it; the empty register constraint keeps the compiler from folding the
+    // two reads into one flat read through a selected pointer
+    const float* cl = K.cw + 3 * (pos < K.wlo ? 0u : kbuf_row(pos, K));
+    float c0 = cl[0], c1 = cl[1], c2 = cl[2];
+    asm volatile("" : "+v"(c0), "+v"(c1), "+v"(c2));
+    if (pos < K.wlo) {
+      const float* c = K.rgb + 3 * (size_t)K.lids[pos];
+      c0 = c[0]; c1 = c[1]; c2 = c[2];
+    }
+    const double D = fma(gCd[0], (double)c0, fma(gCd[1], (double)c1, gCd[2] * (double)c2));
+    Z = fma(-(double)wgt, D, Z);
+    const float inv1m = __builtin_amdgcn_rcpf(1.0f - a);
+    float gA = fmaf(Tb, (float)D, -inv1m * ((float)Z + gTT));
+    if (rho < 0.0f) gA = 0.0f;  // alpha = alpha_max carries no gradient
+    const float c = -a * gA * fg;  // 2 dL/domega^2 (fg: a degree-n response's chain factor, else 1)
+    v[0] = c * px_ * px_; v[1] = c * px_ * py_; v[2] = c * px_ * pz_;
+    v[3] = c * py_ * py_; v[4] = c * py_ * pz_; v[5] = c * pz_ * pz_;
+    v[6] = c * px_; v[7] = c * py_; v[8] = c * pz_;
+    v[9] = gA * fabsf(rho);
+    v[10] = wgt * gC[0]; v[11] = wgt * gC[1]; v[12] = wgt * gC[2];
+  }
+  kbuf_add(on, pos, v, K);
 }
 
 template <bool RS, bool GEN, bool CLIP>
@@ -376,10 +411,11 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
     const float* __restrict__ out_T, const float* __restrict__ d_rgb, const float* __restrict__ d_T,
     double* __restrict__ acc, double* __restrict__ acc_rgb) {
   constexpr int S = Slots<RS, true>::N;
-  __shared__ float4 pd[batch_rows(kKThreadsB) * S];
-  __shared__ unsigned short pf[kKThreadsB];
+  __shared__ float4 pd[batch_rows(kKBatchB) * S];
+  __shared__ unsigned short pf[kKBatchB];
   __shared__ WaveLists lists[kKThreadsB / 64];
   __shared__ uint32_t pew[kWin];
+  __shared__ float cw[kWin * 3];
   __shared__ float accw[kWin * kRow];
   __shared__ TileFrameD F;
   __shared__ QuadBoxes wb;
@@ -392,7 +428,7 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   px += tx * kTile;
   py += ty * kTile;
   if (t == 0) tile_frame(cam, tx, ty, &F);
-  write_dummies<RS, true>(pd, kKThreadsB);
+  write_dummies<RS, true>(pd, kKBatchB);
   for (int i = t; i < kWin * kRow; i += kKThreadsB) accw[i] = 0.0f;
   __syncthreads();
   const bool inside = px < cam.W && py < cam.H;
@@ -423,7 +459,7 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   }
   const uint2 rg = ranges[cam.tile_base + tile];
   const uint32_t len = __builtin_amdgcn_readfirstlane(rg.y - rg.x);
-  KBufGrad K = {acc, acc_rgb, rgb, ids + rg.x, pew, accw, n, cam_idx, th.t_min, 0u};
+  KBufGrad K = {acc, acc_rgb, rgb, ids + rg.x, pew, cw, accw, n, cam_idx, th.t_min, 0u, 0u};
 
   float bd[kKBufB], ba[kKBufB], bx[kKBufB], by[kKBufB], bz[kKBufB], br[kKBufB], bf[kKBufB];
   uint32_t bi[kKBufB];  // list positions
@@ -435,34 +471,37 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   }
   float T = 1.0f;
   uint32_t done = active ? 0u : 1u;  // a 0/1 vector register, as in render_tile
-  for (uint32_t b = 0; b < len; b += kKThreadsB) {
+  int base = -kKBatchB;  // this batch's rows
+  for (uint32_t b = 0; b < len; b += kKBatchB) {
     if (__syncthreads_count(done == 0u) == 0) break;
-    const int half = (int)(b & (uint32_t)kKThreadsB);  // this batch's rows: b mod kWin
-    // the rows of batch b - kWin leave the window (their batch's eval ended
-    // before the barrier above)
-    if (b >= (uint32_t)kWin) kbuf_flush_row(half + t, K);
-    K.wlo = b >= (uint32_t)kKThreadsB ? b - kKThreadsB : 0u;
-    uint32_t fl = 0u;
-    if (b + t < len) {
-      const uint32_t e = ids[rg.x + b + t];
-      pew[half + t] = e;
-      fl = pair_setup<RS, true, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n),
-                                           F, cam, umax, vmax, dtmax, th, l2amin, wb, &pd[batch_row(t) * S]);
+    base = base + kKBatchB == kWin ? 0 : base + kKBatchB;
+    K.wlo = b + kKBatchB > (uint32_t)kWin ? b + kKBatchB - kWin : 0u;
+    K.w0 = b >= (uint32_t)kWin ? b - base - kWin : 0u;
+    if (t < kKBatchB) {
+      // the rows of batch b - kWin leave the window (their batch's eval ended
+      // before the barrier above)
+      if (b >= (uint32_t)kWin) kbuf_flush_row(base + t, K);
+      uint32_t fl = 0u;
+      if (b + t < len) {
+        const uint32_t e = ids[rg.x + b + t];
+        pew[base + t] = e;
+        float* c = cw + 3 * (base + t);
+        c[0] = rgb[3 * (size_t)e]; c[1] = rgb[3 * (size_t)e + 1]; c[2] = rgb[3 * (size_t)e + 2];
+        fl = pair_setup<RS, true, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n),
+                                             F, cam, umax, vmax, dtmax, th, l2amin, wb, &pd[t * S]);
+      }
+      pf[t] = (unsigned short)fl;
     }
-    pf[t] = (unsigned short)fl;
     __syncthreads();
-#pragma unroll 1
-    for (int c = 0; c < kKThreadsB && b + c < len; c += kChunk) {
-      if (!wave_any(done == 0u)) break;
-      const float4* pc = &pd[batch_row(c) * S];
-      const uint32_t lm = build_lists<RS, true>(pc, pf + c, wv, box, done == 0u, lists[wv]);
+    if (wave_any(done == 0u)) {
+      const uint32_t lm = build_lists<RS, true>(pd, pf, wv, box, done == 0u, lists[wv]);
       const int cnt = (int)(lm & ~kMixed);
       const bool mixed = (lm & kMixed) != 0u;
       const unsigned char* mine = lists[wv].row[lane >> 4];
       for (int k = 0; k < cnt; k++) {
         if (!wave_any(done == 0u)) break;
-        const uint32_t i = mine[k], q = c + i;  // (per row of lanes)
-        const float4* P = pc + i * S;
+        const uint32_t i = mine[k];  // (per row of lanes)
+        const float4* P = pd + i * S;
         PairRegs<RS> r;
         load_pair<RS>(P, r);
         Eval ev;
@@ -471,64 +510,63 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
         const bool live = eval_hit<RS>(r, ev) && done == 0u;
         if (!wave_any(live)) continue;
         eval_alpha<RS, GEN>(r, th, &ev);
-        if (live) {
-          float odg;
-          if (!RS) {
-            const float4 p5 = P[5];
-            odg = fmaf(v, p5.z, fmaf(u, p5.y, p5.x));
-          } else {
-            odg = fmaf(v, r.p4.w, fmaf(u, r.p3.w, r.p5.w));
-            odg = fmaf(dt, fmaf(v, r.p9.w, fmaf(u, r.p8.w, r.p7.w)), odg);
-          }
-          const float dist = -odg * dlen * ev.idd;
-          const uint32_t pos = b + q;  // the hit's list position
-          // the closest point p = d_g x (o_g x d_g) / |d_g|^2 and rho, as in render_bwd_kernel
-          float3 dg, cr;
-          pair_vectors<RS>(P, ev, u, v, &dg, &cr);
-          float3 pv = cross3f_fma(dg, cr);
-          pv = f3(pv.x * ev.idd, pv.y * ev.idd, pv.z * ev.idd);
-          const float rho0 = ev.araw * __builtin_amdgcn_exp2f(-r.lsig);
-          const float rho = ev.clamped ? -rho0 - 1e-30f : rho0;
-          // degree n: d alpha / d omega^2 relative to the Gaussian's (as in render_bwd_kernel)
-          const float fg = GEN ? __builtin_amdgcn_exp2f(fmaf(th.k_h - 1.0f, ev.lq, th.k_f)) : 1.0f;
-          if (dist <= bd[0]) {
-            kbuf_blend_bwd(ev.a, pos, pv.x, pv.y, pv.z, rho, fg, K, gC, gCd, gTT, T, Z, done);
-          } else {
-            kbuf_blend_bwd(ba[0], bi[0], bx[0], by[0], bz[0], br[0], bf[0], K, gC, gCd, gTT, T, Z, done);
+        float odg;
+        if (!RS) {
+          const float4 p5 = P[5];
+          odg = fmaf(v, p5.z, fmaf(u, p5.y, p5.x));
+        } else {
+          odg = fmaf(v, r.p4.w, fmaf(u, r.p3.w, r.p5.w));
+          odg = fmaf(dt, fmaf(v, r.p9.w, fmaf(u, r.p8.w, r.p7.w)), odg);
+        }
+        const float dist = -odg * dlen * ev.idd;
+        const uint32_t pos = b + i;  // the hit's list position
+        // the closest point p = d_g x (o_g x d_g) / |d_g|^2 and rho, as in render_bwd_kernel
+        float3 dg, cr;
+        pair_vectors<RS>(P, ev, u, v, &dg, &cr);
+        float3 pv = cross3f_fma(dg, cr);
+        pv = f3(pv.x * ev.idd, pv.y * ev.idd, pv.z * ev.idd);
+        const float rho0 = ev.araw * __builtin_amdgcn_exp2f(-r.lsig);
+        const float rho = ev.clamped ? -rho0 - 1e-30f : rho0;
+        // degree n: d alpha / d omega^2 relative to the Gaussian's (as in render_bwd_kernel)
+        const float fg = GEN ? __builtin_amdgcn_exp2f(fmaf(th.k_h - 1.0f, ev.lq, th.k_f)) : 1.0f;
+        // a lane blends either the hit, if it lies at or before the buffer's
+        // nearest, or that one, which the hit then displaces
+        const bool ins = live && !(dist <= bd[0]);
+        kbuf_blend_bwd(live, ins ? ba[0] : ev.a, ins ? bi[0] : pos, ins ? bx[0] : pv.x, ins ? by[0] : pv.y,
+                       ins ? bz[0] : pv.z, ins ? br[0] : rho, ins ? bf[0] : fg, K, gC, gCd, gTT, T, Z, done);
+        if (ins) {
 #pragma unroll
-            for (int j = 0; j < kKBufB - 1; j++) {
-              const bool nx = bd[j + 1] < dist, here = j == 0 || bd[j] < dist;
-              // sorted buffer and dist > bd[0]: the middle one of bd[j], dist, bd[j + 1]
-              bd[j] = __builtin_amdgcn_fmed3f(bd[j], dist, bd[j + 1]);
-              ba[j] = nx ? ba[j + 1] : (here ? ev.a : ba[j]);
-              bi[j] = nx ? bi[j + 1] : (here ? pos : bi[j]);
-              bx[j] = nx ? bx[j + 1] : (here ? pv.x : bx[j]);
-              by[j] = nx ? by[j + 1] : (here ? pv.y : by[j]);
-              bz[j] = nx ? bz[j + 1] : (here ? pv.z : bz[j]);
-              br[j] = nx ? br[j + 1] : (here ? rho : br[j]);
-              if (GEN) bf[j] = nx ? bf[j + 1] : (here ? fg : bf[j]);
-            }
-            const int L = kKBufB - 1;
-            const bool last = bd[L] < dist;
-            ba[L] = last ? ev.a : ba[L];
-            bi[L] = last ? pos : bi[L];
-            bx[L] = last ? pv.x : bx[L];
-            by[L] = last ? pv.y : by[L];
-            bz[L] = last ? pv.z : bz[L];
-            br[L] = last ? rho : br[L];
-            if (GEN) bf[L] = last ? fg : bf[L];
-            bd[L] = last ? dist : bd[L];
+          for (int j = 0; j < kKBufB - 1; j++) {
+            const bool nx = bd[j + 1] < dist, here = j == 0 || bd[j] < dist;
+            // sorted buffer and dist > bd[0]: the middle one of bd[j], dist, bd[j + 1]
+            bd[j] = __builtin_amdgcn_fmed3f(bd[j], dist, bd[j + 1]);
+            ba[j] = nx ? ba[j + 1] : (here ? ev.a : ba[j]);
+            bi[j] = nx ? bi[j + 1] : (here ? pos : bi[j]);
+            bx[j] = nx ? bx[j + 1] : (here ? pv.x : bx[j]);
+            by[j] = nx ? by[j + 1] : (here ? pv.y : by[j]);
+            bz[j] = nx ? bz[j + 1] : (here ? pv.z : bz[j]);
+            br[j] = nx ? br[j + 1] : (here ? rho : br[j]);
+            if (GEN) bf[j] = nx ? bf[j + 1] : (here ? fg : bf[j]);
           }
+          const int L = kKBufB - 1;
+          const bool last = bd[L] < dist;
+          ba[L] = last ? ev.a : ba[L];
+          bi[L] = last ? pos : bi[L];
+          bx[L] = last ? pv.x : bx[L];
+          by[L] = last ? pv.y : by[L];
+          bz[L] = last ? pv.z : bz[L];
+          br[L] = last ? rho : br[L];
+          if (GEN) bf[L] = last ? fg : bf[L];
+          bd[L] = last ? dist : bd[L];
         }
       }
     }
   }
 #pragma unroll
   for (int j = 0; j < kKBufB; j++)
-    kbuf_blend_bwd(ba[j], bi[j], bx[j], by[j], bz[j], br[j], bf[j], K, gC, gCd, gTT, T, Z, done);
+    kbuf_blend_bwd(true, ba[j], bi[j], bx[j], by[j], bz[j], br[j], bf[j], K, gC, gCd, gTT, T, Z, done);
   __syncthreads();
-  kbuf_flush_row(t, K);
-  kbuf_flush_row(t + kKThreadsB, K);
+  for (int r = t; r < kWin; r += kKThreadsB) kbuf_flush_row(r, K);
 }
 
 // K7a: camera-independent part of the per-particle chain (FP64: the
