@@ -137,42 +137,64 @@ def check(status: int, where: str):
 
 
 def ref(x):
-    return C.cast(C.pointer(x), C.c_void_p)
+    return C.byref(x)
+
+
+_MODELS = {"pinhole": GUT_PINHOLE, "fisheye": GUT_FISHEYE_OPENCV}
+_SHUTTERS = {"global": GUT_GLOBAL_SHUTTER, "rolling": GUT_ROLLING_TOP_TO_BOTTOM}
+
+
+def _values(x):
+    # (one conversion of an array; an element at a time costs ten times as much)
+    return x.tolist() if getattr(x, "ndim", 0) in (1, 2) else x
+
+
+def _rotation(R):
+    """The first nine values of a 3x3 rotation (rows, or flat), as floats."""
+    R = _values(R)
+    flat = []
+    for row in R:
+        if hasattr(row, "__len__"):
+            flat.extend(row)
+        else:
+            flat.append(row)
+    if len(flat) < 9:
+        raise IndexError("a rotation has nine values")
+    return [float(v) for v in flat[:9]]
+
+
+def fill_camera(c: Camera, cam: dict) -> Camera:
+    c.model, c.shutter = _MODELS[cam["model"]], _SHUTTERS[cam["shutter"]]
+    c.width, c.height = int(cam["width"]), int(cam["height"])
+    c.fx, c.fy, c.cx, c.cy = float(cam["fx"]), float(cam["fy"]), float(cam["cx"]), float(cam["cy"])
+    k, t0, t1 = _values(cam["k"]), _values(cam["t0"]), _values(cam["t1"])
+    c.k[:] = [float(k[0]), float(k[1]), float(k[2]), float(k[3])]
+    c.R0[:], c.R1[:] = _rotation(cam["R0"]), _rotation(cam["R1"])
+    c.t0[:] = [float(t0[0]), float(t0[1]), float(t0[2])]
+    c.t1[:] = [float(t1[0]), float(t1[1]), float(t1[2])]
+    return c
 
 
 def camera_struct(cam: dict) -> Camera:
-    c = Camera()
-    c.model = {"pinhole": GUT_PINHOLE, "fisheye": GUT_FISHEYE_OPENCV}[cam["model"]]
-    c.shutter = {"global": GUT_GLOBAL_SHUTTER, "rolling": GUT_ROLLING_TOP_TO_BOTTOM}[cam["shutter"]]
-    c.width, c.height = int(cam["width"]), int(cam["height"])
-    c.fx, c.fy, c.cx, c.cy = (float(cam[k]) for k in ("fx", "fy", "cx", "cy"))
-    for i in range(4):
-        c.k[i] = float(cam["k"][i])
-    R0 = [float(v) for row in cam["R0"] for v in (row if hasattr(row, "__len__") else [row])]
-    R1 = [float(v) for row in cam["R1"] for v in (row if hasattr(row, "__len__") else [row])]
-    for i in range(9):
-        c.R0[i], c.R1[i] = R0[i], R1[i]
-    for i in range(3):
-        c.t0[i], c.t1[i] = float(cam["t0"][i]), float(cam["t1"][i])
-    return c
+    return fill_camera(Camera(), cam)
 
 
 def camera_array(cams):
     arr = (Camera * len(cams))()
     for i, cam in enumerate(cams):
-        arr[i] = camera_struct(cam)
+        fill_camera(arr[i], cam)
     return arr
+
+
+_INT_PARAMS = frozenset(("tile", "rs_iters", "kernel_degree", "kbuffer", "tile_cull"))
 
 
 def params_struct(params: dict | None = None) -> Params:
     p = Params()
-    load().gut_default_params(ref(p))
+    load().gut_default_params(C.byref(p))
     for k, v in (params or {}).items():
         if k == "bg":
-            for i in range(3):
-                p.bg[i] = float(v[i])
-        elif k in ("tile", "rs_iters", "kernel_degree", "kbuffer", "tile_cull"):
-            setattr(p, k, int(v))
+            p.bg[:] = [float(v[0]), float(v[1]), float(v[2])]
         else:
-            setattr(p, k, float(v))
+            setattr(p, k, int(v) if k in _INT_PARAMS else float(v))
     return p

@@ -4,6 +4,7 @@
 #include <cstring>
 
 #include "common.h"
+#include "fisheye_limit.h"
 
 namespace gut {
 
@@ -33,27 +34,6 @@ static bool finite_all(const double* v, int n) {
   for (int i = 0; i < n; i++)
     if (!std::isfinite(v[i])) return false;
   return true;
-}
-
-// Fisheye validity limit: first angle in (0, pi/2] where d theta_d/d theta
-// reaches zero (scan, then bisection), else pi/2.
-static double host_theta_lim(const double* k) {
-  const int steps = 4096;
-  const double half_pi = 1.5707963267948966;
-  double prev = 0.0;
-  for (int i = 1; i <= steps; i++) {
-    double th = half_pi * i / steps;
-    if (thetad_deriv(k, th) <= 0.0) {
-      double lo = prev, hi = th;
-      for (int it = 0; it < 200; it++) {
-        double mid = 0.5 * (lo + hi);
-        if (thetad_deriv(k, mid) > 0.0) lo = mid; else hi = mid;
-      }
-      return lo;
-    }
-    prev = th;
-  }
-  return half_pi;
 }
 
 // Axis and angle of a rotation matrix (row-major), robust near 0 and pi.
@@ -137,7 +117,7 @@ gut_status make_devcam(const gut_camera& c, const gut_params& p, int tile_base,
   o->fx = c.fx; o->fy = c.fy; o->cx = c.cx; o->cy = c.cy;
   for (int i = 0; i < 4; i++) o->k[i] = c.k[i];
   if (c.model == GUT_FISHEYE_OPENCV) {
-    o->theta_lim = host_theta_lim(c.k);
+    o->theta_lim = fisheye_limit(c.k, thetad_deriv);
     if (!(o->theta_lim > 1e-6)) {
       set_error("fisheye distortion leaves no valid field of view");
       return GUT_E_INVALID;

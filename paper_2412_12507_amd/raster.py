@@ -21,11 +21,18 @@ from . import _lib as L
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _args(cams, params):
+    """The C structs of a call's cameras and parameters.  forward makes them
+    once for its three steps: made four times over they took 160 us, half of
+    the time a small image takes."""
+    return L.camera_array(cams), L.params_struct(params)
 
 
 @dataclass
@@ -105,9 +112,11 @@ class Image:
 
 
 def num_tiles(cams, params=None) -> int:
-    arr = L.camera_array(cams)
-    p = L.params_struct(params)
-    t = L.load().gut_num_tiles(arr, len(cams), L.ref(p))
+    return _num_tiles(*_args(cams, params))
+
+
+def _num_tiles(arr, p) -> int:
+    t = L.load().gut_num_tiles(arr, len(arr), L.ref(p))
     if t < 0:
         raise ValueError("bad cameras")
     return int(t)
@@ -128,11 +137,13 @@ def alloc_projection(n, n_cams, device="cuda", debug=False) -> Projection:
 
 def project(scene: GaussianScene, cams, params=None, out: Projection | None = None,
             debug=False) -> Projection:
-    n, nc = scene.n, len(cams)
+    return _project(scene, *_args(cams, params), out, debug)
+
+
+def _project(scene, arr, p, out=None, debug=False) -> Projection:
+    n, nc = scene.n, len(arr)
     if out is None:
         out = alloc_projection(n, nc, scene.means.device, debug)
-    arr = L.camera_array(cams)
-    p = L.params_struct(params)
     ss, ps = scene.struct(), out.struct()
     L.check(L.load().gut_project(L.ref(ss), arr, nc, L.ref(p), L.ref(ps), _stream()),
             "gut_project")
@@ -142,12 +153,14 @@ def project(scene: GaussianScene, cams, params=None, out: Projection | None = No
 def bin_tiles(proj: Projection, cams, params=None, bins: Bins | None = None,
               capacity: int | None = None) -> Bins:
     """gut_bin; grows the pair buffer and retries if it is too small."""
+    return _bin_tiles(proj, *_args(cams, params), bins, capacity)
+
+
+def _bin_tiles(proj, arr, p, bins=None, capacity=None) -> Bins:
     lib = L.load()
-    n, nc = proj.n, len(cams)
+    n, nc = proj.n, len(arr)
     dev = proj.depth.device
-    T = num_tiles(cams, params)
-    arr = L.camera_array(cams)
-    p = L.params_struct(params)
+    T = _num_tiles(arr, p)
     if bins is None or bins.ranges.shape[0] != T:
         # [T,2] ranges followed by the [T] render order, in one buffer
         rbuf = torch.empty(3 * T, dtype=torch.int32, device=dev)
@@ -198,10 +211,12 @@ def _clip_arg(clip, cams):
 
 def render(proj: Projection, bins: Bins, cams, params=None, out: Image | None = None,
            with_eval=False, clip: torch.Tensor | None = None) -> Image:
+    return _render(proj, bins, cams, *_args(cams, params), out, with_eval, clip)
+
+
+def _render(proj, bins, cams, arr, p, out=None, with_eval=False, clip=None) -> Image:
     if out is None:
         out = alloc_image(cams, proj.depth.device, with_eval)
-    arr = L.camera_array(cams)
-    p = L.params_struct(params)
     ps = proj.struct()
     clip = _clip_arg(clip, cams)
     L.check(L.load().gut_render(L.ref(ps), proj.n, _ptr(bins.ranges), _ptr(bins.ids), arr,
@@ -224,8 +239,7 @@ def render_backward(scene: GaussianScene, proj: Projection, bins: Bins, cams, im
     need = lib.gut_render_bwd_workspace_bytes(n, nc)
     if workspace is None or workspace.numel() < need:
         workspace = torch.empty(max(int(need), 256), dtype=torch.uint8, device=dev)
-    arr = L.camera_array(cams)
-    p = L.params_struct(params)
+    arr, p = _args(cams, params)
     ss, ps = scene.struct(), proj.struct()
     d_rgb = d_rgb.contiguous()
     d_T = None if d_T is None else d_T.contiguous()
@@ -241,9 +255,10 @@ def render_backward(scene: GaussianScene, proj: Projection, bins: Bins, cams, im
 
 def forward(scene: GaussianScene, cams, params=None, with_eval=False, clip=None):
     """project -> bin -> render; returns (proj, bins, image)."""
-    proj = project(scene, cams, params)
-    bins = bin_tiles(proj, cams, params)
-    img = render(proj, bins, cams, params, with_eval=with_eval, clip=clip)
+    arr, p = _args(cams, params)
+    proj = _project(scene, arr, p)
+    bins = _bin_tiles(proj, arr, p)
+    img = _render(proj, bins, cams, arr, p, with_eval=with_eval, clip=clip)
     return proj, bins, img
 
 
