@@ -242,10 +242,10 @@ __device__ inline void lds_row_scan(uint32_t* h, int nrow, int txc, int stride) 
   }
 }
 
-// Clears the per-camera totals K2 adds into and the count of lists left to
-// the fallback sort.
-__device__ inline void bin_init(unsigned long long* __restrict__ sw) {
-  if (threadIdx.x < kMaxCams) sw[SmallLayout::cam_pairs / 8 + threadIdx.x] = 0ull;
+// Clears the per-camera totals K2 adds into (clear_cams) and the count of
+// lists left to the fallback sort.
+__device__ inline void bin_init(unsigned long long* __restrict__ sw, bool clear_cams = true) {
+  if (clear_cams && threadIdx.x < kMaxCams) sw[SmallLayout::cam_pairs / 8 + threadIdx.x] = 0ull;
   if (threadIdx.x == 0) *(uint32_t*)((char*)sw + SmallLayout::nfall) = 0u;
 }
 __global__ void bin_init_kernel(unsigned long long* __restrict__ sw) { bin_init(sw); }  // (no entries)
@@ -254,12 +254,20 @@ __global__ void bin_init_kernel(unsigned long long* __restrict__ sw) { bin_init(
 // the block owns).  Each visible entry adds, per
 // tile row, +1 at its first kept column and -1 after its last to an LDS
 // difference array of the camera's tiles (in windows of tile rows); prefix
-// sums along the rows then give the counts.
+// sums along the rows then give the counts.  With one block per camera there
+// is nothing to scan over the blocks: the block writes what K2 would (its
+// tiles' counts, its offsets, all zero, and its camera's total), and K2, 3.3 us
+// and a launch in a call of 1000 entries, is not launched.
 __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(BinArgs a, uint32_t* __restrict__ M,
-                                                                unsigned long long* __restrict__ sw) {
+                                                                unsigned long long* __restrict__ sw,
+                                                                uint2* __restrict__ ranges) {
   extern __shared__ uint32_t h[];
   __shared__ int next;
-  if (blockIdx.x == 0) bin_init(sw);
+  __shared__ unsigned long long sum;
+  const bool one = a.bpc == 1;
+  if (blockIdx.x == 0) bin_init(sw, !one);
+  if (threadIdx.x == 0) sum = 0ull;
+  unsigned long long mine = 0ull;
   const int c = blockIdx.x / a.bpc, b = blockIdx.x % a.bpc;
   const int txc = a.ct.tx[c], Tc = a.ct.count[c], tyc = Tc / txc, S = txc + 1;
   const int64_t e0 = (int64_t)c * a.n;
@@ -284,8 +292,20 @@ __global__ void __launch_bounds__(kBinThreads) bin_count_kernel(BinArgs a, uint3
     lds_row_scan(h, nrow, txc, S);
     __syncthreads();
     for (int r = threadIdx.x >> 6; r < nrow; r += kBinThreads / 64)
-      for (int x = lane; x < txc; x += 64) row[(w0 + r) * txc + x] = h[r * S + x];
+      for (int x = lane; x < txc; x += 64) {
+        const uint32_t v = h[r * S + x];
+        row[(w0 + r) * txc + x] = one ? 0u : v;
+        if (one) {
+          ranges[a.ct.base[c] + (w0 + r) * txc + x].y = v;
+          mine += v;
+        }
+      }
     __syncthreads();
+  }
+  if (one) {
+    if (mine) atomicAdd(&sum, mine);
+    __syncthreads();
+    if (threadIdx.x == 0) sw[SmallLayout::cam_pairs / 8 + c] = sum;
   }
 }
 
@@ -409,6 +429,7 @@ constexpr int kScanThreads = 1024;
 constexpr int kScanItems = 16;
 constexpr int kMidBucket = 21;  // __clz of lengths >= 1024 is at most 21
 constexpr int kBigBucket = 19;  // __clz of lengths >= 4096 is at most 19
+constexpr int kLongBucket = 23;  // __clz of lengths >= 256 is at most 23
 
 __device__ inline uint32_t block_scan_1024(uint32_t v, uint32_t* wsum, uint32_t* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -436,8 +457,8 @@ __device__ inline uint32_t block_scan_1024(uint32_t v, uint32_t* wsum, uint32_t*
 // bit length of the list length, longest first; within a bucket the order
 // may vary from call to call), the number of lists of at least 4096 and of
 // at least 1024 entries (the front of that order), and from the last
-// camera's block the total P for the device and the host (with each
-// camera's count of long lists).
+// camera's block the total P for the device and the host (with the sorts
+// that each camera's lists need).
 __global__ void __launch_bounds__(kScanThreads) bin_scan_kernel(uint2* __restrict__ ranges,
                                                                 uint32_t* __restrict__ order, CamTiles ct,
                                                                 int n_cams, unsigned long long* __restrict__ sw,
@@ -481,18 +502,21 @@ __global__ void __launch_bounds__(kScanThreads) bin_scan_kernel(uint2* __restric
     __syncthreads();  // wsum is reused by the next piece
   }
   if (t == 0) {
-    unsigned acc = 0, big = 0, mid = 0;
+    unsigned acc = 0, big = 0, mid = 0, lng = 0;
     for (int b = 0; b < 33; b++) {
       bcur[b] = acc;
       acc += bcnt[b];
       if (b <= kBigBucket) big += bcnt[b];
       if (b <= kMidBucket) mid += bcnt[b];
+      if (b <= kLongBucket) lng += bcnt[b];
     }
     uint32_t* nb = (uint32_t*)((char*)sw + SmallLayout::nbig);
     uint32_t* nm = (uint32_t*)((char*)sw + SmallLayout::nmid);
     nb[c] = big;
     nm[c] = mid;
-    ((volatile uint32_t*)host)[2 + c] = big;  // for the host: whether the long-list sort has work
+    // for the host: which of the sorts have work
+    ((volatile uint32_t*)host)[2 + c] =
+        (big ? kSortLong : 0u) | (mid > big ? kSortMid : 0u) | (lng ? kSortFallback : 0u);
   }
   __syncthreads();
   for (int j = t; j < Tc; j += kScanThreads) {
@@ -1079,36 +1103,41 @@ __device__ __forceinline__ bool block_bucket_sort(const unsigned long long* __re
 // length (the LDS a wave holds, and so how many waves fit a CU, follows the
 // longest list of the launch): ROWS_MAX 4 takes lists below 256 entries,
 // ROWS_MAX 16 the others (with 16-bit counters: 12 KB of LDS a wave instead
-// of 16, so 13 waves fit a CU instead of 10).  A list whose largest bucket
-// is too large goes on the list for tile_sort_fallback_kernel.
-template <int ROWS_MAX>
+// of 16, so 13 waves fit a CU instead of 10).  Up to kOneSortTiles tiles, all
+// of them fit the chip at 12 KB, and one launch takes both (LO 1).  A list of
+// 256 entries or more whose largest bucket is too large goes on the list for
+// tile_sort_fallback_kernel; a shorter one is ranked in its buckets whatever
+// they hold (at most 255 steps), so that a call without longer lists needs no
+// other sort.
+constexpr int kOneSortTiles = 3328;  // 13 waves on each of 256 CUs
+template <int ROWS_MAX, uint32_t LO>
 __global__ void __launch_bounds__(64) tile_sort_small_kernel(const uint2* __restrict__ ranges,
                                                             const unsigned long long* __restrict__ keys,
                                                             uint32_t* __restrict__ ids,
                                                             const unsigned long long* __restrict__ P_dev,
                                                             unsigned long long cap, uint32_t* __restrict__ nfall,
                                                             uint32_t* __restrict__ fall) {
-  constexpr uint32_t lo = ROWS_MAX == 4 ? 1u : 256u, hi = 64u * ROWS_MAX;
+  constexpr uint32_t hi = 64u * ROWS_MAX, kAny = 256u;
   __shared__ BlockSortSmem<64, ROWS_MAX, ROWS_MAX == 4 ? 9 : 11, ROWS_MAX == 16> S;
   const unsigned long long P = *P_dev;
   const uint2 r = ranges[blockIdx.x];  // written by K3 whatever P is
   if (P > cap) return;                 // the keys were not written
   const uint32_t L = r.y - r.x;
-  if (L < lo || L >= hi || (unsigned long long)r.y > cap) return;
+  if (L < LO || L >= hi || (unsigned long long)r.y > cap) return;
   bool done;
   if (L == 1) {
     if (threadIdx.x == 0) ids[r.x] = (uint32_t)keys[r.x];
     done = true;
   } else if (L <= 64u) {
-    done = block_bucket_sort<64, 1, 7, false>(keys + r.x, L, ids + r.x, *(BlockSortSmem<64, 1, 7>*)&S);
+    done = block_bucket_sort<64, 1, 7, false>(keys + r.x, L, ids + r.x, *(BlockSortSmem<64, 1, 7>*)&S, kAny);
   } else if (L <= 128u) {
-    done = block_bucket_sort<64, 2, 8, false>(keys + r.x, L, ids + r.x, *(BlockSortSmem<64, 2, 8>*)&S);
-  } else if (ROWS_MAX == 4 || L <= 256u) {
-    done = block_bucket_sort<64, 4, 9, false>(keys + r.x, L, ids + r.x, *(BlockSortSmem<64, 4, 9>*)&S);
+    done = block_bucket_sort<64, 2, 8, false>(keys + r.x, L, ids + r.x, *(BlockSortSmem<64, 2, 8>*)&S, kAny);
+  } else if (ROWS_MAX == 4 || L < 256u) {
+    done = block_bucket_sort<64, 4, 9, false>(keys + r.x, L, ids + r.x, *(BlockSortSmem<64, 4, 9>*)&S, kAny);
   } else if (L <= 512u) {
     done = block_bucket_sort<64, 8, 10, false>(keys + r.x, L, ids + r.x, *(BlockSortSmem<64, 8, 10>*)&S);
   } else {
-    done = block_bucket_sort<64, ROWS_MAX, ROWS_MAX == 4 ? 9 : 11, ROWS_MAX == 16>(keys + r.x, L, ids + r.x, S);
+    done = block_bucket_sort<64, 16, 11, true>(keys + r.x, L, ids + r.x, *(BlockSortSmem<64, 16, 11, true>*)&S);
   }
   if (!done && threadIdx.x == 0) fall[atomicAdd(nfall, 1u)] = blockIdx.x;
 }
@@ -1365,7 +1394,7 @@ __global__ void __launch_bounds__(kBigThreads) tile_sort_fallback_kernel(const u
 // Pinned host slot for the pair-count read-back and the event that marks
 // it, one per host thread.
 struct ReadbackSlot {
-  void* p = nullptr;   // host address: P (2 words), then each camera's long lists
+  void* p = nullptr;   // host address: P (2 words), then the sorts each camera's lists need
   void* dp = nullptr;  // the same memory as the device sees it
   hipEvent_t ev = nullptr;
   int n_cams = 0;      // cameras of the last count phase
@@ -1436,11 +1465,13 @@ gut_status bin_count_launch(const gut_projected* proj, int n, int64_t bpc, const
   uint32_t* M = (uint32_t*)cws;
   unsigned long long* sw = (unsigned long long*)(cws + al((size_t)((int64_t)a.bpc * T) * 4));
   if (n > 0) {
-    bin_count_kernel<<<(unsigned)(a.bpc * n_cams), kBinThreads, lds, s>>>(a, M, sw);
+    bin_count_kernel<<<(unsigned)(a.bpc * n_cams), kBinThreads, lds, s>>>(a, M, sw, (uint2*)tile_ranges);
     GUT_LAUNCH_CHECK();
-    bin_colscan_kernel<<<grid_for(T, kColTiles), kColThreads, 0, s>>>(
-        M, a.ct, n_cams, a.bpc, T, (uint2*)tile_ranges, sw + SmallLayout::cam_pairs / 8);
-    GUT_LAUNCH_CHECK();
+    if (a.bpc > 1) {
+      bin_colscan_kernel<<<grid_for(T, kColTiles), kColThreads, 0, s>>>(
+          M, a.ct, n_cams, a.bpc, T, (uint2*)tile_ranges, sw + SmallLayout::cam_pairs / 8);
+      GUT_LAUNCH_CHECK();
+    }
   } else {  // no entries: every count is zero
     bin_init_kernel<<<1, 64, 0, s>>>(sw);
     GUT_LAUNCH_CHECK();
@@ -1454,7 +1485,7 @@ gut_status bin_count_launch(const gut_projected* proj, int n, int64_t bpc, const
   return GUT_OK;
 }
 
-gut_status bin_count_wait(uint64_t* P, uint32_t* n_long) {
+gut_status bin_count_wait(uint64_t* P, int* sorts) {
   GUT_HIP(hipEventSynchronize(g_readback.ev));
   uint32_t w[2 + kMaxCams];
   std::memcpy(w, g_readback.p, 4 * (2 + g_readback.n_cams));
@@ -1464,10 +1495,9 @@ gut_status bin_count_wait(uint64_t* P, uint32_t* n_long) {
     return GUT_E_HIP;
   }
   *P = v;
-  if (n_long) {
-    uint32_t m = 0;
-    for (int c = 0; c < g_readback.n_cams; c++) m += w[2 + c];
-    *n_long = m;
+  if (sorts) {
+    *sorts = 0;
+    for (int c = 0; c < g_readback.n_cams; c++) *sorts |= (int)w[2 + c];
   }
   return GUT_OK;
 }
@@ -1494,12 +1524,20 @@ gut_status bin_sort_launch(const gut_projected* proj, int n, int64_t bpc, const 
                                                                                P_dev, ucap, keys);
       GUT_LAUNCH_CHECK();
     }
-    tile_sort_small_kernel<4><<<(unsigned)T, 64, 0, s>>>((const uint2*)tile_ranges, keys, sorted_ids, P_dev, ucap,
-                                                         nfall, fall);
+    // (one launch up to kOneSortTiles tiles: in a call of 1000 particles, 64
+    // tiles, an empty second one cost 4 us with its gap; above, the short lists'
+    // waves would hold the long ones' LDS)
+    const uint2* rg = (const uint2*)tile_ranges;
+    if (T <= kOneSortTiles) {
+      tile_sort_small_kernel<16, 1><<<(unsigned)T, 64, 0, s>>>(rg, keys, sorted_ids, P_dev, ucap, nfall, fall);
+    } else {
+      tile_sort_small_kernel<4, 1><<<(unsigned)T, 64, 0, s>>>(rg, keys, sorted_ids, P_dev, ucap, nfall, fall);
+      GUT_LAUNCH_CHECK();
+      tile_sort_small_kernel<16, 256><<<(unsigned)T, 64, 0, s>>>(rg, keys, sorted_ids, P_dev, ucap, nfall, fall);
+    }
     GUT_LAUNCH_CHECK();
-    tile_sort_small_kernel<16><<<(unsigned)T, 64, 0, s>>>((const uint2*)tile_ranges, keys, sorted_ids, P_dev, ucap,
-                                                          nfall, fall);
-    GUT_LAUNCH_CHECK();
+  }
+  if (phases & kSortMid) {
     tile_sort_mid_kernel<<<kMidBlocks, kMidThreads, 0, s>>>((const uint2*)tile_ranges, tile_ranges + 2 * T, a.ct,
                                                             n_cams, nbig, nmid, keys, sorted_ids, P_dev, ucap, nfall,
                                                             fall);
@@ -1582,17 +1620,18 @@ extern "C" gut_status gut_bin(const gut_projected* proj, int64_t n, const gut_ca
   char* cws = (char*)ws;
   char* pws = cws + cb;
   if ((st = bin_count_launch(proj, (int)n, bpc, dc, n_cams, T, cull, cws, tile_ranges, s)) != GUT_OK) return st;
-  // The scatter and the sorts up to 4095 entries are queued before the one
-  // wait (they check the capacity on the device); the long lists' sort is
-  // queued after it, only if there are long lists, and the fallback last.
+  // The scatter and the sorts up to 1023 entries are queued before the one
+  // wait (they check the capacity on the device); the longer lists' sorts and
+  // the fallback are queued after it, those that have lists to sort (an empty
+  // launch takes 2 to 3 us and a gap of 1.5).
   if ((st = bin_sort_launch(proj, (int)n, bpc, dc, n_cams, T, cull, cws, pair_capacity, pws, tile_ranges, sorted_ids, s,
                             kSortLists)) != GUT_OK)
     return st;
   uint64_t P = 0;
-  uint32_t n_long = 0;
-  if ((st = bin_count_wait(&P, &n_long)) != GUT_OK) return st;
+  int sorts = 0;
+  if ((st = bin_count_wait(&P, &sorts)) != GUT_OK) return st;
   if ((st = bin_sort_launch(proj, (int)n, bpc, dc, n_cams, T, cull, cws, pair_capacity, pws, tile_ranges, sorted_ids, s,
-                            (n_long ? kSortLong : 0) | kSortFallback)) != GUT_OK)
+                            sorts)) != GUT_OK)
     return st;
   if (n_pairs) *n_pairs = (int64_t)P;
   if ((int64_t)P > pair_capacity) {

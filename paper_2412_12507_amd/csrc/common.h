@@ -120,12 +120,13 @@ size_t bin_count_bytes(int64_t bpc, int64_t T);
 size_t bin_pair_bytes(int64_t cap);
 gut_status bin_count_launch(const gut_projected* proj, int n, int64_t bpc, const DevCam* dc, int n_cams, int64_t T,
                             bool cull, char* cws, uint32_t* tile_ranges, hipStream_t s);
-// bin_count_wait also returns the number of lists of 4096 entries or more
-// (n_long, when not null); the sort phase's parts can be queued separately:
-// the scatter and the sorts of shorter lists, the long lists' sort, and the
-// fallback sort of lists whose buckets came out too large, in that order.
-gut_status bin_count_wait(uint64_t* P, uint32_t* n_long = nullptr);
-constexpr int kSortLists = 1, kSortLong = 2, kSortFallback = 4, kSortAll = 7;
+// The sort phase's parts can be queued separately, in this order: the scatter
+// and the sorts of lists below 1024 entries, those of 1024 to 4095 and of 4096
+// and more, and the fallback sort of lists whose buckets came out too large.
+// bin_count_wait also returns which of them beyond the first have lists they
+// may be needed for (sorts, when not null).
+constexpr int kSortLists = 1, kSortMid = 2, kSortLong = 4, kSortFallback = 8, kSortAll = 15;
+gut_status bin_count_wait(uint64_t* P, int* sorts = nullptr);
 gut_status bin_sort_launch(const gut_projected* proj, int n, int64_t bpc, const DevCam* dc, int n_cams, int64_t T,
                            bool cull,
                            char* cws, int64_t cap, char* pws, uint32_t* tile_ranges, uint32_t* sorted_ids,
