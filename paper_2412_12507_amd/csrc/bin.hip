@@ -1190,14 +1190,18 @@ __global__ void __launch_bounds__(kMidThreads, 4) tile_sort_mid_kernel(
 }
 
 // K5 for lists of 4096 entries and more (the positions [0, nbig)): a fixed
-// grid of 1024-thread blocks, one per CU, by the bucket sort with up to 8192
-// buckets (16-bit counters) for lists of up to 16384 entries.  A longer list
+// grid of 1024-thread blocks, one per CU, by the bucket sort with dealt digits
+// (4096 buckets, 16-bit counters) for lists of up to 16384 entries.  A longer list
 // is first cut into runs of at most 16384 by the top 8 bits of the distance
 // from its lowest key (runs of whole digit values, so every key of a run is below
 // every key of the next), moved run by run into the ping-pong buffer, and
 // each run is bucket-sorted there.  A list with a run or bucket of more than
 // 128 entries, or a digit value of more than 16384, goes on the list for
-// tile_sort_fallback_kernel.
+// tile_sort_fallback_kernel.  Plain digits take a third less time, but of
+// hundreds of such lists a few usually have a bucket too large for them, and
+// those few then took as long again in the fallback: 457 lists of a 3M scene
+// 75 us and 99 there with plain digits, 117 and 5 with dealt ones (two lists of
+// a 1M scene 18 and 22).
 constexpr int kBigThreads = 1024, kBigBlocks = 256, kBigRows = 16;
 constexpr uint32_t kBigMax = kBigThreads * kBigRows;
 constexpr uint32_t kBigBucketMax = 128;
@@ -1314,14 +1318,14 @@ __global__ void __launch_bounds__(kBigThreads) tile_sort_big_kernel(
     const uint32_t L = r.y - r.x;
     bool done = false;
     if (L <= kBigMax) {
-      done = block_bucket_sort<kBigThreads, kBigRows, 13, true>(keys + r.x, L, ids + r.x, S.bucket, kBigBucketMax);
+      done = block_bucket_sort<kBigThreads, kBigRows, 13, true, true>(keys + r.x, L, ids + r.x, S.bucket, kBigBucketMax);
     } else if (L <= kBigMax * (kMaxRuns / 2) && split_list(keys + r.x, L, tmp + r.x, S.split, bounds, &nrun)) {
       const uint32_t m = nrun;
       done = true;
       for (uint32_t k = 0; k < m && done; k++) {
         const uint32_t a = bounds[k], n = bounds[k + 1] - a;
         if (n > 0)
-          done = block_bucket_sort<kBigThreads, kBigRows, 13, true>(tmp + r.x + a, n, ids + r.x + a, S.bucket,
+          done = block_bucket_sort<kBigThreads, kBigRows, 13, true, true>(tmp + r.x + a, n, ids + r.x + a, S.bucket,
                                                                     kBigBucketMax);
         __syncthreads();
       }
