@@ -90,8 +90,8 @@ def render_launches(cams):
 
 def pmc_summary(fetch_dir, write_dir, out_path, command):
     """Per-launch HBM bytes of the timed render kernel (render_multi_kernel<false,
-    false, false, false>: global shutter, no n_eval, Gaussian response, no
-    clip, both views in one launch) from two
+    false, false, false, 2>: global shutter, no n_eval, Gaussian response, no
+    clip, two quadrants a wave, both views in one launch) from two
     rocprofv3 --pmc runs of `bench.py --calib-copy` (FETCH_SIZE, then
     WRITE_SIZE, KiB per dispatch).
     Each counter is scaled by what it reads for a kernel of known traffic in
@@ -115,8 +115,8 @@ def pmc_summary(fetch_dir, write_dir, out_path, command):
     fr, wr = read(fetch_dir, "FETCH_SIZE"), read(write_dir, "WRITE_SIZE")
     f_add = pick(fr, "CUDAFunctor_add", "CUDAFunctorOnSelf_add")
     w_fill = pick(wr, "FillFunctor")
-    f_r = pick(fr, "gut::render_multi_kernel<false, false, false, false>")
-    w_r = pick(wr, "gut::render_multi_kernel<false, false, false, false>")
+    f_r = pick(fr, "gut::render_multi_kernel<false, false, false, false, 2>")
+    w_r = pick(wr, "gut::render_multi_kernel<false, false, false, false, 2>")
     if not (f_add and w_fill and f_r and w_r):
         raise SystemExit("pmc summary: calibration or render dispatches missing")
     ff = CALIB_BYTES / (f_add[0] * 1024.0)
@@ -142,10 +142,10 @@ def pmc_summary(fetch_dir, write_dir, out_path, command):
 # 4 B depth by the scatter; per pair 8 B of key written and read back, 4 B of
 # id written; per tile 24 B of counts, starts, ranges and order.
 PROJ_CAMS_PER_LAUNCH = 4
-# init, count, column scan, list scan, scatter, 4 sorts (three list lengths and the radix fallback); the
+# count, column scan, list scan, scatter, 4 sorts (three list lengths and the fallback); the
 # sort of lists of 4096 entries or more is launched only when there are such lists, and the two-view
 # benchmark batch has none
-BIN_KERNELS = 9
+BIN_KERNELS = 8
 
 
 def project_bytes(n, n_cams):

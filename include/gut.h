@@ -175,7 +175,7 @@ size_t gut_bin_workspace_bytes(int64_t n, const gut_camera* cams, int32_t n_cams
 /* Global per-tile depth sort (Sec. 4.3): each tile's list holds the visible
  * entries whose rectangle covers it (and, with tile_cull, whose extent
  * ellipse meets it), ordered by (depth, entry id).  The lists are built by a
- * counting sort over tiles and a per-tile radix sort in LDS.
+ * counting sort over tiles and a per-tile bucket sort in LDS.
  *   tile_ranges [3T] uint32   out: [T,2] [start, end) of each tile in sorted_ids
  *                             (an empty list has start == end),
  *                             then [T] the render order: for each camera, its

@@ -22,10 +22,13 @@
 //                           bits of the distance from its nearest key, with a
 //                           direct rank count inside each bucket; one wave per
 //                           list below 1024 entries, 256 threads up to 4095,
-//                           1024 threads beyond (cutting lists over 16384 into
-//                           runs first); lists with a large bucket go to a
-//                           sort with buckets dealt out by need, and from
-//                           there, if need be, to a stable LSD radix sort
+//                           1024 threads beyond, with buckets dealt out by need
+//                           (cutting lists over 16384 into runs first); lists
+//                           with a large bucket go to a fallback with dealt
+//                           buckets, and from there, if need be, to a stable
+//                           LSD radix sort
+// K2 is left out where a camera has one block, and the sorts beyond 1023
+// entries where no list needs them.
 // Nothing needs a device-wide atomic per pair or per touched tile: blocks on
 // different XCDs meet only in the count matrix, whose columns K2 scans.
 // The (depth bits, id) key orders exactly as a full (tile, depth, id) sort
@@ -52,8 +55,8 @@ constexpr int kLdsTiles = 16000;  // tiles counted in LDS at once (64 KB); large
 
 // Small per-call values after the count matrix: per-camera pair totals, the
 // total P, per camera the number of lists of at least 4096 and of at least
-// 1024 entries (the front of its render order), and the number of short
-// lists left to the radix sort; then that list of tiles (u32 [T]).
+// 1024 entries (the front of its render order), and the number of
+// lists left to the fallback sort; then that list of tiles (u32 [T]).
 struct SmallLayout {
   static constexpr size_t cam_pairs = 0;                     // u64 [kMaxCams]
   static constexpr size_t total = cam_pairs + 8 * kMaxCams;  // u64
@@ -864,10 +867,10 @@ __device__ __forceinline__ void sort_list_chunked(unsigned long long* __restrict
 // range gets a power of two of the buckets in proportion to its keys, from a
 // count of the pieces; half of the counters hold the buckets and the pieces'
 // table lies behind them.  Such lists of a 3M-particle rolling-shutter view
-// (1600x1200) take 95 us there and took 390 by the radix sort.  (Dealing in
+// (1600x1200) took 95 us there and 390 by the radix sort.  (Dealing in
 // every list, or after a failed count in the same kernel, holds more
-// registers: the sorts of 256 entries and more then run at half the waves or
-// spill, and took 1.3 to 3 times as long.)
+// registers: the sorts of 256 to 4095 entries then run at half the waves or
+// spill, and took 1.3 to 2 times as long.)
 constexpr uint32_t kBucketMax = 64;
 
 // A block of NT threads sorts one list of L <= NT ROWS keys with the bucket
@@ -1330,7 +1333,7 @@ __global__ void __launch_bounds__(kBigThreads) tile_sort_big_kernel(
         __syncthreads();
       }
     }
-    // the list's keys are still whole in keys: the radix sort takes it over
+    // the list's keys are still whole in keys: the fallback takes it over
     if (!done && threadIdx.x == 0) fall[atomicAdd(nfall, 1u)] = tile;
     __syncthreads();  // the LDS is reused by the next list
   }

@@ -342,7 +342,9 @@ __global__ void __launch_bounds__(kRThreads<NQ>, RS ? 3 : 5) render_multi_kernel
 // round-robin), and each XCD has its own counter, so every XCD walks its
 // share longest-first; a block that drains its XCD's share steals from the
 // others, and leaves once every counter is past its share.  Images go to
-// outs[camera] ([H, W, 3]).
+// outs[camera] ([H, W, 3]).  A batch has thousands of tiles, so the global
+// shutter takes two quadrants a wave (see quads_per_wave); the rolling shutter's
+// pairs hold too many registers for a second pixel a thread.
 template <bool RS>
 constexpr int kBatchNQ = RS ? 1 : 2;
 template <bool RS, bool GEN>

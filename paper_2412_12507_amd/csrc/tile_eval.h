@@ -625,8 +625,8 @@ struct WaveLists {
 
 // Builds the wave's lists for one chunk (pd: its first row, pf: its pairs'
 // flags) of quadrant q and returns the longest's length, with kMixed set if
-// the sign of o_g . d_g varies over the tile for one of their pairs.  The pairs flagged for quadrant q
-// are packed first; then each row of lanes tests 16 of them at a time against
+// the sign of o_g . d_g varies over the tile for one of their pairs.  The
+// pairs flagged for quadrant q are packed first; then each row of lanes tests 16 of them at a time against
 // its own block (a convex quadratic over a box as in ellipse_meets_box, here
 // in FP32 with slack for its rounding, relative to the quadratic's own terms
 // and 1e-4 of the ellipse, whose K' already carries 1e-3), so the test costs
@@ -635,7 +635,7 @@ struct WaveLists {
 constexpr uint32_t kMixed = 1u << 31;
 template <bool RS, bool BWD>
 __device__ inline uint32_t build_lists(const float4* pd, const unsigned short* pf, int q, const BlockBox& box,
-                                       bool run,                                       WaveLists& L) {
+                                       bool run, WaveLists& L) {
   constexpr int S = Slots<RS, BWD>::N;
   const int lane = threadIdx.x & 63, j0 = lane & 15;
   const uint32_t f0 = pf[lane], f1 = pf[lane + 64];
