@@ -26,9 +26,7 @@
 //
 // Blocks take tiles in the render order from gut_bin (longest lists first), and
 // waves of long lists raise their issue priority, so that the longest tiles
-// neither start last nor crawl behind short ones.  The global-shutter kernels
-// ask for five waves per SIMD (96 VGPRs; the FP64 pair setup keeps a few values
-// in scratch), the rolling-shutter ones for three.
+// neither start last nor crawl behind short ones.
 #include "tile_eval.h"
 
 namespace gut {
@@ -40,6 +38,15 @@ constexpr int kRThreads = 256 / NQ;
 // as their registers allow).
 template <bool RS, int NQ>
 constexpr int kRBatch = RS ? 128 : 256 / NQ;
+// Waves per SIMD asked for.  Global shutter, NQ = 2: five (96 VGPRs; the FP64
+// pair setup keeps a few values in scratch), two 1M 1920x1080 views 0.956 ms a
+// forward against 0.988 with four.  NQ = 1: four blocks of 32 KB are all the
+// LDS holds, and with the registers of four waves (122) nothing spills: 1M
+// 1280x720 with clip 0.461 against 0.488 ms with five and 0.482 with three.
+// Rolling shutter: three (167; with four 3M 1600x1200 takes 1.171 against
+// 1.092 ms, 132 bytes a lane in scratch).
+template <bool RS, int NQ>
+constexpr int kRWaves = RS ? 3 : NQ == 1 ? 4 : 5;
 
 // A thread's pixel: its ray in tile coordinates, transmittance and running
 // sums.  A pixel that has stopped (or is outside the image) has u = NaN: its
@@ -292,7 +299,7 @@ __device__ __forceinline__ void render_tile(
 // One block per tile, taken in the render order (longest lists first).  NE:
 // also count each pixel's evaluated entries (out_ne non-null).
 template <bool RS, bool NE, bool GEN, bool CLIP, int NQ>
-__global__ void __launch_bounds__(kRThreads<NQ>, RS ? 3 : 5) render_kernel(
+__global__ void __launch_bounds__(kRThreads<NQ>, (kRWaves<RS, NQ>)) render_kernel(
     DevCam cam, Thresholds th, int n, int cam_idx, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ ids,
     const float4* __restrict__ record, const float* __restrict__ rgb, const float* __restrict__ clip,
@@ -322,7 +329,7 @@ struct MultiCams {
 };
 
 template <bool RS, bool NE, bool GEN, bool CLIP, int NQ>
-__global__ void __launch_bounds__(kRThreads<NQ>, RS ? 3 : 5) render_multi_kernel(
+__global__ void __launch_bounds__(kRThreads<NQ>, (kRWaves<RS, NQ>)) render_multi_kernel(
     MultiCams mc, Thresholds th, int n, const uint2* __restrict__ ranges,
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ ids,
     const float4* __restrict__ record, const float* __restrict__ rgb, const float* __restrict__ clip,
