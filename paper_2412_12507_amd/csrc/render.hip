@@ -33,11 +33,13 @@ namespace gut {
 
 template <int NQ>
 constexpr int kRThreads = 256 / NQ;
-// Pairs per batch: one per thread, but under a rolling shutter, whose pairs
-// take 192 bytes of LDS, 128 (three blocks of 256 a CU hold 12 waves, as many
-// as their registers allow).
-template <bool RS, int NQ>
-constexpr int kRBatch = RS ? 128 : 256 / NQ;
+// Pairs per batch: one per thread.  (A rolling shutter's pairs take 192 bytes
+// of LDS; three blocks of 53 KB still fit a CU, as many as their registers
+// allow, and against batches of 128 half the barriers are left: 3M
+// particles 1600x1200 1.070 against 1.090 ms, a 300k training step at 800x600
+// 1.032 against 1.059.)
+template <int NQ>
+constexpr int kRBatch = 256 / NQ;
 // Waves per SIMD asked for.  Global shutter, NQ = 2: five (96 VGPRs; the FP64
 // pair setup keeps a few values in scratch), two 1M 1920x1080 views 0.956 ms a
 // forward against 0.988 with four.  NQ = 1: four blocks of 32 KB are all the
@@ -134,8 +136,8 @@ __device__ __forceinline__ bool pair_step(const PairRegs<RS>& r, const float4* P
 // A block's LDS.
 template <bool RS, int NQ>
 struct TileSmem {
-  float4 pd[batch_rows(kRBatch<RS, NQ>) * Slots<RS, false>::N];
-  unsigned short pf[kRBatch<RS, NQ>];
+  float4 pd[batch_rows(kRBatch<NQ>) * Slots<RS, false>::N];
+  unsigned short pf[kRBatch<NQ>];
   WaveLists lists[NQ == 1 ? 4 : 1];
   TileFrameD F;
   QuadBoxes wb;
@@ -153,7 +155,7 @@ __device__ __forceinline__ void render_tile(
     float* __restrict__ out_rgb,
     float* __restrict__ out_T, uint32_t* __restrict__ out_nc, uint32_t* __restrict__ out_ne,
     long long pix_base, TileSmem<RS, NQ>& sm) {
-  constexpr int S = Slots<RS, false>::N, B = kRBatch<RS, NQ>;
+  constexpr int S = Slots<RS, false>::N, B = kRBatch<NQ>;
   TileFrameD& F = sm.F;
   const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
   const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
