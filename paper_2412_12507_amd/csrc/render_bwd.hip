@@ -119,15 +119,18 @@ __device__ __forceinline__ bool bwd_step(const PairRegs<RS>& r, const float4* P,
   g[7] = cq.y;
   g[8] = cq.z;
   g[9] = gA * (ev.araw * __builtin_amdgcn_exp2f(-r.lsig));  // rho = (sigma rho) / sigma
-  g[10] = wgt * p.gC[0];
-  g[11] = wgt * p.gC[1];
-  g[12] = wgt * p.gC[2];
+  // (selected and not left to the zero weight: a loss gradient may be infinite or
+  // NaN, and must not reach entries its pixel does not blend)
+  g[10] = hit ? wgt * p.gC[0] : 0.0f;
+  g[11] = hit ? wgt * p.gC[1] : 0.0f;
+  g[12] = hit ? wgt * p.gC[2] : 0.0f;
   g[13] = g[14] = g[15] = 0.0f;
   return true;
 }
 
 // The step on pair i of the batch from list position b on, and its sums into
-// the pair's row.
+// the pair's row (of the lists' padding too, kChunk, whose sums are zero).
+static_assert(kChunk <= kBwBatch, "the padding has a row");
 template <bool RS, bool GEN, bool CLIP>
 __device__ __forceinline__ void bwd_pair(const PairRegs<RS>& r, const float4* pd, uint32_t i, uint32_t b, bool mixed,
                                          const Thresholds& th, BwPixel& p, double* rows, int lane) {
@@ -173,7 +176,7 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
     double* __restrict__ acc_rgb) {
   constexpr int S = Slots<RS, true>::N;
   __shared__ float4 pd[batch_rows(kBwBatch) * S];
-  __shared__ double rows[kBwBatch * kRow];
+  __shared__ double rows[(kBwBatch + 1) * kRow];  // the last one the padding's, never read
   __shared__ uint32_t pe[2][kBwBatch];  // the entries of this batch and of the one before
   __shared__ unsigned short pf[kBwBatch];
   __shared__ WaveLists lists[kBwThreads / 64];
@@ -191,7 +194,7 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
   py += ty * kTile;
   if (t == 0) { tile_frame(cam, tx, ty, &F); maxlast_s = 0; }
   write_dummies<RS, true>(pd, kBwBatch);
-  for (int i = t; i < kBwBatch * kRow; i += kBwThreads) rows[i] = 0.0;
+  for (int i = t; i < (kBwBatch + 1) * kRow; i += kBwThreads) rows[i] = 0.0;
   __syncthreads();
 
   BwPixel p = {};
