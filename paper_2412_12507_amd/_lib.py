@@ -9,6 +9,9 @@ from __future__ import annotations
 import ctypes as C
 import os
 
+import numpy as np
+import torch
+
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "libgut.so")
 
@@ -144,30 +147,41 @@ _MODELS = {"pinhole": GUT_PINHOLE, "fisheye": GUT_FISHEYE_OPENCV}
 _SHUTTERS = {"global": GUT_GLOBAL_SHUTTER, "rolling": GUT_ROLLING_TOP_TO_BOTTOM}
 
 
-def _values(x):
-    # (one conversion of an array; an element at a time costs ten times as much)
-    return x.tolist() if getattr(x, "ndim", 0) in (1, 2) else x
+def _plain(x):
+    """Whether x is an array whose tolist() holds what its elements give one at
+    a time (which costs ten times as much): a numpy array or torch tensor of
+    real numbers.  Other forms are read element by element."""
+    if type(x) is np.ndarray:
+        return x.dtype.kind in "fiu"
+    return type(x) is torch.Tensor and not x.is_complex()
+
+
+def _vector(x):
+    # (of a column, (n, 1), each element is an array of one value, which float takes)
+    return x.tolist() if _plain(x) and x.ndim == 1 else x
 
 
 def _rotation(R):
     """The first nine values of a 3x3 rotation (rows, or flat), as floats."""
-    R = _values(R)
+    if _plain(R) and (R.ndim == 2 or (R.ndim == 1 and type(R) is np.ndarray)):
+        R = R.tolist()
     flat = []
     for row in R:
         if hasattr(row, "__len__"):
             flat.extend(row)
         else:
             flat.append(row)
+    flat = [float(v) for v in flat]
     if len(flat) < 9:
         raise IndexError("a rotation has nine values")
-    return [float(v) for v in flat[:9]]
+    return flat[:9]
 
 
 def fill_camera(c: Camera, cam: dict) -> Camera:
     c.model, c.shutter = _MODELS[cam["model"]], _SHUTTERS[cam["shutter"]]
     c.width, c.height = int(cam["width"]), int(cam["height"])
     c.fx, c.fy, c.cx, c.cy = float(cam["fx"]), float(cam["fy"]), float(cam["cx"]), float(cam["cy"])
-    k, t0, t1 = _values(cam["k"]), _values(cam["t0"]), _values(cam["t1"])
+    k, t0, t1 = _vector(cam["k"]), _vector(cam["t0"]), _vector(cam["t1"])
     c.k[:] = [float(k[0]), float(k[1]), float(k[2]), float(k[3])]
     c.R0[:], c.R1[:] = _rotation(cam["R0"]), _rotation(cam["R1"])
     c.t0[:] = [float(t0[0]), float(t0[1]), float(t0[2])]
