@@ -291,9 +291,9 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
 //
 // Sums.  A lane blends the nearest hit of its own buffer, so the hits one
 // step blends are a few different particles.  Their 13 values go to FP32 LDS
-// rows by list position, over a window of the six latest batches (768
-// positions); a row is added to the FP64 per-particle sums when its batch
-// leaves the window, 13 atomics per (tile, particle).  Lanes that blend the
+// rows by list position, over a window of the latest positions, from the last
+// multiple of 256 less 256 on; a row is added to the FP64 per-particle sums
+// when its batch has left the window, 13 atomics per (tile, particle).  Lanes that blend the
 // same hit would meet on one LDS address, one after the other (with every
 // lane adding its own values, LDS was busy 58% of the kernel, at 43 cycles an
 // atomic), so each row of 16 lanes first sums the lanes that share its first
@@ -302,11 +302,13 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
 // the second or fourth hit that lanes share costs more instructions than it
 // saves: 1.95 and 2.08 ms a training step against 1.92.)  The
 // buffer holds list positions; a hit that has stayed longer than the window
-// (a buffer usually turns over within a batch) goes to the FP64 sums at once.
+// (a buffer usually turns over within a batch) goes to the FP64 sums at once,
+// each lane's values by themselves.
 constexpr int kKBufB = 16;
 constexpr int kKThreadsB = 256;
 constexpr int kKBatchB = 128;
-constexpr int kWin = 6 * kKBatchB;  // list positions with an LDS row (of 13 values: an odd stride spreads them over the banks)
+constexpr int kWinStep = 2 * kKBatchB;  // the window starts at a multiple of this
+constexpr int kWin = 2 * kWinStep;  // list positions with an LDS row (of 13 values: an odd stride spreads them over the banks)
 
 struct KBufGrad {
   double* acc;
@@ -318,14 +320,11 @@ struct KBufGrad {
   float* accw;           // the window's rows (LDS)
   int n, cam_idx;
   float t_min;
-  uint32_t wlo, w0;  // lowest list position in the window; a multiple of kWin up to 2 kWin below its end
+  uint32_t wlo;  // lowest list position in the window
 };
 
-// The row of list position pos, pos mod kWin, for wlo <= pos < wlo + kWin.
-__device__ __forceinline__ uint32_t kbuf_row(uint32_t pos, const KBufGrad& K) {
-  const uint32_t r = pos - K.w0;
-  return min(r, r - (uint32_t)kWin);
-}
+// The row of list position pos, wlo <= pos < wlo + kWin.
+__device__ __forceinline__ uint32_t kbuf_row(uint32_t pos) { return pos & (kWin - 1); }
 
 // Value k of the 13 into the FP64 sums of entry e.
 __device__ __forceinline__ void kbuf_add64(uint32_t e, int k, double x, const KBufGrad& K) {
@@ -338,25 +337,22 @@ __device__ __forceinline__ void kbuf_add64(uint32_t e, int k, double x, const KB
 // pos) to the sums.
 __device__ __forceinline__ void kbuf_add(bool act, uint32_t pos, const float (&v)[kRow], const KBufGrad& K) {
   const int lane = threadIdx.x & 63, k0 = lane & 15;
-  const unsigned long long A = __builtin_amdgcn_ballot_w64(act);
-  if (A == 0ull) return;
+  if (__builtin_amdgcn_ballot_w64(act) == 0ull) return;
+  const unsigned long long A = __builtin_amdgcn_ballot_w64(act && pos >= K.wlo);
   const uint32_t bits = (lane & 32 ? (uint32_t)(A >> 32) : (uint32_t)A) >> (lane & 16) & 0xffffu;
   const int lead = bits ? (lane & 48) + __builtin_ctz(bits) : lane;
   const uint32_t pl = (uint32_t)__shfl((int)pos, lead, 64);
-  const bool match = act && pos == pl;
+  const bool match = act && pos >= K.wlo && pos == pl;
   float g[16];
 #pragma unroll
   for (int k = 0; k < kRow; k++) g[k] = match ? v[k] : 0.0f;
   g[13] = g[14] = g[15] = 0.0f;
   const float tot = row_reduce16(g, lane);
-  if (k0 < kRow && tot != 0.0f) {
-    if (pl >= K.wlo) atomicAdd(&K.accw[kbuf_row(pl, K) * kRow + k0], tot);
-    else kbuf_add64(K.lids[pl], k0, (double)tot, K);
-  }
+  if (k0 < kRow && tot != 0.0f) atomicAdd(&K.accw[kbuf_row(pl) * kRow + k0], tot);
   act = act && !match;
   if (!act) return;
   if (pos >= K.wlo) {
-    float* row = K.accw + kbuf_row(pos, K) * kRow;
+    float* row = K.accw + kbuf_row(pos) * kRow;
 #pragma unroll
     for (int k = 0; k < kRow; k++) atomicAdd(&row[k], v[k]);
   } else {
@@ -403,7 +399,7 @@ __device__ __forceinline__ void kbuf_blend_bwd(bool on, float a, uint32_t pos, f
     // an LDS row is read in any case and an older hit's colour then replaces
     // it; the empty register constraint keeps the compiler from folding the
     // two reads into one flat read through a selected pointer
-    const float* cl = K.cw + 3 * (pos < K.wlo ? 0u : kbuf_row(pos, K));
+    const float* cl = K.cw + 3 * kbuf_row(pos);
     float c0 = cl[0], c1 = cl[1], c2 = cl[2];
     asm volatile("" : "+v"(c0), "+v"(c1), "+v"(c2));
     if (pos < K.wlo) {
@@ -482,7 +478,7 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   }
   const uint2 rg = ranges[cam.tile_base + tile];
   const uint32_t len = __builtin_amdgcn_readfirstlane(rg.y - rg.x);
-  KBufGrad K = {acc, acc_rgb, rgb, ids + rg.x, pew, cw, accw, n, cam_idx, th.t_min, 0u, 0u};
+  KBufGrad K = {acc, acc_rgb, rgb, ids + rg.x, pew, cw, accw, n, cam_idx, th.t_min, 0u};
 
   float bd[kKBufB], ba[kKBufB], bx[kKBufB], by[kKBufB], bz[kKBufB], br[kKBufB], bf[kKBufB];
   uint32_t bi[kKBufB];  // list positions
@@ -494,15 +490,12 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   }
   float T = 1.0f;
   uint32_t done = active ? 0u : 1u;  // a 0/1 vector register, as in render_tile
-  int base = -kKBatchB;  // this batch's rows
   for (uint32_t b = 0; b < len; b += kKBatchB) {
     if (__syncthreads_count(done == 0u) == 0) break;
-    base = base + kKBatchB == kWin ? 0 : base + kKBatchB;
-    K.wlo = b + kKBatchB > (uint32_t)kWin ? b + kKBatchB - kWin : 0u;
-    K.w0 = b >= (uint32_t)kWin ? b - base - kWin : 0u;
+    const uint32_t wb0 = b & ~(uint32_t)(kWinStep - 1), base = b & (kWin - 1);  // base: this batch's rows
+    K.wlo = wb0 >= (uint32_t)kWinStep ? wb0 - kWinStep : 0u;
     if (t < kKBatchB) {
-      // the rows of batch b - kWin leave the window (their batch's eval ended
-      // before the barrier above)
+      // the rows of batch b - kWin have left the window (before the barrier above)
       if (b >= (uint32_t)kWin) kbuf_flush_row(base + t, K);
       uint32_t fl = 0u;
       if (b + t < len) {
