@@ -27,6 +27,8 @@
 // Blocks take tiles in the render order from gut_bin (longest lists first), and
 // waves of long lists raise their issue priority, so that the longest tiles
 // neither start last nor crawl behind short ones.
+#include <type_traits>
+
 #include "tile_eval.h"
 
 namespace gut {
@@ -120,10 +122,10 @@ __device__ __forceinline__ bool list_step(const Entry<RS>& e, uint32_t base, boo
 
 // NQ = 2, one step: one pair (1-based place idx1) against one quadrant.
 template <bool RS, bool NE, bool GEN, bool CLIP>
-__device__ __forceinline__ bool pair_step(const PairRegs<RS>& r, const float4* P, uint32_t idx1, bool mixed,
+__device__ __forceinline__ bool pair_step(const PairRegs<RS>& r, const float4* P, uint32_t idx1, uint32_t mixed,
                                           const Thresholds& th, Pixel& p) {
   Eval ev;
-  eval_test<RS>(r, P, p.u, p.v, p.dt, mixed, &ev);
+  eval_test<RS>(r, P, p.u, p.v, p.dt, mixed != 0u, &ev);
   if (CLIP) clip_test<RS>(r, P, p.u, p.v, p.dt, p.dlen, p.clip, &ev);
   const bool live = eval_hit<RS>(r, ev);
   if (!wave_any(live)) return false;  // nothing reaches alpha_min here
@@ -133,16 +135,22 @@ __device__ __forceinline__ bool pair_step(const PairRegs<RS>& r, const float4* P
   return pixel_blend<NE>(live, live ? ev.a : 0.0f, col, idx1, idx1, th, p, p.last);
 }
 
-// A block's LDS.
+// A block's LDS: what its walk uses.
+struct NoLists {};
 template <bool RS, int NQ>
 struct TileSmem {
-  float4 pd[batch_rows(kRBatch<NQ>) * Slots<RS, false>::N];
+  float4 pd[(NQ == 1 ? batch_rows(kRBatch<NQ>) : kRBatch<NQ>) * Slots<RS, false>::N];
   unsigned short pf[kRBatch<NQ>];
-  WaveLists lists[NQ == 1 ? 4 : 1];
+  typename std::conditional<NQ == 1, WaveLists[4], NoLists>::type lists;
   TileFrameD F;
   QuadBoxes wb;
   float red[12 / NQ];
 };
+// Global shutter, NQ = 2: ten blocks of two waves a CU are the five waves a
+// SIMD asked for; LDS is dealt in units of 1280 bytes.  (With 15840 bytes, nine
+// blocks: two 1M 1920x1080 views 521 against 495 us, one 3840x2160 735
+// against 692.)
+static_assert(10 * ((sizeof(TileSmem<false, 2>) + 1279) / 1280) * 1280 <= 160 * 1024, "ten blocks a CU");
 
 // One tile of one camera.  out_* are indexed by pix_base + y * W + x.  GEN:
 // response of degree th.kdeg > 2.  CLIP: per-pixel clip distances (hybrid
@@ -164,7 +172,7 @@ __device__ __forceinline__ void render_tile(
   px += tx * kTile;
   py0 += ty * kTile;
   if (t == 0) tile_frame(cam, tx, ty, &F);
-  write_dummies<RS, false>(sm.pd, B);
+  if (NQ == 1) write_dummies<RS, false>(sm.pd, B);
   const uint2 rg = ranges[cam.tile_base + tile];
   const uint32_t len = __builtin_amdgcn_readfirstlane(rg.y - rg.x);
   __syncthreads();
@@ -268,7 +276,11 @@ __device__ __forceinline__ void render_tile(
           const float4* P = &sm.pd[q * S];
           PairRegs<RS> r;
           load_pair<RS>(P, r);
-          const bool mixed = ((uint32_t)(xm >> ql) & 1u) != 0u;
+          uint32_t mixed = (uint32_t)(xm >> ql) & 1u;
+          if (!RS) {  // this pair's own flag, kept out of vector registers (three instructions of 60 a pair)
+            mixed = __builtin_amdgcn_readfirstlane(mixed);
+            r.flag = -1.0f;
+          }
           if ((ma >> ql) & 1ull)
             if (pair_step<RS, NE, GEN, CLIP>(r, P, idx1, mixed, th, p[0]) && !wave_any(p[0].u == p[0].u)) {
               ma = 0ull;
