@@ -74,9 +74,10 @@ struct BwPixel {
 // One step: each lane's own list entry (at list position idx) against its
 // pixel: the pixel's terms of the entry's sums, G = sum c p p^T (symmetric,
 // 6), h = sum c p (3), dL/dsigma, dL/dc (3), zero where it is not hit.
-// Returns false when no lane is hit (g is then not written).
+// Returns false when no lane is hit (g is then not written).  odd (uniform over
+// the wave): the loss gradient of some pixel is not finite.
 template <bool RS, bool GEN, bool CLIP>
-__device__ __forceinline__ bool bwd_step(const PairRegs<RS>& r, const float4* P, uint32_t idx, bool mixed,
+__device__ __forceinline__ bool bwd_step(const PairRegs<RS>& r, const float4* P, uint32_t idx, bool mixed, bool odd,
                                          const Thresholds& th, BwPixel& p, float (&g)[16]) {
   Eval ev;
   eval_test<RS>(r, P, p.u, p.v, p.dt, mixed, &ev);
@@ -119,11 +120,15 @@ __device__ __forceinline__ bool bwd_step(const PairRegs<RS>& r, const float4* P,
   g[7] = cq.y;
   g[8] = cq.z;
   g[9] = gA * (ev.araw * __builtin_amdgcn_exp2f(-r.lsig));  // rho = (sigma rho) / sigma
-  // (selected and not left to the zero weight: a loss gradient may be infinite or
-  // NaN, and must not reach entries its pixel does not blend)
-  g[10] = hit ? wgt * p.gC[0] : 0.0f;
-  g[11] = hit ? wgt * p.gC[1] : 0.0f;
-  g[12] = hit ? wgt * p.gC[2] : 0.0f;
+  g[10] = wgt * p.gC[0];
+  g[11] = wgt * p.gC[1];
+  g[12] = wgt * p.gC[2];
+  if (odd) {  // an infinite or NaN gradient does not reach entries its pixel does not blend
+    asm volatile("");  // (kept a branch: as selects these take 0.8% of a training step)
+    g[10] = hit ? g[10] : 0.0f;
+    g[11] = hit ? g[11] : 0.0f;
+    g[12] = hit ? g[12] : 0.0f;
+  }
   g[13] = g[14] = g[15] = 0.0f;
   return true;
 }
@@ -133,9 +138,9 @@ __device__ __forceinline__ bool bwd_step(const PairRegs<RS>& r, const float4* P,
 static_assert(kChunk <= kBwBatch, "the padding has a row");
 template <bool RS, bool GEN, bool CLIP>
 __device__ __forceinline__ void bwd_pair(const PairRegs<RS>& r, const float4* pd, uint32_t i, uint32_t b, bool mixed,
-                                         const Thresholds& th, BwPixel& p, double* rows, int lane) {
+                                         bool odd, const Thresholds& th, BwPixel& p, double* rows, int lane) {
   float g[16];
-  if (!bwd_step<RS, GEN, CLIP>(r, pd + i * Slots<RS, true>::N, b + i, mixed, th, p, g)) return;
+  if (!bwd_step<RS, GEN, CLIP>(r, pd + i * Slots<RS, true>::N, b + i, mixed, odd, th, p, g)) return;
   const float tot = row_reduce16(g, lane);
   if ((lane & 15) < kRow && tot != 0.0f) atomicAdd(&rows[i * kRow + (lane & 15)], (double)tot);
 }
@@ -220,6 +225,7 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
       p.Z = fma((double)p.gC[c], (double)out_rgb[3 * pix + c], p.Z);
     }
   }
+  const bool odd = wave_any(!(fabsf(p.gC[0]) < INFINITY && fabsf(p.gC[1]) < INFINITY && fabsf(p.gC[2]) < INFINITY));
   atomicMax(&maxlast_s, p.last);
   __syncthreads();  // (also publishes wb)
   const uint2 rg = ranges[cam.tile_base + tile];
@@ -262,11 +268,11 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
     for (int k = 0; k < cnt; k += 2) {
       load_pair<RS>(pd + i1 * S, r1);
       const uint32_t i2 = mine[k + 2];
-      bwd_pair<RS, GEN, CLIP>(r0, pd, i0, b, mixed, th, p, rows, lane);
+      bwd_pair<RS, GEN, CLIP>(r0, pd, i0, b, mixed, odd, th, p, rows, lane);
       i0 = i2;
       load_pair<RS>(pd + i0 * S, r0);
       const uint32_t i3 = mine[k + 3];
-      bwd_pair<RS, GEN, CLIP>(r1, pd, i1, b, mixed, th, p, rows, lane);
+      bwd_pair<RS, GEN, CLIP>(r1, pd, i1, b, mixed, odd, th, p, rows, lane);
       i1 = i3;
     }
   }
