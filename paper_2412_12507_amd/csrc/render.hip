@@ -747,22 +747,35 @@ static gut_status launch_render_kbuffer(const DevCam& cam, const Thresholds& th,
   return GUT_OK;
 }
 
-// Quadrants per wave of a launch over this many tiles.  Up to 10000 tiles a
-// launch ends with its longest lists or has few waves to hide a step's latency
-// behind, and the lists win (ms per render, lists against pairs): 1k particles
-// 128x128 0.014 (0.017), 300k 800x600 rolling 0.32 (0.51), 1M 1280x720 0.33
-// (0.38), 3M 1600x1200 rolling (7500 tiles) 0.53 (0.64), one 1M fisheye
-// 1920x1080 view (8160) 0.30 (0.29).  Beyond, the vector ALUs are full either
-// way (250M instructions) and the pairs' shorter waits win: two 1M 1920x1080
-// views (16320) 0.60 (0.55).
-static int quads_per_wave(unsigned tiles) { return tiles < 10000u ? 1 : 2; }
+// Quadrants per wave of a launch over this many tiles and entries (particles
+// times cameras).  Lists spread a tile's walk over twice the waves and skip
+// what misses a 4x4 block: they win where few tiles have the chip to themselves
+// and where the longest lists outlast the others, and lose where the launch
+// fills the chip evenly, since a pair that covers its quadrants then takes twice
+// the steps.  The host does not know the lists' lengths, so particles a tile
+// stand for them.  us a render, lists against pairs (1 against 2):
+//   1900 tiles   100k clustered 41 (75), 20k large 85 (89), the same rolling 61 (111)
+//   3600         100k 57 (58), fisheye 62 (118), rolling 87 (153); 20k large 130 (112)
+//   5700         100k 81 (61), fisheye 87 (99); 1M 220 (204), fisheye 223 (336);
+//                200k large 211 (185)
+//   7500         100k 102 (76); 1M 282 (270), fisheye 249 (322), rolling 391 (421);
+//                3M rolling 498 (532); 200k large 266 (226)
+//   8160         100k 116 (83); 1M 306 (260), rolling 445 (425), fisheye 293 (273) and,
+//                from three other eyes, 240 to 270 (289 to 331)
+//   16320        two 1M views 556 to 584 (481 to 489)
+//   32400        1M 897 (671), fisheye 770 (602), rolling 1200 (1035)
+// So lists below 2048 tiles, pairs from 10000 on, and between lists from
+// tiles / 150 particles a tile on.
+static int quads_per_wave(int64_t tiles, int64_t entries) {
+  return tiles < 2048 || (tiles < 10000 && 150 * entries >= tiles * tiles) ? 1 : 2;
+}
 
 gut_status launch_render(const DevCam& cam, const Thresholds& th, int n, int cam_idx,
                          const uint32_t* ranges, const uint32_t* order, const uint32_t* ids,
                          const float* record, const float* rgb, const float* clip, float* out_rgb,
                          float* out_T, uint32_t* out_nc, uint32_t* out_ne, hipStream_t s) {
   dim3 grid(cam.tiles_x * cam.tiles_y);
-  const int nq = quads_per_wave(grid.x);
+  const int nq = quads_per_wave(grid.x, n);
 #define GUT_RKQ(RS, NE, GEN, CLIP, NQ)                                                             \
   render_kernel<RS, NE, GEN, CLIP, NQ><<<grid, kRThreads<NQ>, 0, s>>>(cam, th, n, cam_idx, (const uint2*)ranges, \
                                                           order, ids, (const float4*)record, rgb,     \
@@ -801,7 +814,7 @@ static gut_status launch_render_group(const DevCam* dc, int c0, int c1, const Th
     mc.idx[k] = c0 + k;
   }
   dim3 grid(mc.n * dc[c0].tiles_x * dc[c0].tiles_y);
-  const int nq = quads_per_wave(grid.x);
+  const int nq = quads_per_wave(grid.x, (int64_t)n * mc.n);
 #define GUT_RMQ(RS, NE, GEN, CLIP, NQ)                                                               \
   render_multi_kernel<RS, NE, GEN, CLIP, NQ><<<grid, kRThreads<NQ>, 0, s>>>(mc, th, n, (const uint2*)ranges, order, \
                                                                 ids, (const float4*)record, rgb, clip,  \
