@@ -147,31 +147,32 @@ _MODELS = {"pinhole": GUT_PINHOLE, "fisheye": GUT_FISHEYE_OPENCV}
 _SHUTTERS = {"global": GUT_GLOBAL_SHUTTER, "rolling": GUT_ROLLING_TOP_TO_BOTTOM}
 
 
-def _plain(x):
-    """Whether x is an array whose tolist() holds what its elements give one at
-    a time (which costs ten times as much): a numpy array or torch tensor of
-    real numbers.  Other forms are read element by element."""
-    if type(x) is np.ndarray:
-        return x.dtype.kind in "fiu"
-    return type(x) is torch.Tensor and not x.is_complex()
-
-
+# Arrays are read at once where tolist() holds what their elements give one at a
+# time (which costs ten times as much): numpy arrays and torch tensors of real
+# numbers.  Other forms are read element by element; of a column, (n, 1), each
+# element is an array of one value, which float takes.
 def _vector(x):
-    # (of a column, (n, 1), each element is an array of one value, which float takes)
-    return x.tolist() if _plain(x) and x.ndim == 1 else x
+    t = type(x)
+    if t is np.ndarray:
+        return x.tolist() if x.ndim == 1 and x.dtype.kind in "fiu" else x
+    return x.tolist() if t is torch.Tensor and x.ndim == 1 and not x.is_complex() else x
 
 
 def _rotation(R):
-    """The first nine values of a 3x3 rotation (rows, or flat), as floats."""
-    if _plain(R) and (R.ndim == 2 or (R.ndim == 1 and type(R) is np.ndarray)):
-        R = R.tolist()
-    flat = []
-    for row in R:
-        if hasattr(row, "__len__"):
-            flat.extend(row)
-        else:
-            flat.append(row)
-    flat = [float(v) for v in flat]
+    """The first nine values of a 3x3 rotation (rows, or flat)."""
+    t = type(R)
+    if t is np.ndarray and R.dtype.kind in "fiu" and 0 < R.ndim < 3:
+        flat = R.ravel().tolist()
+    else:
+        if t is torch.Tensor and R.ndim == 2 and not R.is_complex():
+            R = R.tolist()
+        flat = []
+        for row in R:
+            if hasattr(row, "__len__"):
+                flat.extend(row)
+            else:
+                flat.append(row)
+        flat = [float(v) for v in flat]
     if len(flat) < 9:
         raise IndexError("a rotation has nine values")
     return flat[:9]
