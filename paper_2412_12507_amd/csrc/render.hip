@@ -310,6 +310,29 @@ __device__ __forceinline__ void render_tile(
   }
 }
 
+// Quadrants per wave of a launch over this many tiles and entries (particles
+// times cameras).  Lists spread a tile's walk over twice the waves and skip
+// what misses a 4x4 block: they win where few tiles have the chip to themselves
+// and where the longest lists outlast the others, and lose where the launch
+// fills the chip evenly, since a pair that covers its quadrants then takes twice
+// the steps.  The host does not know the lists' lengths, so particles a tile
+// stand for them.  us a render, lists against pairs (1 against 2):
+//   1900 tiles   100k clustered 41 (75), 20k large 85 (89), the same rolling 61 (111)
+//   3600         100k 57 (58), fisheye 62 (118), rolling 87 (153); 20k large 130 (112)
+//   5700         100k 81 (61), fisheye 87 (99); 1M 220 (204), fisheye 223 (336);
+//                200k large 211 (185)
+//   7500         100k 102 (76); 1M 282 (270), fisheye 249 (322), rolling 391 (421);
+//                3M rolling 498 (532); 200k large 266 (226)
+//   8160         100k 116 (83); 1M 306 (260), rolling 445 (425), fisheye 293 (273) and,
+//                from three other eyes, 240 to 270 (289 to 331)
+//   16320        two 1M views 556 to 584 (481 to 489)
+//   32400        1M 897 (671), fisheye 770 (602), rolling 1200 (1035)
+// So lists below 2048 tiles, pairs from 10000 on, and between lists from
+// tiles / 150 particles a tile on.
+static int quads_per_wave(int64_t tiles, int64_t entries) {
+  return tiles < 2048 || (tiles < 10000 && 150 * entries >= tiles * tiles) ? 1 : 2;
+}
+
 // One block per tile, taken in the render order (longest lists first).  NE:
 // also count each pixel's evaluated entries (out_ne non-null).
 template <bool RS, bool NE, bool GEN, bool CLIP, int NQ>
@@ -363,19 +386,17 @@ __global__ void __launch_bounds__(kRThreads<NQ>, (kRWaves<RS, NQ>)) render_multi
 // round-robin), and each XCD has its own counter, so every XCD walks its
 // share longest-first; a block that drains its XCD's share steals from the
 // others, and leaves once every counter is past its share.  Images go to
-// outs[camera] ([H, W, 3]).  A batch has thousands of tiles, so the global
-// shutter takes two quadrants a wave (see quads_per_wave); the rolling shutter's
-// pairs hold too many registers for a second pixel a thread.
-template <bool RS>
-constexpr int kBatchNQ = RS ? 1 : 2;
-template <bool RS, bool GEN>
-__global__ void __launch_bounds__(kRThreads<kBatchNQ<RS>>, RS ? 3 : 4) render_batch_kernel(
+// outs[camera] ([H, W, 3]).  Either walk, by the same rule as a launch of its own
+// (us, two requests in turn, lists against pairs: one rolling 3840x2160 camera
+// each, 1M particles, 4540 (3967); two rolling 800x600, 300k, 1123 (1573)).
+template <bool RS, bool GEN, int NQ>
+__global__ void __launch_bounds__(kRThreads<NQ>, RS ? 3 : 4) render_batch_kernel(
     const DevCam* __restrict__ cams, const int* __restrict__ cam_list,
     const int* __restrict__ item_start, int n_list, int n_items, unsigned* __restrict__ counters,
     Thresholds th, int n, const uint2* __restrict__ ranges, const uint32_t* __restrict__ order,
     const uint32_t* __restrict__ ids,
     const float4* __restrict__ record, const float* __restrict__ rgb, float* const* __restrict__ outs) {
-  __shared__ TileSmem<RS, kBatchNQ<RS>> sm;
+  __shared__ TileSmem<RS, NQ> sm;
   __shared__ int item_s;
   const int nx = 8;
   const int my = blockIdx.x % nx;
@@ -404,8 +425,8 @@ __global__ void __launch_bounds__(kRThreads<kBatchNQ<RS>>, RS ? 3 : 4) render_ba
     const int c = __builtin_amdgcn_readfirstlane(cam_list[j]);
     const DevCam& cam = cams[c];
     const int tile = (int)order[cam.tile_base + (item - item_start[j])];
-    render_tile<RS, false, GEN, false, kBatchNQ<RS>>(cam, th, n, c, tile, ranges, ids, record, rgb, nullptr, outs[c],
-                                       nullptr, nullptr, nullptr, 0, sm);
+    render_tile<RS, false, GEN, false, NQ>(cam, th, n, c, tile, ranges, ids, record, rgb, nullptr, outs[c],
+                                           nullptr, nullptr, nullptr, 0, sm);
   }
 }
 
@@ -435,14 +456,18 @@ gut_status render_batch_launch(const DevCam* d_cams, const DevCam* h_cams, int n
     if (m == 0) continue;
     int* dl = d_lists + type * (2 * kMaxCams + 1);
     GUT_HIP(hipMemcpyAsync(dl, hl, (2 * kMaxCams + 1) * sizeof(int), hipMemcpyHostToDevice, s));
-#define GUT_RB(RS, GEN)                                                                          \
-  render_batch_kernel<RS, GEN><<<n_blocks, kRThreads<kBatchNQ<RS>>, 0, s>>>(                                    \
+    const int nq = quads_per_wave(items, (int64_t)n * m);
+#define GUT_RBQ(RS, GEN, NQ)                                                                     \
+  render_batch_kernel<RS, GEN, NQ><<<n_blocks, kRThreads<NQ>, 0, s>>>(                              \
       d_cams, dl, dl + kMaxCams, m, items, d_counters + 8 * type, th, n, (const uint2*)ranges, order, \
       ids, (const float4*)record, rgb, d_outs)
+#define GUT_RB(RS, GEN) \
+  do { if (nq == 1) GUT_RBQ(RS, GEN, 1); else GUT_RBQ(RS, GEN, 2); } while (0)
     const bool gen = th.kdeg != 2;
     if (type == 1) { if (gen) GUT_RB(true, true); else GUT_RB(true, false); }
     else { if (gen) GUT_RB(false, true); else GUT_RB(false, false); }
 #undef GUT_RB
+#undef GUT_RBQ
     GUT_LAUNCH_CHECK();
   }
   return GUT_OK;
@@ -745,29 +770,6 @@ static gut_status launch_render_kbuffer(const DevCam& cam, const Thresholds& th,
 #undef GUT_RKB2
   GUT_LAUNCH_CHECK();
   return GUT_OK;
-}
-
-// Quadrants per wave of a launch over this many tiles and entries (particles
-// times cameras).  Lists spread a tile's walk over twice the waves and skip
-// what misses a 4x4 block: they win where few tiles have the chip to themselves
-// and where the longest lists outlast the others, and lose where the launch
-// fills the chip evenly, since a pair that covers its quadrants then takes twice
-// the steps.  The host does not know the lists' lengths, so particles a tile
-// stand for them.  us a render, lists against pairs (1 against 2):
-//   1900 tiles   100k clustered 41 (75), 20k large 85 (89), the same rolling 61 (111)
-//   3600         100k 57 (58), fisheye 62 (118), rolling 87 (153); 20k large 130 (112)
-//   5700         100k 81 (61), fisheye 87 (99); 1M 220 (204), fisheye 223 (336);
-//                200k large 211 (185)
-//   7500         100k 102 (76); 1M 282 (270), fisheye 249 (322), rolling 391 (421);
-//                3M rolling 498 (532); 200k large 266 (226)
-//   8160         100k 116 (83); 1M 306 (260), rolling 445 (425), fisheye 293 (273) and,
-//                from three other eyes, 240 to 270 (289 to 331)
-//   16320        two 1M views 556 to 584 (481 to 489)
-//   32400        1M 897 (671), fisheye 770 (602), rolling 1200 (1035)
-// So lists below 2048 tiles, pairs from 10000 on, and between lists from
-// tiles / 150 particles a tile on.
-static int quads_per_wave(int64_t tiles, int64_t entries) {
-  return tiles < 2048 || (tiles < 10000 && 150 * entries >= tiles * tiles) ? 1 : 2;
 }
 
 gut_status launch_render(const DevCam& cam, const Thresholds& th, int n, int cam_idx,
