@@ -71,6 +71,48 @@ struct BwPixel {
   uint32_t last;
 };
 
+__device__ __forceinline__ bool finite3(const float (&x)[3]) {
+  return fabsf(x[0]) < INFINITY && fabsf(x[1]) < INFINITY && fabsf(x[2]) < INFINITY;
+}
+
+// A pixel's terms of one entry: the closest point q, c q, the factor of rho in
+// dL/dsigma and the weight of the loss gradient in dL/dc.
+struct BwTerms {
+  float3 q, cq;
+  float s, w;
+};
+
+// Blends the entry (colour cold) on a pixel it hits, and its terms, zero but for
+// q on a pixel that is not hit.
+template <bool RS, bool GEN>
+__device__ __forceinline__ void bwd_terms(const PairRegs<RS>& r, const float4* P, const double (&cold)[3],
+                                          const Thresholds& th, bool hit, Eval& ev, BwPixel& p, BwTerms& o) {
+  eval_alpha<RS, GEN>(r, th, &ev);
+  const float Tb = p.T;
+  const float ae = hit ? ev.a : 0.0f;
+  o.w = ae * Tb;
+  p.T = fmaf(-ae, Tb, Tb);  // the forward's update, bit for bit
+  // D = gC . c_j; after this entry Z = sum_c gC_c (C_c - C_<=j,c)
+  const double D = fma((double)p.gC[0], cold[0], fma((double)p.gC[1], cold[1], (double)p.gC[2] * cold[2]));
+  p.Z = fma(-(double)o.w, D, p.Z);
+  // dL/dalpha = T_j gC.c_j - (gC.(C - C_<=j) + gT T_N) / (1 - alpha_j)
+  const float inv1m = __builtin_amdgcn_rcpf(1.0f - ev.a);
+  float gA = fmaf(Tb, (float)D, -inv1m * ((float)p.Z + p.gTT));
+  const bool geo = hit && !ev.clamped;  // alpha = alpha_max carries no gradient
+  gA = geo ? gA : 0.0f;
+  // 2 dL/domega^2; a degree-n response scales d alpha / d omega^2 by
+  // 2 lambda (n/2) (omega^2)^(n/2 - 1) relative to the Gaussian's
+  // (0 for a lane that is not hit, whose omega may be infinite)
+  float c = -ev.a * gA;
+  if (GEN) c = geo ? c * __builtin_amdgcn_exp2f(fmaf(th.k_h - 1.0f, ev.lq, th.k_f)) : 0.0f;
+  float3 dg, cr;
+  pair_vectors<RS>(P, ev, p.u, p.v, &dg, &cr);
+  const float3 q = cross3f_fma(dg, cr);
+  o.q = f3(q.x * ev.idd, q.y * ev.idd, q.z * ev.idd);
+  o.cq = f3(c * o.q.x, c * o.q.y, c * o.q.z);
+  o.s = gA * (ev.araw * __builtin_amdgcn_exp2f(-r.lsig));  // rho = (sigma rho) / sigma
+}
+
 // One step: each lane's own list entry (at list position idx) against its
 // pixel: the pixel's terms of the entry's sums, G = sum c p p^T (symmetric,
 // 6), h = sum c p (3), dL/dsigma, dL/dc (3), zero where it is not hit.
@@ -87,44 +129,27 @@ __device__ __forceinline__ bool bwd_step(const PairRegs<RS>& r, const float4* P,
   const bool hit = on && in;
   double cold[3];
   pair_colour<RS>(P, cold);
-  eval_alpha<RS, GEN>(r, th, &ev);
-  const float Tb = p.T;
-  const float ae = hit ? ev.a : 0.0f;
-  const float wgt = ae * Tb;
-  p.T = fmaf(-ae, Tb, Tb);  // the forward's update, bit for bit
-  // D = gC . c_j; after this entry Z = sum_c gC_c (C_c - C_<=j,c)
-  const double D = fma((double)p.gC[0], cold[0], fma((double)p.gC[1], cold[1], (double)p.gC[2] * cold[2]));
-  p.Z = fma(-(double)wgt, D, p.Z);
-  // dL/dalpha = T_j gC.c_j - (gC.(C - C_<=j) + gT T_N) / (1 - alpha_j)
-  const float inv1m = __builtin_amdgcn_rcpf(1.0f - ev.a);
-  float gA = fmaf(Tb, (float)D, -inv1m * ((float)p.Z + p.gTT));
-  const bool geo = hit && !ev.clamped;  // alpha = alpha_max carries no gradient
-  gA = geo ? gA : 0.0f;
-  // 2 dL/domega^2; a degree-n response scales d alpha / d omega^2 by
-  // 2 lambda (n/2) (omega^2)^(n/2 - 1) relative to the Gaussian's
-  // (0 for a lane that is not hit, whose omega may be infinite)
-  float c = -ev.a * gA;
-  if (GEN) c = geo ? c * __builtin_amdgcn_exp2f(fmaf(th.k_h - 1.0f, ev.lq, th.k_f)) : 0.0f;
-  float3 dg, cr;
-  pair_vectors<RS>(P, ev, p.u, p.v, &dg, &cr);
-  float3 q = cross3f_fma(dg, cr);
-  q = f3(q.x * ev.idd, q.y * ev.idd, q.z * ev.idd);
-  const float3 cq = f3(c * q.x, c * q.y, c * q.z);
-  g[0] = cq.x * q.x;
-  g[1] = cq.x * q.y;
-  g[2] = cq.x * q.z;
-  g[3] = cq.y * q.y;
-  g[4] = cq.y * q.z;
-  g[5] = cq.z * q.z;
-  g[6] = cq.x;
-  g[7] = cq.y;
-  g[8] = cq.z;
-  g[9] = gA * (ev.araw * __builtin_amdgcn_exp2f(-r.lsig));  // rho = (sigma rho) / sigma
-  g[10] = wgt * p.gC[0];
-  g[11] = wgt * p.gC[1];
-  g[12] = wgt * p.gC[2];
-  if (odd) {  // an infinite or NaN gradient does not reach entries its pixel does not blend
-    asm volatile("");  // (kept a branch: as selects these take 0.8% of a training step)
+  BwTerms o;
+  bwd_terms<RS, GEN>(r, P, cold, th, hit, ev, p, o);
+  g[0] = o.cq.x * o.q.x;
+  g[1] = o.cq.x * o.q.y;
+  g[2] = o.cq.x * o.q.z;
+  g[3] = o.cq.y * o.q.y;
+  g[4] = o.cq.y * o.q.z;
+  g[5] = o.cq.z * o.q.z;
+  g[6] = o.cq.x;
+  g[7] = o.cq.y;
+  g[8] = o.cq.z;
+  g[9] = o.s;
+  g[10] = o.w * p.gC[0];
+  g[11] = o.w * p.gC[1];
+  g[12] = o.w * p.gC[2];
+  // An infinite or NaN gradient does not reach entries its pixel does not blend.
+  // (As selects in every step this takes 0.8% of a 1M fisheye training step,
+  // behind a branch nothing; of a rolling one, whose longest tiles wait for each
+  // step, the branch takes 1% and selects 0.3%.)
+  if (RS || odd) {
+    if (!RS) asm volatile("");  // (kept a branch)
     g[10] = hit ? g[10] : 0.0f;
     g[11] = hit ? g[11] : 0.0f;
     g[12] = hit ? g[12] : 0.0f;
@@ -162,7 +187,7 @@ __device__ inline void bwd_flush(double* rows, const uint32_t* pe, int m, int n,
   }
 }
 
-// The forward's blocks, pixels, pair setup and lists.  A step sums its pixels'
+// The forward's blocks, pixels, pair setup and lists (NQ = 1).  A step sums its pixels'
 // terms over each row of lanes (up to four different pairs at once) and adds
 // the rows' totals to the pairs' rows in LDS, in FP64; a row goes to the
 // per-particle sums when its batch is done, one atomic per value and (tile,
@@ -225,7 +250,7 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
       p.Z = fma((double)p.gC[c], (double)out_rgb[3 * pix + c], p.Z);
     }
   }
-  const bool odd = wave_any(!(fabsf(p.gC[0]) < INFINITY && fabsf(p.gC[1]) < INFINITY && fabsf(p.gC[2]) < INFINITY));
+  const bool odd = wave_any(!finite3(p.gC));
   atomicMax(&maxlast_s, p.last);
   __syncthreads();  // (also publishes wb)
   const uint2 rg = ranges[cam.tile_base + tile];
@@ -278,6 +303,170 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
   }
   __syncthreads();
   bwd_flush(rows, pe[par], m, n, cam_idx, acc, acc_rgb);
+}
+
+// The same by pairs: 128 threads, a wave for two quadrants and a thread for a
+// pixel of either, as the forward's pair walk.  A step takes one pair against
+// both pixels of each lane, whose terms are added before the sum over each row
+// of lanes (so 32 pixels are summed in FP32); the rows' totals are added in
+// FP64 and go to the per-particle sums, one atomic per value and (wave,
+// particle).  See bwd_by_pairs for where this wins.
+constexpr int kBpThreads = 128, kBpBatch = 128;
+
+// x summed over the wave's four rows of 16 lanes, in every row.
+__device__ __forceinline__ double rows_sum(double x) {
+  uint32_t lo = (uint32_t)__double2loint(x), hi = (uint32_t)__double2hiint(x);
+  auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  x = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  lo = (uint32_t)__double2loint(x);
+  hi = (uint32_t)__double2hiint(x);
+  l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+
+template <bool RS, bool GEN, bool CLIP>
+__global__ void __launch_bounds__(kBpThreads, 3) render_bwd_pairs_kernel(
+    DevCam cam, Thresholds th, int n, int cam_idx, const uint2* __restrict__ ranges,
+    const uint32_t* __restrict__ order, const uint32_t* __restrict__ ids,
+    const float4* __restrict__ record, const float* __restrict__ clip,
+    const float* __restrict__ rgb, const float* __restrict__ out_rgb,
+    const float* __restrict__ out_T, const uint32_t* __restrict__ out_nc,
+    const float* __restrict__ d_rgb, const float* __restrict__ d_T, double* __restrict__ acc,
+    double* __restrict__ acc_rgb) {
+  constexpr int S = Slots<RS, true>::N;
+  __shared__ float4 pd[kBpBatch * S];
+  __shared__ uint32_t pe[kBpBatch];
+  __shared__ unsigned short pf[kBpBatch];
+  __shared__ TileFrameD F;
+  __shared__ QuadBoxes wb;
+  __shared__ float red[6];
+  __shared__ uint32_t maxlast_s;
+
+  const int tile = (int)order[cam.tile_base + blockIdx.x];  // longest lists first
+  const int tx = tile % cam.tiles_x, ty = tile / cam.tiles_x;
+  const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  int px, py0;  // the thread's first pixel; its second lies 8 rows below
+  lane_pixel(wv, lane, &px, &py0);
+  px += tx * kTile;
+  py0 += ty * kTile;
+  if (t == 0) { tile_frame(cam, tx, ty, &F); maxlast_s = 0; }
+  __syncthreads();
+
+  bool active[2];
+  float u[2], v[2], dt[2];
+#pragma unroll
+  for (int k = 0; k < 2; k++) {
+    u[k] = v[k] = dt[k] = 0.0f;
+    active[k] = px < cam.W && py0 + 8 * k < cam.H && pixel_ray(cam, F, px, py0 + 8 * k, &u[k], &v[k], &dt[k]);
+  }
+  float umax, vmax, dtmax;
+  tile_bounds<2>(u, v, dt, active, red, &umax, &vmax, &dtmax);
+  const float l2amin = log2f(th.alpha_min);
+  BwPixel p[2];
+  bool odd = false;
+#pragma unroll
+  for (int k = 0; k < 2; k++) {
+    (void)block_box(u[k], v[k], active[k], 0.0f, wv + 2 * k, &wb);
+    p[k] = BwPixel{u[k], v[k], dt[k], 1.0f, 0.0f, 1.0f, {0.0f, 0.0f, 0.0f}, 0.0f, 0.0, 0u};
+    const long long pix = cam.pixel_base + (long long)(py0 + 8 * k) * cam.W + px;
+    if (CLIP) {  // the forward's clip test operands
+      if (active[k]) {
+        p[k].clip = clip[pix];
+        p[k].dlen = sqrtf(fmaf(u[k], u[k], fmaf(v[k], v[k], 1.0f)));
+      }
+      quad_clip_max(p[k].clip, active[k], wv + 2 * k, &wb);
+    }
+    if (active[k]) {
+      p[k].last = out_nc[pix];
+      p[k].gTT = (d_T ? d_T[pix] : 0.0f) * out_T[pix];
+      for (int c = 0; c < 3; c++) {
+        p[k].gC[c] = d_rgb[3 * pix + c];
+        p[k].Z = fma((double)p[k].gC[c], (double)out_rgb[3 * pix + c], p[k].Z);
+      }
+    }
+    odd = odd || wave_any(!finite3(p[k].gC));
+  }
+  atomicMax(&maxlast_s, max(p[0].last, p[1].last));
+  __syncthreads();  // (also publishes wb)
+  const uint2 rg = ranges[cam.tile_base + tile];
+  // never past the tile's list
+  const uint32_t maxlast = __builtin_amdgcn_readfirstlane(min(maxlast_s, rg.y - rg.x));
+  if (maxlast >= 2048) __builtin_amdgcn_s_setprio(3);
+  else if (maxlast >= 1024) __builtin_amdgcn_s_setprio(2);
+  else if (maxlast >= 256) __builtin_amdgcn_s_setprio(1);
+
+  for (uint32_t b = 0; b < maxlast; b += kBpBatch) {
+    if (b) __syncthreads();
+    uint32_t fl = 0u;
+    if (b + t < maxlast) {
+      const uint32_t e = ids[rg.x + b + t];
+      pe[t] = e;
+      fl = pair_setup<RS, true, GEN, CLIP>(record, rgb, e, (int)(e - (uint32_t)cam_idx * (uint32_t)n), F, cam, umax,
+                                           vmax, dtmax, th, l2amin, wb, &pd[t * S]);
+    }
+    pf[t] = (unsigned short)fl;
+    __syncthreads();
+#pragma unroll 1
+    for (int h = 0; h < 2; h++) {
+      // the pairs that the forward walked for the wave's quadrants
+      const uint32_t f = pf[lane + 64 * h];
+      unsigned long long m = __builtin_amdgcn_ballot_w64((f >> wv & 5u) != 0u);
+      const unsigned long long xm = __builtin_amdgcn_ballot_w64((f & kMixedBit) != 0u);
+      while (m) {
+        const uint32_t ql = (uint32_t)__builtin_ctzll(m), q = 64u * h + ql, idx = b + q;
+        m &= m - 1ull;
+        if (!wave_any(idx < p[0].last || idx < p[1].last)) break;
+        const float4* P = &pd[q * S];
+        PairRegs<RS> r;
+        load_pair<RS>(P, r);
+        r.flag = -1.0f;  // (mixed is this pair's own)
+        const uint32_t mixed = __builtin_amdgcn_readfirstlane((uint32_t)(xm >> ql) & 1u);
+        Eval ev[2];
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+          eval_test<RS>(r, P, p[k].u, p[k].v, p[k].dt, mixed != 0u, &ev[k]);
+          if (CLIP) clip_test<RS>(r, P, p[k].u, p[k].v, p[k].dt, p[k].dlen, p[k].clip, &ev[k]);
+        }
+        const bool hit0 = eval_hit<RS>(r, ev[0]) && idx < p[0].last;
+        const bool hit1 = eval_hit<RS>(r, ev[1]) && idx < p[1].last;
+        if (!wave_any(hit0 || hit1)) continue;
+        double cold[3];
+        pair_colour<RS>(P, cold);
+        BwTerms o[2];
+        bwd_terms<RS, GEN>(r, P, cold, th, hit0, ev[0], p[0], o[0]);
+        bwd_terms<RS, GEN>(r, P, cold, th, hit1, ev[1], p[1], o[1]);
+        float g[16];
+        g[0] = fmaf(o[0].cq.x, o[0].q.x, o[1].cq.x * o[1].q.x);
+        g[1] = fmaf(o[0].cq.x, o[0].q.y, o[1].cq.x * o[1].q.y);
+        g[2] = fmaf(o[0].cq.x, o[0].q.z, o[1].cq.x * o[1].q.z);
+        g[3] = fmaf(o[0].cq.y, o[0].q.y, o[1].cq.y * o[1].q.y);
+        g[4] = fmaf(o[0].cq.y, o[0].q.z, o[1].cq.y * o[1].q.z);
+        g[5] = fmaf(o[0].cq.z, o[0].q.z, o[1].cq.z * o[1].q.z);
+        g[6] = o[0].cq.x + o[1].cq.x;
+        g[7] = o[0].cq.y + o[1].cq.y;
+        g[8] = o[0].cq.z + o[1].cq.z;
+        g[9] = o[0].s + o[1].s;
+#pragma unroll
+        for (int c = 0; c < 3; c++) g[10 + c] = fmaf(o[0].w, p[0].gC[c], o[1].w * p[1].gC[c]);
+        if (odd) {  // as in bwd_step
+          asm volatile("");
+#pragma unroll
+          for (int c = 0; c < 3; c++)
+            g[10 + c] = (hit0 ? o[0].w * p[0].gC[c] : 0.0f) + (hit1 ? o[1].w * p[1].gC[c] : 0.0f);
+        }
+        g[13] = g[14] = g[15] = 0.0f;
+        const double tot = rows_sum((double)row_reduce16(g, lane));
+        if (lane < kRow && tot != 0.0) {
+          const uint32_t e = pe[q];
+          const long long i = (long long)(e - (uint32_t)cam_idx * (uint32_t)n);
+          if (lane < kAcc) atomicAdd(&acc[i * kAcc + lane], tot);
+          else atomicAdd(&acc_rgb[3 * (long long)e + (lane - kAcc)], tot);
+        }
+      }
+    }
+  }
 }
 
 // Backward of the k-buffer render ("Ours (sorted)", Sec. 4.3).  It replays
@@ -758,6 +947,24 @@ extern "C" size_t gut_render_bwd_workspace_bytes(int64_t n, int32_t n_cams) {
   return a + (size_t)n * n_cams * 3 * 8 + 256;
 }
 
+// Whether the tile-order backward of a camera of this many tiles takes pairs
+// (128 threads, two pixels a thread) or lists.  Lists reach fewer pixels in
+// vain and spread a tile's walk over twice the waves; pairs sum twice the pixels
+// in a step, which wins where few small particles lie on a tile: each then
+// covers its quadrants, or the launch's fixed work a tile counts most.  us a
+// backward, lists (pairs); "large" are particles of several quadrants:
+//   1200 tiles   2k large 132 (157), 100k 113 (245)
+//   2560         2k large 220 (218), rolling 121 (145)
+//   3600         2k large 283 (273), rolling 161 (148); 20k large 338 (314),
+//                rolling 181 (196); 100k 157 (164), rolling 163 (364)
+//   7500         20k large 608 (527); 100k 257 (250), rolling 246 (293)
+//   8160         20k large 647 (577), rolling 342 (308); 100k 286 (262), rolling
+//                269 (270); 1M 894 (937), fisheye 819 (941), rolling 881 (1014)
+//   14400        100k 442 (373); 1M 1348 (1319), fisheye 1131 (1232)
+//   32400        200k large 2397 (2032); 1M 2573 (2342), fisheye 1979 (1982)
+// So lists below 3072 tiles and from tiles / 1000 particles a tile on.
+static bool bwd_by_pairs(int64_t tiles, int64_t n) { return tiles >= 3072 && 1000 * n < tiles * tiles; }
+
 // The whole backward with its FP64 accumulators in ws (ws_bytes available):
 // argument checks, then every launch on `stream`.
 static gut_status render_bwd_run(const gut_scene* scene, const gut_projected* proj,
@@ -821,11 +1028,17 @@ static gut_status render_bwd_run(const gut_scene* scene, const gut_projected* pr
     GUT_LAUNCH_CHECK();
   }
   for (int c = 0; c < n_cams && p->kbuffer == 0; c++) {
-    dim3 grid(dc[c].tiles_x * dc[c].tiles_y), block(kBwThreads);
-#define GUT_RBW(RS, GEN, CLIP)                                                                      \
-  render_bwd_kernel<RS, GEN, CLIP><<<grid, block, 0, s>>>(                                           \
+    dim3 grid(dc[c].tiles_x * dc[c].tiles_y);
+    const bool pairs = bwd_by_pairs(grid.x, n);
+#define GUT_RBWK(K, NT, RS, GEN, CLIP)                                                               \
+  K<RS, GEN, CLIP><<<grid, NT, 0, s>>>(                                                              \
       dc[c], th, (int)n, c, (const uint2*)tile_ranges, order, sorted_ids,                         \
       (const float4*)proj->record, clip_depth, proj->rgb, rgb, T_final, n_contrib, d_rgb, d_T, acc, acc_rgb)
+#define GUT_RBW(RS, GEN, CLIP)                                                            \
+  do {                                                                                    \
+    if (pairs) GUT_RBWK(render_bwd_pairs_kernel, kBpThreads, RS, GEN, CLIP);              \
+    else GUT_RBWK(render_bwd_kernel, kBwThreads, RS, GEN, CLIP);                          \
+  } while (0)
 #define GUT_RBW1(RS, GEN) \
   if (clip_depth) GUT_RBW(RS, GEN, true); else GUT_RBW(RS, GEN, false)
     const bool gen = th.kdeg != 2;
@@ -833,6 +1046,7 @@ static gut_status render_bwd_run(const gut_scene* scene, const gut_projected* pr
     else { if (gen) { GUT_RBW1(false, true); } else { GUT_RBW1(false, false); } }
 #undef GUT_RBW1
 #undef GUT_RBW
+#undef GUT_RBWK
     GUT_LAUNCH_CHECK();
   }
   dim3 g1((unsigned)((n + 255) / 256)), b1(256);
