@@ -378,13 +378,18 @@ __device__ __forceinline__ void load_pair(const float4* P, PairRegs<RS>& r) {
   }
 }
 
+// Discards the hit where no is set: cc = +inf against |d_g|^2 = 1, so that
+// eval_hit stays one bare compare, whatever |d_g|^2 was (a ballot of a combined
+// lane flag goes through a vector register, two instructions more).
+__device__ __forceinline__ void reject(bool no, Eval* o) {
+  o->cc = no ? INFINITY : o->cc;
+  o->dd = no ? 1.0f : o->dd;
+}
+
 // Stage 1 of the response on one pixel ray (Eq. 11): omega'^2 |d_g|^2 and
 // |d_g|^2, for eval_hit's test omega'^2 <= Kp (<=> alpha >= alpha_min)
 // without any transcendental (mixed: the chunk holds pairs whose tau_max sign
-// varies over the tile).  Where the tau_max > 0 test (and clip_test's
-// clip) discards the hit it sets cc to +inf, so that eval_hit stays one
-// bare compare: a ballot of a combined lane flag goes through a vector
-// register, two instructions more.
+// varies over the tile: their hits behind the camera are discarded here).
 template <bool RS>
 __device__ __forceinline__ void eval_test(const PairRegs<RS>& r, const float4* P, float u, float v,
                                           float dt, bool mixed, Eval* o) {
@@ -398,7 +403,7 @@ __device__ __forceinline__ void eval_test(const PairRegs<RS>& r, const float4* P
     if (mixed) {  // rare, and uniform across the wave
       const float4 p5 = P[5];
       const float sg = fmaf(v, p5.z, fmaf(u, p5.y, p5.x));
-      o->cc = sg < 0.0f || !__builtin_signbitf(r.flag) ? o->cc : INFINITY;
+      reject(!(sg < 0.0f || !__builtin_signbitf(r.flag)), o);
     }
   } else {
     float3 dg = f3(fmaf(v, r.p2.x, fmaf(u, r.p1.x, r.p0.x)), fmaf(v, r.p2.y, fmaf(u, r.p1.y, r.p0.y)),
@@ -413,7 +418,7 @@ __device__ __forceinline__ void eval_test(const PairRegs<RS>& r, const float4* P
     if (mixed) {
       float sg = fmaf(v, r.p4.w, fmaf(u, r.p3.w, r.p5.w));
       sg = fmaf(dt, fmaf(v, r.p9.w, fmaf(u, r.p8.w, r.p7.w)), sg);
-      o->cc = sg < 0.0f || !__builtin_signbitf(r.flag) ? o->cc : INFINITY;
+      reject(!(sg < 0.0f || !__builtin_signbitf(r.flag)), o);
     }
     o->dg = dg;
     o->cr = cr;
@@ -464,7 +469,7 @@ __device__ __forceinline__ void clip_test(const PairRegs<RS>& r, const float4* P
     odg = fmaf(v, r.p4.w, fmaf(u, r.p3.w, r.p5.w));
     odg = fmaf(dt, fmaf(v, r.p9.w, fmaf(u, r.p8.w, r.p7.w)), odg);
   }
-  o->cc = -odg * dlen > clip * o->dd ? INFINITY : o->cc;
+  reject(-odg * dlen > clip * o->dd, o);
 }
 
 // Colour of a pair (FP64 slots).
