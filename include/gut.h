@@ -166,10 +166,11 @@ gut_status gut_project(const gut_scene* scene, const gut_camera* cams, int32_t n
 
 /* Workspace for gut_bin (bytes, 256-aligned base expected) for n particles
  * seen by the n_cams cameras (host array) and pair_capacity pairs: a count
- * matrix of ceil(n / 8192) rows or more (at most 512) by the cameras' total tile
- * count (u32), 4 KiB, 4 bytes per tile and 16 bytes per pair.  gut_bin also takes
- * a workspace of ceil(n / 8192) rows and is then slower for small n.  0 on bad
- * arguments. */
+ * matrix (u32) of the cameras' total tile count by ceil(n / 8192) rows, or more
+ * for small n (up to 512 over the call's cameras), 4 KiB, 4 bytes per tile and 16
+ * bytes per pair.  gut_bin also takes a workspace of ceil(n / 8192) rows and is then
+ * slower for small n.  Ask here rather than reckon: the rows for small n may
+ * change.  0 on bad arguments. */
 size_t gut_bin_workspace_bytes(int64_t n, const gut_camera* cams, int32_t n_cams, int64_t pair_capacity);
 
 /* Global per-tile depth sort (Sec. 4.3): each tile's list holds the visible

@@ -45,8 +45,9 @@ constexpr int kRBatch = 256 / NQ;
 // Waves per SIMD asked for.  Global shutter, NQ = 2: five (96 VGPRs; the FP64
 // pair setup keeps a few values in scratch), two 1M 1920x1080 views 0.956 ms a
 // forward against 0.988 with four.  NQ = 1: four blocks of 32 KB are all the
-// LDS holds, and with the registers of four waves (122) nothing spills: 1M
-// 1280x720 with clip 0.461 against 0.488 ms with five and 0.482 with three.
+// LDS holds, and with the registers of four waves nothing spills (122), with
+// clip distances 4 (128): 1M 1280x720 with clip 0.461 against 0.488 ms with five
+// and 0.482 with three.
 // Rolling shutter: three (167; with four 3M 1600x1200 takes 1.171 against
 // 1.092 ms, 132 bytes a lane in scratch).
 template <bool RS, int NQ>
@@ -494,12 +495,17 @@ gut_status render_batch_launch(const DevCam* d_cams, const DevCam* h_cams, int n
 // (a buffer usually turns over within a batch), else through the list.
 constexpr int kKBuf = 16;
 constexpr int kKThreads = 256;
-// Four waves per SIMD (128 VGPRs, some of the buffer in scratch): the walk
-// waits on LDS and on the colour fetches of evicted hits, and a fourth wave
-// hides more of that than the spills cost.  (Keeping the hits' payloads in an
-// LDS table instead, so that only 32-bit keys move, cuts the VALU work of an
-// insertion by two thirds but takes so much LDS that two waves per SIMD fit,
-// and is slower.)
+// Four waves per SIMD are asked for.  Global shutter: 128 VGPRs, some of the
+// buffer in scratch; the walk waits on LDS and on the colour fetches of evicted
+// hits, and a fourth wave hides more of that than the spills cost.  (Keeping the
+// hits' payloads in an LDS table instead, so that only 32-bit keys move, cuts the
+// VALU work of an insertion by two thirds but takes so much LDS that two waves per
+// SIMD fit, and is slower.)  Rolling shutter: a block's pairs take 59 KB of LDS
+// in all, two blocks a CU, so the compiler, which cannot meet the bound, spends
+// two waves' registers (219 to 251) and spills nothing.  That is the best there: 300k
+// 1280x720 0.38 ms a render, against 0.77 with batches of 128 pairs (34 KB) and
+// four waves (117 values spilled), 0.47 with those and three, and 0.41 where two
+// waves are asked for outright (the same registers, another schedule).
 
 // Colours of the hits at list positions [wlo, wlo + kKWin) (the two latest
 // batches) are kept in LDS, row pos mod kKWin; an older hit's colour is read

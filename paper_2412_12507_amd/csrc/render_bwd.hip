@@ -19,7 +19,9 @@
 // plus dL/dsigma and dL/dc are summed over the pixels of a 4 x 4 block in FP32
 // (one reduce-scatter for all 13), over the tile in FP64 in LDS, and over the
 // tiles by one FP64 atomic per value and (tile, particle), so the
-// per-particle totals carry no order-dependent FP32 rounding.
+// per-particle totals carry no order-dependent FP32 rounding.  (By pairs: over two
+// such blocks in FP32, over the half tile in FP64, one atomic per value and
+// (half tile, particle).)
 //
 // K7 (per particle) then applies M = S^-1 R^T:
 //   dL/ds_k = -G_kk / s_k,   dL/dR = R S G S^-1,   dL/dmu = -R S^-1 h,

@@ -24,13 +24,20 @@ namespace gut {
 
 constexpr size_t kStage = 64 * 1024;
 
+// Blocks of entries per camera: as few as gut_bin takes.  A batch is admitted
+// by the memory it may need, and the count matrix is as long as its blocks are
+// many; with the blocks of a call of its own (bin_blocks) 8 views of 1920x1080 of
+// a small scene would reserve 17 MB for it instead of 1 to 6, and the binning of
+// one batch runs beside the render of another.
+static int64_t batch_bin_blocks(int64_t n) { return bin_blocks_min(n); }
+
 // Device memory one batch needs before its pair count is known: the
 // projection (rect, tiles, depth, rgb, mean, extent ellipse), the count
 // phase's workspace, ranges and render order, and the launch tables.
 static size_t batch_entry_bytes(int64_t n, int n_cams, int64_t T) {
   const int64_t E = n * (int64_t)n_cams;
   return al256(E * 8) + al256(E * 4) * 2 + al256(E * 12) + al256(E * 8) + al256(E * 16) +
-         al256(bin_count_bytes(bin_blocks_min(n), T)) + al256(T * 12) + al256(n_cams * sizeof(DevCam)) +
+         al256(bin_count_bytes(batch_bin_blocks(n), T)) + al256(T * 12) + al256(n_cams * sizeof(DevCam)) +
          al256(n_cams * sizeof(float*)) + al256(2 * (2 * kMaxCams + 1) * sizeof(int)) +
          al256(16 * sizeof(unsigned)) + 4096;
 }
@@ -92,7 +99,7 @@ class HipBackend {
     m.proj.mean2d = (float*)take(E * 8);
     m.proj.extent = (float*)take(E * 16);
     m.proj.record = (float*)(base + record_off);
-    m.cws = take(bin_count_bytes(bin_blocks_min(scene.n), T));
+    m.cws = take(bin_count_bytes(batch_bin_blocks(scene.n), T));
     m.ranges = (uint32_t*)take(T * 12);
     m.d_cams = (DevCam*)take(nc * sizeof(DevCam));
     m.d_outs = (float**)take(nc * sizeof(float*));
@@ -119,8 +126,8 @@ class HipBackend {
     if ((st = project_launch(&scene, W.dc.data(), nc, make_ut(params), make_thresholds(params), &m.proj,
                              false, s)) != GUT_OK)
       return st;
-    if ((st = bin_count_launch(&m.proj, (int)scene.n, bin_blocks_min(scene.n), W.dc.data(), nc, W.T, params.tile_cull != 0, m.cws,
-                               m.ranges, s)) != GUT_OK)
+    if ((st = bin_count_launch(&m.proj, (int)scene.n, batch_bin_blocks(scene.n), W.dc.data(), nc, W.T,
+                               params.tile_cull != 0, m.cws, m.ranges, s)) != GUT_OK)
       return st;
     return bin_count_wait(P);
   }
@@ -136,8 +143,8 @@ class HipBackend {
     char* pws = pb + al256((P > 0 ? P : 1) * 4);
     int* h_lists = (int*)((char*)W.pinned + 49152);
     gut_status st;
-    if ((st = bin_sort_launch(&m.proj, (int)scene.n, bin_blocks_min(scene.n), W.dc.data(), nc, W.T, params.tile_cull != 0, m.cws,
-                              (int64_t)P, pws, m.ranges, ids, s)) != GUT_OK ||
+    if ((st = bin_sort_launch(&m.proj, (int)scene.n, batch_bin_blocks(scene.n), W.dc.data(), nc, W.T,
+                              params.tile_cull != 0, m.cws, (int64_t)P, pws, m.ranges, ids, s)) != GUT_OK ||
         (st = render_batch_launch(m.d_cams, W.dc.data(), nc, make_thresholds(params), (int)scene.n, m.ranges,
                                   m.ranges + 2 * W.T, ids, m.proj.record, m.proj.rgb, m.d_outs,
                                   m.d_counters, m.d_lists, h_lists, n_blocks, s)) != GUT_OK)
