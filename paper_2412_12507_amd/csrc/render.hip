@@ -149,8 +149,8 @@ struct TileSmem {
 };
 // Global shutter, NQ = 2: ten blocks of two waves a CU are the five waves a
 // SIMD asked for; LDS is dealt in units of 1280 bytes.  (With 15840 bytes, nine
-// blocks: two 1M 1920x1080 views 521 against 495 us, one 3840x2160 735
-// against 692.)
+// blocks, renders took 5% longer: two 1M 1920x1080 views 521 against 495 us, one
+// 3840x2160 735 against 692.)
 static_assert(10 * ((sizeof(TileSmem<false, 2>) + 1279) / 1280) * 1280 <= 160 * 1024, "ten blocks a CU");
 
 // One tile of one camera.  out_* are indexed by pix_base + y * W + x.  GEN:
@@ -261,7 +261,7 @@ __device__ __forceinline__ void render_tile(
         p[0].last = last != (uint32_t)kChunk ? b + c + last + 1 : p[0].last;
       }
     } else {
-      const bool run0 = wave_any(p[0].u == p[0].u), run1 = wave_any(p[NQ - 1].u == p[NQ - 1].u);
+      bool run0 = wave_any(p[0].u == p[0].u), run1 = wave_any(p[NQ - 1].u == p[NQ - 1].u);
 #pragma unroll 1
       for (int h = 0; h < 2; h++) {
         // the batch's pairs that may reach alpha_min somewhere in the wave's quadrants
@@ -284,12 +284,14 @@ __device__ __forceinline__ void render_tile(
           }
           if ((ma >> ql) & 1ull)
             if (pair_step<RS, NE, GEN, CLIP>(r, P, idx1, mixed, th, p[0]) && !wave_any(p[0].u == p[0].u)) {
+              run0 = false;  // (nor does it walk the batch's other half)
               ma = 0ull;
               m &= mb;
             }
           if ((mb >> ql) & 1ull)
             if (pair_step<RS, NE, GEN, CLIP>(r, P, idx1, mixed, th, p[NQ - 1]) &&
                 !wave_any(p[NQ - 1].u == p[NQ - 1].u)) {
+              run1 = false;
               mb = 0ull;
               m &= ma;
             }
@@ -318,16 +320,16 @@ __device__ __forceinline__ void render_tile(
 // fills the chip evenly, since a pair that covers its quadrants then takes twice
 // the steps.  The host does not know the lists' lengths, so particles a tile
 // stand for them.  us a render, lists against pairs (1 against 2):
-//   1900 tiles   100k clustered 41 (75), 20k large 85 (89), the same rolling 61 (111)
-//   3600         100k 57 (58), fisheye 62 (118), rolling 87 (153); 20k large 130 (112)
-//   5700         100k 81 (61), fisheye 87 (99); 1M 220 (204), fisheye 223 (336);
-//                200k large 211 (185)
-//   7500         100k 102 (76); 1M 282 (270), fisheye 249 (322), rolling 391 (421);
-//                3M rolling 498 (532); 200k large 266 (226)
-//   8160         100k 116 (83); 1M 306 (260), rolling 445 (425), fisheye 293 (273) and,
-//                from three other eyes, 240 to 270 (289 to 331)
-//   16320        two 1M views 556 to 584 (481 to 489)
-//   32400        1M 897 (671), fisheye 770 (602), rolling 1200 (1035)
+//   1900 tiles   100k clustered 41 (75); 20k large 80 (81), rolling 59 (100)
+//   2560         100k 45 (64); 20k large 98 (84), rolling 80 (95)
+//   3600         100k 57 (59), fisheye 63 (119), rolling 91 (152); 20k large 128 (110)
+//   5700         100k 82 (63), fisheye 88 (101); 1M 222 (204), fisheye 226 (340);
+//                200k large 204 (181)
+//   7500         100k 103 (78); 1M 293 (262), fisheye 246 (324), rolling 389 (408);
+//                3M rolling 397 to 462 (577 to 725); 200k large 262 (212)
+//   8160         100k 116 (85); 1M 306 (260), three fisheye views 243 to 262 (279 to 336)
+//   16320        two 1M views 565 to 590 (461); rolling 868 (793)
+//   32400        1M 897 (650), fisheye 770 (586), rolling 1200 (1010)
 // So lists below 2048 tiles, pairs from 10000 on, and between lists from
 // tiles / 150 particles a tile on.
 static int quads_per_wave(int64_t tiles, int64_t entries) {
