@@ -964,8 +964,8 @@ extern "C" size_t gut_render_bwd_workspace_bytes(int64_t n, int32_t n_cams) {
 //                269 (270); 1M 894 (937), fisheye 819 (941), rolling 881 (1014)
 //   14400        100k 442 (373); 1M 1348 (1319), fisheye 1131 (1232)
 //   32400        200k large 2397 (2032); 1M 2573 (2342), fisheye 1979 (1982)
-// So lists below 3072 tiles and from tiles / 1000 particles a tile on.
-static bool bwd_by_pairs(int64_t tiles, int64_t n) { return tiles >= 3072 && 1000 * n < tiles * tiles; }
+// So lists below 3072 tiles and from tiles / 650 particles a tile on.
+static bool bwd_by_pairs(int64_t tiles, int64_t n) { return tiles >= 3072 && 650 * n < tiles * tiles; }
 
 // The whole backward with its FP64 accumulators in ws (ws_bytes available):
 // argument checks, then every launch on `stream`.

@@ -1,5 +1,5 @@
 """The tile-order backward by pairs (3072 tiles and more with fewer than
-tiles / 1000 particles a tile) and by lists.
+tiles / 650 particles a tile) and by lists.
 
 - By pairs against the FP64 oracle on sampled tiles, at the gradients' usual
   bound: pinhole, fisheye and rolling shutter, both responses, with clip
@@ -36,7 +36,7 @@ def setup(kind, clip=False):
         if kind == "rolling":
             cam = G.with_motion(cam, 0.1, 0.3)
     cl = np.random.default_rng(4600).uniform(6.0, 11.0, (H, W)).astype(np.float32) if clip else None
-    assert R.num_tiles([cam]) == TILES and 1000 * N < TILES * TILES
+    assert R.num_tiles([cam]) == TILES and 650 * N < TILES * TILES
     return scene, cam, cl
 
 
@@ -67,11 +67,11 @@ def test_pairs_against_lists(kind, degree, clip):
     d_rgb = torch.randn(W * H, 3, generator=gen, device="cuda")
     d_T = torch.randn(W * H, generator=gen, device="cuda")
     g = []
-    for sc in (scene, padded(scene, 8000)):
+    for sc in (scene, padded(scene, 16000)):
         gs = R.GaussianScene.from_host(sc)
         proj, bins, img = R.forward(gs, [cam], p, clip=cl)
         g.append(R.render_backward(gs, proj, bins, [cam], img, d_rgb, d_T, p, clip=cl))
-    assert 1000 * (N + 8000) >= TILES * TILES
+    assert 650 * (N + 16000) >= TILES * TILES
     for key, a in g[0].items():
         b = g[1][key]
         assert (b[N:] == 0).all()
