@@ -1,5 +1,5 @@
 """MI355X-native 3DGUT rasterizer: Unscented-Transform projection, tile
-binning by device radix sort, per-tile 3D-response compositing and its
+binning by a counting sort over tiles, per-tile 3D-response compositing and its
 backward, as hand-written HIP kernels for gfx950 behind the C ABI of
 include/gut.h, plus a continuous-batching server.
 
