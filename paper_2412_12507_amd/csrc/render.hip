@@ -173,7 +173,7 @@ __device__ __forceinline__ void render_tile(
   px += tx * kTile;
   py0 += ty * kTile;
   if (t == 0) tile_frame(cam, tx, ty, &F);
-  if (NQ == 1) write_dummies<RS, false>(sm.pd, B);
+  if (NQ == 1) write_dummies<RS>(sm.pd, B);
   const uint2 rg = ranges[cam.tile_base + tile];
   const uint32_t len = __builtin_amdgcn_readfirstlane(rg.y - rg.x);
   __syncthreads();
@@ -613,7 +613,7 @@ __global__ void __launch_bounds__(kKThreads, 4) render_kbuffer_kernel(
   px += tx * kTile;
   py += ty * kTile;
   if (t == 0) tile_frame(cam, tx, ty, &F);
-  write_dummies<RS, false>(pd, kKThreads);
+  write_dummies<RS>(pd, kKThreads);
   __syncthreads();
   const bool inside = px < cam.W && py < cam.H;
   float u = 0.f, v = 0.f, dt = 0.f;

@@ -225,7 +225,11 @@ __global__ void __launch_bounds__(kBwThreads, 3) render_bwd_kernel(
   px += tx * kTile;
   py += ty * kTile;
   if (t == 0) { tile_frame(cam, tx, ty, &F); maxlast_s = 0; }
-  write_dummies<RS, true>(pd, kBwBatch);
+  // the padding's row (written for any number of chunks and threads: with the
+  // bounds as constants the compiler makes the whole kernel 2% slower under a
+  // rolling shutter, 558 against 548 us for 300k particles at 800x600)
+  for (int i = t; i < (kBwBatch + kChunk - 1) / kChunk * S; i += blockDim.x)
+    pd[((i / S + 1) * (kChunk + 1) - 1) * S + i % S] = dummy_slot<RS>(i % S);
   for (int i = t; i < (kBwBatch + 1) * kRow; i += kBwThreads) rows[i] = 0.0;
   __syncthreads();
 
@@ -644,7 +648,8 @@ __global__ void __launch_bounds__(kKThreadsB, 2) render_kbuffer_bwd_kernel(
   px += tx * kTile;
   py += ty * kTile;
   if (t == 0) tile_frame(cam, tx, ty, &F);
-  write_dummies<RS, true>(pd, kKBatchB);
+  static_assert(kKBatchB == kChunk, "one row for the padding");
+  for (int i = t; i < S; i += kKThreadsB) pd[kKBatchB * S + i] = dummy_slot<RS>(i);
   for (int i = t; i < kWin * kRow; i += kKThreadsB) accw[i] = 0.0f;
   __syncthreads();
   const bool inside = px < cam.W && py < cam.H;

@@ -607,16 +607,20 @@ __device__ inline void quad_clip_max(float clip, bool valid, int k, QuadBoxes* w
 constexpr int kChunk = 128;
 __host__ __device__ constexpr int batch_rows(int batch) { return batch + (batch + kChunk - 1) / kChunk; }
 __device__ __forceinline__ int batch_row(int t) { return t + t / kChunk; }
-// omega^2 = 0, |d_g| = 1, Kp = -1, at the rows behind each chunk.
-template <bool RS, bool BWD>
+// Slot t of that row: omega^2 = 0, |d_g| = 1, Kp = -1.
+template <bool RS>
+__device__ __forceinline__ float4 dummy_slot(int t) {
+  return RS ? make_float4(t == 0 ? 1.0f : 0.0f, 0.0f, 0.0f, t == 2 ? -1.0f : 0.0f)
+            : make_float4(0.0f, 0.0f, t == 3 ? 1.0f : 0.0f, t == 0 ? -1.0f : 0.0f);
+}
+// The rows behind each chunk (forward).
+template <bool RS>
 __device__ inline void write_dummies(float4* pd, int batch) {
-  constexpr int S = Slots<RS, BWD>::N;
-  for (int i = threadIdx.x; i < (batch + kChunk - 1) / kChunk * S; i += blockDim.x) {
-    const int t = i % S;
-    pd[((i / S + 1) * (kChunk + 1) - 1) * S + t] =
-        RS ? make_float4(t == 0 ? 1.0f : 0.0f, 0.0f, 0.0f, t == 2 ? -1.0f : 0.0f)
-           : make_float4(0.0f, 0.0f, t == 3 ? 1.0f : 0.0f, t == 0 ? -1.0f : 0.0f);
-  }
+  constexpr int S = Slots<RS, false>::N;
+  const int t = threadIdx.x;
+  if (t >= S) return;
+  const float4 d = dummy_slot<RS>(t);
+  for (int c = 1; c <= (batch + kChunk - 1) / kChunk; c++) pd[(c * (kChunk + 1) - 1) * S + t] = d;
 }
 
 // A wave's lists: of each of its blocks, the places in the chunk of the pairs
